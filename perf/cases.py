@@ -78,8 +78,8 @@ def draw(rng):
     kind = rng.choice(["gram", "gram", "gram", "loss", "solve", "mlp", "train", "features", "search", "rotinit",
                        "translation"])
     if kind in ("gram", "features"):
-        c = _draw_graph(rng, 20, 3000 if kind == "gram" else 600)
-        c["mean"] = round(math.exp(rng.uniform(math.log(60.0), math.log(1100.0))), 1)
+        c = _draw_graph(rng, 20, 1200 if kind == "gram" else 600)
+        c["mean"] = round(math.exp(rng.uniform(math.log(60.0), math.log(800.0))), 1)
         c["sizes"] = rng.choice(["lognormal", "powerlaw"])
         c["dtype"] = rng.choice(["f64", "f32", "bf16"])
     elif kind == "loss":
