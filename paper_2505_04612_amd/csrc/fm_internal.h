@@ -516,14 +516,58 @@ __device__ inline void row_sum6(double (&acc)[6], int lane) {
   for (int k = 0; k < 6; ++k) acc[k] = __shfl(v, base + 8 * (k / 3) + 2 * (k % 3));
 }
 
-// Wave-wide total of 6 per-lane sums, in every lane: the row reduction, the
-// four rows added, the gather.
-__device__ inline void wave_sum6(double (&acc)[6], int lane) {
-  double v = row_partial6(acc, lane);
+// Wave-wide totals of 6 per-lane sums and of a seventh (a loss):
+// reduce-scatter over lane
+// bits 3..1 (7 -> 4 -> 2 -> 1), the partner over bit 0 added, the four rows
+// added (fixed order); entry e ends in lanes 8 (e / 4) + 4 (e / 2 % 2) + 2 (e % 2) of every
+// row.  acc receives the six totals in every lane; the return value is the
+// seventh's total in lane kLossLane.
+constexpr int kLossLane = 12;
+__device__ inline double wave_sum6_loss(double (&acc)[6], double loss, int lane) {
+  const double in[7] = {acc[0], acc[1], acc[2], acc[3], acc[4], acc[5], loss};
+  double b4[4], b2[2], b1[1];
+  rs_stage_d<7, 3>(in, b4, lane);
+  rs_stage_d<4, 2>(b4, b2, lane);
+  rs_stage_d<2, 1>(b2, b1, lane);
+  double v = b1[0] + dpp_mov_d<0xB1>(b1[0]);   // quad_perm xor 1
   v += __shfl_xor(v, 16);
   v += __shfl_xor(v, 32);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) acc[k] = __shfl(v, 8 * (k / 3) + 2 * (k % 3));
+  for (int k = 0; k < 6; ++k) acc[k] = __shfl(v, 8 * (k / 4) + 4 * (k / 2 % 2) + 2 * (k % 2));
+  return v;
+}
+
+// Loss trace of the fused epipolar loops.  Every iteration leaves `slots`
+// partial losses in row k % (2 kTraceBatch) of `part`; the rows of
+// kTraceBatch iterations are then summed together after the barrier that
+// ends the last of them, one wavefront per iteration, lanes over the slots.
+// (One thread summing each iteration's partials in turn costs a chain of
+// loads past the caches on the loop's critical path: 100 traced iterations
+// took 1,070 us on the 200-camera helix graph and 3,528 us on the
+// 5,000-camera street graph, against 585 and 2,213 us so.)  A batch's rows are
+// rewritten one batch later, when every workgroup has passed barriers that
+// its reader reached after reading.
+constexpr int kTraceBatch = 16;
+
+__device__ inline double* trace_row(double* part, int64_t slots, int k) {
+  return part + (int64_t)(k % (2 * kTraceBatch)) * slots;
+}
+
+// After the barrier of iteration k: the batch it ends, if it ends one (every
+// kTraceBatch iterations, and at the launch's last, K - 1).
+__device__ inline void trace_batch(double* part, int64_t slots, int k, int K, double scale, double* __restrict__ trace,
+                                   int64_t gwave, int64_t nwaves, int lane) {
+  if ((k + 1) % kTraceBatch != 0 && k + 1 != K) return;
+  const int k0 = k - k % kTraceBatch;
+  for (int64_t g = k0 + gwave; g <= k; g += nwaves) {
+    const double* p = trace_row(part, slots, (int)g);
+    double s = 0.0;
+#pragma unroll 4
+    for (int64_t q = lane; q < slots; q += 64) s += p[q];
+#pragma unroll
+    for (int sh = 32; sh >= 1; sh >>= 1) s += __shfl_xor(s, sh);
+    if (lane == 0) trace[g] = s * scale;
+  }
 }
 
 // A camera's summed body-frame rotation gradient om (sums of its pairs'

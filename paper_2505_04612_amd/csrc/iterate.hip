@@ -468,14 +468,12 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
     const double v = pair_phase_slots<WT>(a.params, k > 0 ? a.rot : nullptr, a.cams, a.pair_slot, W36, a.P,
                                                 2.0 * iz, a.contrib, gtid, gsize, ci0, cj0, ci1, cj1, qi0, qj0, qi1,
                                                 qj1);
-    const double t = block_sum(v, lds);
-    if (threadIdx.x == 0) a.loss_part[blockIdx.x] = t;
-    loop_sync<XS>(gb, xs);
-    if (a.loss_trace && gtid == 0) {
-      double s = 0.0;
-      for (int b = 0; b < (int)gridDim.x; ++b) s += a.loss_part[b];
-      a.loss_trace[k] = s * iz;
+    if (a.loss_trace) {
+      const double t = block_sum(v, lds);
+      if (threadIdx.x == 0) trace_row(a.loss_part, gridDim.x, k)[blockIdx.x] = t;
     }
+    loop_sync<XS>(gb, xs);
+    if (a.loss_trace) trace_batch(a.loss_part, gridDim.x, k, a.K, iz, a.loss_trace, gwave, nwaves, lane);
     const double frac = sch.frac;
     const double bc1 = 1.0 - sch.p1, bc2 = 1.0 - sch.p2;
     sch.next();
@@ -558,7 +556,7 @@ struct CamSolveArgs {
   const int32_t* cam_ptr;
   const int32_t* cam_items;
   double* rot;         // [2, N, 9]
-  double* loss_part;   // [2, gridDim.x]
+  double* loss_part;   // [2 kTraceBatch, min(N, wavefronts)]
   double* loss_trace;
   unsigned* bar;
   const int64_t* Z_dev;
@@ -610,7 +608,6 @@ __device__ inline void cam_store_rot(double* __restrict__ rot, int64_t c, float 
 
 template <typename WT, bool XS>
 __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
-  __shared__ double lds[kCamBlock / 64];
   const double iz = a.Z_dev ? 1.0 / (double)(*a.Z_dev > 0 ? *a.Z_dev : 1) : a.inv_Z;
   const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
@@ -619,6 +616,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
   const int kq = lane < 9 ? lane : 8;
   const WT* W36 = reinterpret_cast<const WT*>(a.W36);
   const int64_t NR = (int64_t)a.N * 9;
+  const int64_t slots = nwaves < a.N ? nwaves : a.N;   // wavefronts with a camera
   // static data of the first 64 incidence entries of this wavefront's first
   // camera (one per lane: the pair, the camera's side, both cameras), read
   // once, so that each iteration's loads of that pass (poses, rotations,
@@ -669,7 +667,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
     const double frac = sch.frac;
     const double bc1 = 1.0 - sch.p1, bc2 = 1.0 - sch.p2;
     sch.next();
-    double lsum = 0.0;
+    double lwave = 0.0;   // in lane kLossLane: the wavefront's loss
     // the loop bound is uniform over the wavefront, so the wavefront sums
     // run with every lane present
     for (int64_t c = gwave; c < a.N; c += nwaves) {
@@ -698,7 +696,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
       }
       // this camera's side of each of its pairs: body-frame rotation
       // gradient (om for camera j, -om for camera i) and dL/dt
-      double acc6[6], acc[12];
+      double acc6[6], acc[12], lsum = 0.0;
 #pragma unroll
       for (int j = 0; j < 6; ++j) acc6[j] = 0.0;
       for (int q = lo + lane; q < hi; q += 64) {
@@ -716,7 +714,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
           acc6[3 + j] += (double)(float)(side ? dtj[j] : dti[j]);
         }
       }
-      wave_sum6(acc6, lane);
+      lwave += wave_sum6_loss(acc6, lsum, lane);
       omega_grad(f, acc6, acc6 + 3, acc);
       gs_adjoint(acc, f, a2, g);
       const double lr = (lane < 6 ? a.lr_rot : a.lr_t) * frac;
@@ -744,24 +742,18 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
         cam_store_rot<!XS>(rw, c, pq, lane);
       }
     }
-    if (a.loss_trace) {
-      const double t = block_sum(lsum, lds);
-      if (threadIdx.x == 0) {
-        if constexpr (XS)
-          a.loss_part[rb * gridDim.x + blockIdx.x] = t;
-        else
-          store_wt(&a.loss_part[rb * gridDim.x + blockIdx.x], t);
-      }
+    if (a.loss_trace && lane == kLossLane && gwave < slots) {
+      double* lp = trace_row(a.loss_part, slots, k) + gwave;
+      if constexpr (XS)
+        *lp = lwave;
+      else
+        store_wt(lp, lwave);
     }
     if constexpr (XS)
       grid_sync(a.bar, xs);
     else
       grid_barrier_wt(gb);
-    if (a.loss_trace && gtid == 0) {
-      double sum = 0.0;
-      for (int b = 0; b < (int)gridDim.x; ++b) sum += a.loss_part[rb * gridDim.x + b];
-      a.loss_trace[k] = sum * iz;
-    }
+    if (a.loss_trace) trace_batch(a.loss_part, slots, k, a.K, iz, a.loss_trace, gwave, nwaves, lane);
   }
   // the first camera's moments, kept in registers during the launch
   if (own && lane < 9) {
@@ -850,7 +842,8 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   if (cfg->blocks > 0) want = cfg->blocks;
   if (want < 1) want = 1;
   if (want > s->coop_blocks) want = s->coop_blocks;
-  if (want > s->loss_part_cap) return fm_fail(ctx, FM_ECOOP, "fm_epipolar_solve: loss workspace too small");
+  if (2 * kTraceBatch * want > s->loss_part_cap)
+    return fm_fail(ctx, FM_ECOOP, "fm_epipolar_solve: loss workspace too small");
   SolveArgs a;
   a.params = params; a.m = m; a.v = v;
   a.cams = s->pair_cams; a.W36 = W36; a.cam_ptr = s->cam_ptr; a.cam_items = s->cam_items;
@@ -869,7 +862,8 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   // or a larger graph runs the pair loop
   int64_t want_cam = grid_for((int64_t)s->N * 64, kCamBlock);
   if (want_cam > s->coop_blocks_cam) want_cam = s->coop_blocks_cam;
-  if ((cfg->blocks < 0 || (cfg->blocks == 0 && s->P < kCamLoopMaxPairs)) && 2 * want_cam <= s->loss_part_cap) {
+  if ((cfg->blocks < 0 || (cfg->blocks == 0 && s->P < kCamLoopMaxPairs)) &&
+      2 * kTraceBatch * want_cam * (kCamBlock / 64) <= s->loss_part_cap) {
     CamSolveArgs ca;
     ca.params = params; ca.params_alt = s->params_alt; ca.m = m; ca.v = v;
     ca.cams = s->pair_cams; ca.W36 = W36; ca.cam_ptr = s->cam_ptr; ca.cam_items = s->cam_items;

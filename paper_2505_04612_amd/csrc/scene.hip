@@ -468,8 +468,10 @@ extern "C" fm_status fm_scene_create(fm_ctx* ctx, int64_t P, int64_t M, int32_t 
     return fm_fail(ctx, FM_ECOOP, "cannot size the cooperative solve kernel");
   }
   s->loss_part_cap = (int64_t)grid_for(P, kBlock);   // also covers k_pair_phase's blocks
-  if (s->loss_part_cap < (int64_t)s->coop_blocks) s->loss_part_cap = s->coop_blocks;
-  if (s->loss_part_cap < 2 * (int64_t)s->coop_blocks_cam) s->loss_part_cap = 2 * (int64_t)s->coop_blocks_cam;   // the camera loop double-buffers its partials
+  // the fused epipolar loops' trace rows: one slot per workgroup (pair loop)
+  // or per wavefront (camera loop)
+  const int64_t slots = std::max<int64_t>(s->coop_blocks, (int64_t)s->coop_blocks_cam * (kCamBlock / 64));
+  if (s->loss_part_cap < 2 * kTraceBatch * slots) s->loss_part_cap = 2 * kTraceBatch * slots;
   SCENE_TRY(hipMalloc(&s->partials, sizeof(float) * 36 * (s->n_partials > 0 ? s->n_partials : 1)));
   SCENE_TRY(hipMalloc(&s->ess, sizeof(double) * 9 * (P > 0 ? P : 1)));
   SCENE_TRY(hipMalloc(&s->contrib, sizeof(float) * 24 * (P > 0 ? P : 1)));
