@@ -131,7 +131,7 @@ struct fm_scene {
   int32_t* pair_slot = nullptr;   // [2P] position of item 2*pair + side in cam_items
   // workspace
   float* partials = nullptr;      // [n_big, 36]
-  double* ess = nullptr;          // [P, 9] essential matrices (reweight)
+  double* ess = nullptr;          // [P, 12] essential matrices (reweight: rows of 9) or relative poses (features: rows of 12)
   float* contrib = nullptr;       // [P, 24] per-pair gradient records
   float* fo_rec = nullptr;        // [P, 2] per-pair focal-scale gradient records (side i, side j)
   double* loss_part = nullptr;    // [loss_part_cap]
@@ -164,6 +164,8 @@ fm_status fm_check_finite(fm_ctx* ctx, hipStream_t st, const void* p, int64_t n,
 // E_n of every pair at `params` into the scene's workspace (gram.hip); in
 // check mode it also flags degenerate pairs and non-finite parameters.
 fm_status fm_launch_essentials(fm_scene* s, const float* params, hipStream_t st);
+// The same, leaving each pair's (R_ij, t_hat) [P, 12] there instead.
+fm_status fm_launch_pair_poses(fm_scene* s, const float* params, hipStream_t st);
 
 // Error reporting helpers: set ctx->err and return the status.
 fm_status fm_fail(fm_ctx* ctx, fm_status st, const char* fmt, ...);

@@ -406,10 +406,12 @@ __global__ __launch_bounds__(kBlock) void k_check_coords(const void* __restrict_
 }
 
 // E_n for every pair at the given poses (float64), for the residual pass.
-// In check mode (flag != NULL) a pair whose |t_ij| is at most 1e-7 of
+// POSE: instead of E_n [9], the relative pose (R_ij row-major, t_hat) [12]
+// that the feature pass reads.  In check mode (flag != NULL) a pair whose |t_ij| is at most 1e-7 of
 // |t_i| + |t_j| (below the resolution of float32 parameters, so its direction
 // is rounding noise; exactly 0 included) or whose E_n is not finite (from
 // non-finite parameters) is flagged.
+template <bool POSE>
 __global__ void k_pair_essentials(const float* __restrict__ params, const int32_t* __restrict__ cams,
                                   int64_t P, double* __restrict__ ess, unsigned* __restrict__ flag) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -431,10 +433,13 @@ __global__ void k_pair_essentials(const float* __restrict__ params, const int32_
     if (!fin) bits |= FM_CHECK_PARAMS;
     if (bits) atomicOr(flag, bits);
   }
+  constexpr int kRow = POSE ? 12 : 9;
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+  for (int a = 0; a < 3; ++a) {
 #pragma unroll
-    for (int b = 0; b < 3; ++b) ess[n * 9 + 3 * a + b] = E[a][b];
+    for (int b = 0; b < 3; ++b) ess[n * kRow + 3 * a + b] = POSE ? Rij[a][b] : E[a][b];
+    if constexpr (POSE) ess[n * kRow + 9 + a] = th[a];
+  }
 }
 
 // ------------------------------------------------------------------ host side
@@ -481,17 +486,22 @@ static fm_status launch_finalize(fm_scene* s, double* W64, float* W32, int64_t* 
   return FM_OK;
 }
 
+template <bool POSE>
 static fm_status launch_essentials(fm_scene* s, const float* params, hipStream_t st) {
   fm_timed timer(s->ctx, FM_K_ESSENTIALS, st, true);
-  hipExtLaunchKernelGGL(k_pair_essentials, dim3(grid_for(s->P > 0 ? s->P : 1, kBlock)), dim3(kBlock), 0, st, timer.a,
-                        timer.b, 0, params, (const int32_t*)s->pair_cams, s->P, s->ess,
+  hipExtLaunchKernelGGL(k_pair_essentials<POSE>, dim3(grid_for(s->P > 0 ? s->P : 1, kBlock)), dim3(kBlock), 0, st,
+                        timer.a, timer.b, 0, params, (const int32_t*)s->pair_cams, s->P, s->ess,
                         s->ctx->check ? s->ctx->check_flag : nullptr);
   FM_CHECK_LAUNCH(s->ctx);
   return FM_OK;
 }
 
 fm_status fm_launch_essentials(fm_scene* s, const float* params, hipStream_t st) {
-  return launch_essentials(s, params, st);
+  return launch_essentials<false>(s, params, st);
+}
+
+fm_status fm_launch_pair_poses(fm_scene* s, const float* params, hipStream_t st) {
+  return launch_essentials<true>(s, params, st);
 }
 
 // Check mode: one extra pass over the stored coordinates.
@@ -553,7 +563,7 @@ extern "C" fm_status fm_reweight(fm_ctx* ctx, fm_scene* s, const float* params, 
   hipStream_t st = (hipStream_t)stream;
   if ((rc = launch_check_coords(s, st)) != FM_OK) return rc;
   fm_timed call(ctx, FM_K_GRAM_CALL, st);
-  if ((rc = launch_essentials(s, params, st)) != FM_OK) return rc;
+  if ((rc = launch_essentials<false>(s, params, st)) != FM_OK) return rc;
   if ((rc = launch_pass<W_IRLS, false, true>(s, nullptr, delta, tau, nullptr, nullptr, w_out, r_out, st)) != FM_OK)
     return rc;
   return launch_finalize(s, nullptr, nullptr, kept, st);
@@ -568,7 +578,7 @@ extern "C" fm_status fm_reweight_build(fm_ctx* ctx, fm_scene* s, const float* pa
   hipStream_t st = (hipStream_t)stream;
   if ((rc = launch_check_coords(s, st)) != FM_OK) return rc;
   fm_timed call(ctx, FM_K_GRAM_CALL, st);
-  if ((rc = launch_essentials(s, params, st)) != FM_OK) return rc;
+  if ((rc = launch_essentials<false>(s, params, st)) != FM_OK) return rc;
   if ((rc = launch_pass<W_IRLS, true, false>(s, nullptr, delta, tau, W64, W32, nullptr, nullptr, st)) != FM_OK)
     return rc;
   return launch_finalize(s, W64, W32, kept, st);

@@ -353,64 +353,126 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_mlp_reduce(const float* __re
 
 // ------------------------------------------------------------------ features
 
+// A constant held in scalar registers: a polynomial step then is one v_fma_f64
+// with a scalar addend, instead of a copy of the constant into the
+// accumulator and a v_fmac_f64.
+__device__ inline double in_sgpr(double c) {
+  asm("" : "+s"(c));
+  return c;
+}
+
+// Reciprocal of a normal double by one Newton step on the hardware estimate
+// (2^-23 or better), relative error below 1e-13: the features are rounded to
+// float32.
+__device__ inline double rcp_newton(double d) {
+  const double r = __builtin_amdgcn_rcp(d);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+
+// log x for x > 0 (+inf included), relative error below 1e-12: x = 2^e m with
+// m in [1/sqrt 2, sqrt 2), log m = 2 atanh(s), s = (m - 1)/(m + 1), as s times
+// the degree-5 polynomial in s^2 that interpolates 2 atanh(s)/s at the
+// Chebyshev nodes of [0, 0.02944] (2.7e-14).
+__device__ inline float log_f32(double x) {
+  double m = __builtin_amdgcn_frexp_mant(x);
+  int e = __builtin_amdgcn_frexp_exp(x);
+  const bool low = m < 0.70710678118654752;
+  m = low ? m + m : m;
+  e -= low ? 1 : 0;
+  const double s = (m - 1.0) * rcp_newton(m + 1.0), z = s * s;
+  double q = in_sgpr(0.19608097136405317);
+  q = fma(q, z, in_sgpr(0.22174249811019753));
+  q = fma(q, z, in_sgpr(0.2857216614814168));
+  q = fma(q, z, in_sgpr(0.39999994891811563));
+  q = fma(q, z, in_sgpr(0.6666666667957932));
+  q = fma(q, z, in_sgpr(1.9999999999999472));
+  const float r = (float)fma((double)e, 0.69314718055994531, s * q);
+  return __builtin_isinf(x) ? INFINITY : r;
+}
+
+// atan2(sqrt(y2), x) for y2 >= 0, relative error below 1e-12: the octant's
+// ratio t = min/max, reduced by atan t = pi/4 + atan((t - 1)/(t + 1)) above
+// tan(pi/8) (numerator and denominator, so one reciprocal serves both), then
+// z P(z^2) with the degree-7 polynomial that interpolates atan(z)/z at the
+// Chebyshev nodes of [0, tan^2(pi/8)] (7.6e-13).
+__device__ inline float angle_f32(double y2, double x) {
+  // sqrt(y2) by one step on the reciprocal square root's estimate
+  const double c = fmax(y2, 1e-300), h = __builtin_amdgcn_rsq(c), t0 = c * h;
+  const double y = fma(0.5 * t0, fma(-t0, h, 1.0), t0);
+  const double ax = fabs(x), mn = fmin(y, ax), mx = fmax(y, ax);
+  const bool big = mn > 0.41421356237309505 * mx;
+  const double num = big ? mn - mx : mn, den = big ? mn + mx : mx;
+  const double z = num * rcp_newton(den), w = z * z;
+  double q = in_sgpr(-0.03765508568903965);
+  q = fma(q, w, in_sgpr(0.06974196550225259));
+  q = fma(q, w, in_sgpr(-0.08992552657899722));
+  q = fma(q, w, in_sgpr(0.11103456882226026));
+  q = fma(q, w, in_sgpr(-0.14285386552286725));
+  q = fma(q, w, in_sgpr(0.1999999305351789));
+  q = fma(q, w, in_sgpr(-0.3333333327692213));
+  q = fma(q, w, in_sgpr(0.9999999999992447));
+  double a = fma(z, q, big ? 0.78539816339744831 : 0.0);
+  a = y > ax ? 1.5707963267948966 - a : a;
+  a = x < 0.0 ? 3.1415926535897931 - a : a;
+  // a quotient of non-finite terms stays NaN (fmin and fmax drop one)
+  return (float)(isnan(y2) || isnan(x) ? NAN : a);
+}
+
+struct __attribute__((packed, aligned(4))) Feat3 {
+  float f0, f1, f2;
+};
+
 // Per match: f0 = log max(|r|, delta) with r = x2~^T E_n x1~ (float64),
 // f1 = log |Q_n|, f2 = angle between R_i^T x1~ and R_j^T x2~.  One wavefront
-// per Gram work item; E_n comes from the per-pair essentials pass.
+// per 1,024-match work item, one match per lane and row.  From the pair's
+// relative pose alone: with a = R_ij x1~ (the angle is that between a and
+// x2~) and c = a x x2~, r = t_hat . c and the angle is atan2(|c|, a . x2~), 18
+// float64 operations.  Bound by float64 VALU issue (~75 operations per match,
+// 12 bytes out and 8 to 32 in): the library log, atan2 and sqrt with the
+// rotations per wavefront and a search for the wavefront's pair: 81 us a call
+// over 4.9M bfloat16 matches, this 36 us (20 us at the copy rate).
 template <int DT>
 __global__ __launch_bounds__(256) void k_features(const void* __restrict__ uv, const int64_t* __restrict__ off,
-                                                  const int64_t* __restrict__ wi_off, int64_t P, int64_t n_wi,
-                                                  const int32_t* __restrict__ cams, const float* __restrict__ params,
-                                                  const double* __restrict__ ess, double delta,
+                                                  const int64_t* __restrict__ wi_off,
+                                                  const int32_t* __restrict__ wi_pair, int64_t n_wi,
+                                                  const double* __restrict__ pose, double delta,
                                                   float* __restrict__ feats) {
   const int lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  // wave-uniform, so that the pair's data are scalar loads
+  const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= n_wi) return;
-  int64_t lo = 0, hi = P;
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (wi_off[mid] <= w) lo = mid; else hi = mid;
-  }
-  const int64_t n = lo;
+  const int64_t n = wi_pair[w];
   const int64_t start = off[n] + (w - wi_off[n]) * kChunk;
   const int64_t stop = min(off[n + 1], start + kChunk);
   const float f1 = logf((float)(off[n + 1] - off[n]));
-  double E[9];
+  double R[9], th[3];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) E[k] = ess[n * 9 + k];
-  double a1[3], a2[3], t[3], Ri[3][3], Rj[3][3];
-  load_pose(params, cams[2 * n], a1, a2, t);
-  gs_matrix(gs_forward(a1, a2), Ri);
-  load_pose(params, cams[2 * n + 1], a1, a2, t);
-  gs_matrix(gs_forward(a1, a2), Rj);
+  for (int k = 0; k < 9; ++k) R[k] = pose[n * 12 + k];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) th[k] = pose[n * 12 + 9 + k];
   for (int64_t m = start + lane; m < stop; m += kLanes) {
-    double x[4];
+    double u1, v1, u2, v2;
     if constexpr (DT == FM_F32) {
       const float4 v = reinterpret_cast<const float4*>(uv)[m];
-      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+      u1 = v.x; v1 = v.y; u2 = v.z; v2 = v.w;
     } else if constexpr (DT == FM_BF16) {
       const uint2 v = reinterpret_cast<const uint2*>(uv)[m];
-      x[0] = __uint_as_float(v.x << 16); x[1] = __uint_as_float(v.x & 0xffff0000u);
-      x[2] = __uint_as_float(v.y << 16); x[3] = __uint_as_float(v.y & 0xffff0000u);
+      u1 = __uint_as_float(v.x << 16); v1 = __uint_as_float(v.x & 0xffff0000u);
+      u2 = __uint_as_float(v.y << 16); v2 = __uint_as_float(v.y & 0xffff0000u);
     } else {
       const double2* d = reinterpret_cast<const double2*>(uv) + 2 * m;
-      x[0] = d[0].x; x[1] = d[0].y; x[2] = d[1].x; x[3] = d[1].y;
+      const double2 p = d[0], q = d[1];
+      u1 = p.x; v1 = p.y; u2 = q.x; v2 = q.y;
     }
-    const double e0 = E[0] * x[0] + E[1] * x[1] + E[2];
-    const double e1 = E[3] * x[0] + E[4] * x[1] + E[5];
-    const double e2 = E[6] * x[0] + E[7] * x[1] + E[8];
-    const double res = fabs(x[2] * e0 + x[3] * e1 + e2);
-    double ra[3], rb[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      ra[c] = Ri[0][c] * x[0] + Ri[1][c] * x[1] + Ri[2][c];
-      rb[c] = Rj[0][c] * x[2] + Rj[1][c] * x[3] + Rj[2][c];
-    }
-    const double cx = ra[1] * rb[2] - ra[2] * rb[1], cy = ra[2] * rb[0] - ra[0] * rb[2],
-                 cz = ra[0] * rb[1] - ra[1] * rb[0];
-    const double dotp = ra[0] * rb[0] + ra[1] * rb[1] + ra[2] * rb[2];
-    feats[m * 3 + 0] = (float)log(res > delta ? res : delta);
-    feats[m * 3 + 1] = f1;
-    feats[m * 3 + 2] = (float)atan2(sqrt(cx * cx + cy * cy + cz * cz), dotp);
+    const double a0 = fma(R[0], u1, fma(R[1], v1, R[2])), a1 = fma(R[3], u1, fma(R[4], v1, R[5])),
+                 a2 = fma(R[6], u1, fma(R[7], v1, R[8]));
+    const double c0 = fma(-a2, v2, a1), c1 = fma(a2, u2, -a0), c2 = fma(a0, v2, -a1 * u2);
+    const double res = fabs(fma(th[0], c0, fma(th[1], c1, th[2] * c2)));
+    Feat3 f;
+    f.f0 = log_f32(res > delta ? res : delta);
+    f.f1 = f1;
+    f.f2 = angle_f32(fma(c0, c0, fma(c1, c1, c2 * c2)), fma(a0, u2, fma(a1, v2, a2)));
+    reinterpret_cast<Feat3*>(feats)[m] = f;
   }
 }
 
@@ -498,21 +560,21 @@ extern "C" fm_status fm_match_features(fm_ctx* ctx, fm_scene* s, const float* pa
   if (!(delta > 0.0f)) return fm_fail(ctx, FM_EINVAL, "fm_match_features: delta must be > 0");
   FM_HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
-  fm_status rc = fm_launch_essentials(s, params, st);
+  fm_status rc = fm_launch_pair_poses(s, params, st);
   if (rc != FM_OK || s->n_wi == 0) return rc;
   const dim3 grid(grid_for(s->n_wi, 4)), block(256);
   switch (s->dtype) {
     case FM_F32:
-      hipLaunchKernelGGL(k_features<FM_F32>, grid, block, 0, st, s->uv, s->offsets, s->wi_off, s->P, s->n_wi,
-                         s->pair_cams, params, s->ess, (double)delta, feats);
+      hipLaunchKernelGGL(k_features<FM_F32>, grid, block, 0, st, s->uv, s->offsets, s->wi_off, s->wi_pair, s->n_wi,
+                         s->ess, (double)delta, feats);
       break;
     case FM_BF16:
-      hipLaunchKernelGGL(k_features<FM_BF16>, grid, block, 0, st, s->uv, s->offsets, s->wi_off, s->P, s->n_wi,
-                         s->pair_cams, params, s->ess, (double)delta, feats);
+      hipLaunchKernelGGL(k_features<FM_BF16>, grid, block, 0, st, s->uv, s->offsets, s->wi_off, s->wi_pair, s->n_wi,
+                         s->ess, (double)delta, feats);
       break;
     default:
-      hipLaunchKernelGGL(k_features<FM_F64>, grid, block, 0, st, s->uv, s->offsets, s->wi_off, s->P, s->n_wi,
-                         s->pair_cams, params, s->ess, (double)delta, feats);
+      hipLaunchKernelGGL(k_features<FM_F64>, grid, block, 0, st, s->uv, s->offsets, s->wi_off, s->wi_pair, s->n_wi,
+                         s->ess, (double)delta, feats);
       break;
   }
   FM_CHECK_LAUNCH(ctx);

@@ -473,7 +473,7 @@ extern "C" fm_status fm_scene_create(fm_ctx* ctx, int64_t P, int64_t M, int32_t 
   const int64_t slots = std::max<int64_t>(s->coop_blocks, (int64_t)s->coop_blocks_cam * (kCamBlock / 64));
   if (s->loss_part_cap < 2 * kTraceBatch * slots) s->loss_part_cap = 2 * kTraceBatch * slots;
   SCENE_TRY(hipMalloc(&s->partials, sizeof(float) * 36 * (s->n_partials > 0 ? s->n_partials : 1)));
-  SCENE_TRY(hipMalloc(&s->ess, sizeof(double) * 9 * (P > 0 ? P : 1)));
+  SCENE_TRY(hipMalloc(&s->ess, sizeof(double) * 12 * (P > 0 ? P : 1)));
   SCENE_TRY(hipMalloc(&s->contrib, sizeof(float) * 24 * (P > 0 ? P : 1)));
   SCENE_TRY(hipMalloc(&s->fo_rec, sizeof(float) * 2 * (P > 0 ? P : 1)));
   SCENE_TRY(hipMalloc(&s->loss_part, sizeof(double) * s->loss_part_cap));
