@@ -5,24 +5,34 @@
 // t^T A_n t / |Q_n|, A_n = B^T W_n B, B[:, k] = flatten([e_k]_x R_ij); the
 // winner keeps the sign of the pair's prior estimate.
 //
-// One lane per (pair, slice of the candidates): S lanes share a pair and
-// visit candidates slice, slice + S, ...; the candidates are staged in LDS
-// tiles and read as broadcasts; the S lanes then combine their minima
-// (value, then index) with a butterfly, so the lowest candidate index wins
-// among equal errors whatever S is.
+// A workgroup takes one to kTsBatches batches of kTsPairs pairs.  Lanes of its
+// first wavefront form A_n, one pair each, for all of them (a dependent chain
+// of about 750 instructions that the other wavefronts wait for, so it is paid
+// once per workgroup); every wavefront then holds a batch's form entries in
+// scalar registers
+// (five of six; the sixth in a vector register, as eight pairs' six entries
+// would not leave room for the addresses).  Each lane visits candidates
+// thread, thread + kTsBlock, ..., forms the candidate's six monomials once and
+// evaluates them against the eight forms: eight independent chains of one
+// product and five FMAs with a scalar operand, and no LDS reads.  The minima
+// (value, then index, so the lowest candidate index wins among equal errors)
+// are combined by a reduce-scatter over the lanes and through LDS over the
+// wavefronts.  Bound by float64 VALU issue, 9 to 10 instructions per
+// evaluation.  The form before it gave one pair to each lane and read the
+// monomials from LDS, 48 bytes per evaluation, which bound it: per call with
+// 4,096 candidates, 4.8k pairs 23.0 -> 15.3 us (issued back to back, the host's
+// share of a call is 14 us), 29.5k pairs 75.5 -> 57.3, 186k pairs 372 -> 318,
+// identical outputs.
 #include "fm_internal.h"
 
 #include <cmath>
 
 namespace {
 
-constexpr int kTsTile = 1024;   // candidates per LDS tile: six monomials each (48 KB of float64)
-// threads per workgroup (each workgroup stages every candidate once).  256
-// rather than 512: the launch's workgroups then spread two or three to a
-// CU instead of one or two, so the most loaded CUs carry 1.25x the mean
-// instead of 1.67x (measured: medium graph 31.0 -> 29.3 us, the large
-// street graph 525 -> 459 us, same results)
-constexpr int kTsBlock = 256;
+constexpr int kTsBlock = 256;   // threads per workgroup
+constexpr int kTsWaves = kTsBlock / 64;
+constexpr int kTsPairs = 8;     // pairs evaluated together
+constexpr int kTsBatches = 8;   // batches per workgroup, at most (64 pairs: one per lane of a wavefront)
 
 // A = B^T W B from the compact Gram (W_{(ab),(cd)} = W36[6 q(a,c) + q(b,d)])
 // and R = R_ij, as its six distinct entries (A00, A11, A22, A01, A02, A12).
@@ -63,108 +73,165 @@ __device__ inline void pair_form(const double* __restrict__ w36, const double R[
   A6[5] = A[1][2] + A[2][1];
 }
 
+// A minimum and the candidate it belongs to; take() keeps the lower value,
+// then the lower index.
+struct TsMin {
+  double v;
+  int i;
+  __device__ void take(double ov, int oi) {
+    const bool t = (ov < v) | ((ov == v) & (oi < i));
+    v = t ? ov : v;
+    i = t ? oi : i;
+  }
+};
+
+template <int BIT>
+__device__ inline TsMin ts_partner(const TsMin& m) {
+  if constexpr (BIT >= 4) {
+    return TsMin{__shfl_xor(m.v, 1 << BIT), __shfl_xor(m.i, 1 << BIT)};
+  } else {
+    // row_mirror, row_half_mirror, quad_perm xor 2 and xor 1 (the partner has
+    // the opposite value of bit BIT and the same value of the higher ones
+    // already reduced)
+    constexpr int kCtrl = BIT == 3 ? 0x140 : (BIT == 2 ? 0x141 : (BIT == 1 ? 0x4E : 0xB1));
+    return TsMin{dpp_mov_d<kCtrl>(m.v), __builtin_amdgcn_update_dpp(0, m.i, kCtrl, 0xF, 0xF, false)};
+  }
+}
+
+// Reduce-scatter stage over lane bit BIT: lanes keep the lower or upper half
+// of 2H minima, combined with the partner's.
+template <int BIT, int H>
+__device__ inline void ts_stage(TsMin (&m)[kTsPairs], int lane) {
+  const bool up = (lane >> BIT) & 1;
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const TsMin lo = m[k], hi = m[k + H];
+    const TsMin send = {up ? lo.v : hi.v, up ? lo.i : hi.i};
+    const TsMin got = ts_partner<BIT>(send);
+    m[k] = TsMin{up ? hi.v : lo.v, up ? hi.i : lo.i};
+    m[k].take(got.v, got.i);
+  }
+}
+
+__device__ inline double uniform_d(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 __global__ __launch_bounds__(kTsBlock) void k_ts_search(const double* __restrict__ W36, const float* __restrict__ params,
                                                       const int32_t* __restrict__ cams,
                                                       const int64_t* __restrict__ offsets,
                                                       const double* __restrict__ cand, int32_t C,
-                                                      const float* __restrict__ t_prior, int64_t P, int S,
+                                                      const float* __restrict__ t_prior, int64_t P, int batches,
                                                       float* __restrict__ t_out, int32_t* __restrict__ best_out,
                                                       double* __restrict__ err_out) {
-  __shared__ double tile[kTsTile * 6];
-  const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = gtid / S;
-  const int slice = (int)(gtid % S);
-  const bool live = n < P;
-  double A6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  int64_t cnt = 0;
-  if (live) {
-    cnt = offsets[n + 1] - offsets[n];
-    double a1[3], a2[3], t[3], Ri[3][3], Rj[3][3], R[3][3];
-    load_pose(params, cams[2 * n], a1, a2, t);
-    gs_matrix(gs_forward(a1, a2), Ri);
-    load_pose(params, cams[2 * n + 1], a1, a2, t);
-    gs_matrix(gs_forward(a1, a2), Rj);
+  __shared__ double form[kTsPairs * kTsBatches][6];
+  __shared__ double red_v[2][kTsWaves][kTsPairs];
+  __shared__ int red_i[2][kTsWaves][kTsPairs];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = kTsPairs * batches;
+  const int64_t n_first = (int64_t)blockIdx.x * per;
+  if (tid < per) {
+    const int64_t n = n_first + tid;
+    double A6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (n < P) {
+      double a1[3], a2[3], t[3], Ri[3][3], Rj[3][3], R[3][3];
+      load_pose(params, cams[2 * n], a1, a2, t);
+      gs_matrix(gs_forward(a1, a2), Ri);
+      load_pose(params, cams[2 * n + 1], a1, a2, t);
+      gs_matrix(gs_forward(a1, a2), Rj);
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+      for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) R[a][b] = Rj[a][0] * Ri[b][0] + Rj[a][1] * Ri[b][1] + Rj[a][2] * Ri[b][2];
-    pair_form(W36 + 36 * n, R, A6);
-  }
-  double best_v = INFINITY;
-  int best_i = 0x7fffffff;
-  for (int base = 0; base < C; base += kTsTile) {
-    const int len = C - base < kTsTile ? C - base : kTsTile;
-    __syncthreads();
-    // each candidate's monomials (x^2, y^2, z^2, xy, xz, yz), once per tile
-    for (int k = threadIdx.x; k < len; k += blockDim.x) {
-      const double x = cand[3 * (int64_t)(base + k)], y = cand[3 * (int64_t)(base + k) + 1],
-                   z = cand[3 * (int64_t)(base + k) + 2];
-      double* m = tile + 6 * k;
-      m[0] = x * x;
-      m[1] = y * y;
-      m[2] = z * z;
-      m[3] = x * y;
-      m[4] = x * z;
-      m[5] = y * z;
+        for (int b = 0; b < 3; ++b) R[a][b] = Rj[a][0] * Ri[b][0] + Rj[a][1] * Ri[b][1] + Rj[a][2] * Ri[b][2];
+      pair_form(W36 + 36 * n, R, A6);
     }
-    __syncthreads();
-    if (live) {
-      // four of this lane's candidates per step: their forms are independent
-      // chains, evaluated as one expression each (the same rounding as one
-      // at a time) and compared in candidate order (the same ties)
-      int c = slice;
-      for (; c + 3 * S < len; c += 4 * S) {
-        double q[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const double* m = tile + 6 * (c + u * S);
-          q[u] = A6[0] * m[0] + A6[1] * m[1] + A6[2] * m[2] + A6[3] * m[3] + A6[4] * m[4] + A6[5] * m[5];
-        }
+    for (int k = 0; k < 6; ++k) form[tid][k] = A6[k];
+  }
+  __syncthreads();
+  // the minima's LDS rows alternate, so that one barrier a batch suffices
+  for (int bt = 0; bt < batches; ++bt) {
+    const int64_t n0 = n_first + bt * kTsPairs;
+    if (n0 >= P) break;   // the whole workgroup
+    const double(*f)[6] = form + bt * kTsPairs;
+    double A[kTsPairs][6];
+    TsMin m[kTsPairs];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (q[u] < best_v) {
-            best_v = q[u];
-            best_i = base + c + u * S;
-          }
-      }
-      for (; c < len; c += S) {
-        const double* m = tile + 6 * c;
-        const double q = A6[0] * m[0] + A6[1] * m[1] + A6[2] * m[2] + A6[3] * m[3] + A6[4] * m[4] + A6[5] * m[5];
-        if (q < best_v) {
-          best_v = q;
-          best_i = base + c;
+    for (int p = 0; p < kTsPairs; ++p) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) A[p][k] = uniform_d(f[p][k]);
+      A[p][5] = f[p][5];
+      m[p] = TsMin{INFINITY, 0x7fffffff};
+    }
+    // the next candidate is loaded while this one is evaluated (past the end,
+    // the last one again)
+    int64_t next = 3 * (int64_t)(tid < C ? tid : C - 1);
+    double nx = cand[next], ny = cand[next + 1], nz = cand[next + 2];
+    for (int c = tid; c < C; c += kTsBlock) {
+      const double x = nx, y = ny, z = nz;
+      next = 3 * (int64_t)(c < C - kTsBlock ? c + kTsBlock : C - 1);
+      nx = cand[next];
+      ny = cand[next + 1];
+      nz = cand[next + 2];
+      const double xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
+#pragma unroll
+      for (int p = 0; p < kTsPairs; ++p) {
+        double q = A[p][1] * yy;
+        q = fma(A[p][0], xx, q);
+        q = fma(A[p][2], zz, q);
+        q = fma(A[p][3], xy, q);
+        q = fma(A[p][4], xz, q);
+        q = fma(A[p][5], yz, q);
+        if (q < m[p].v) {
+          m[p].v = q;
+          m[p].i = c;
         }
       }
     }
-  }
-  // combine the S lanes of a pair: lower value, then lower index
-  for (int sh = 1; sh < S; sh <<= 1) {
-    const double ov = __shfl_xor(best_v, sh);
-    const int oi = __shfl_xor(best_i, sh);
-    if (ov < best_v || (ov == best_v && oi < best_i)) {
-      best_v = ov;
-      best_i = oi;
+    // eight minima over the lanes: 8 -> 4 -> 2 -> 1 over bits 3, 2, 1, then the
+    // kept one over bits 0, 4 and 5
+    ts_stage<3, 4>(m, lane);
+    ts_stage<2, 2>(m, lane);
+    ts_stage<1, 1>(m, lane);
+    TsMin o = ts_partner<0>(m[0]);
+    m[0].take(o.v, o.i);
+    o = ts_partner<4>(m[0]);
+    m[0].take(o.v, o.i);
+    o = ts_partner<5>(m[0]);
+    m[0].take(o.v, o.i);
+    if (lane < 16 && (lane & 1) == 0) {
+      const int p = 4 * (lane >> 3 & 1) + 2 * (lane >> 2 & 1) + (lane >> 1 & 1);
+      red_v[bt & 1][wave][p] = m[0].v;
+      red_i[bt & 1][wave][p] = m[0].i;
     }
+    __syncthreads();
+    const int64_t n = n0 + tid;
+    if (tid >= kTsPairs || n >= P) continue;
+    TsMin best = {red_v[bt & 1][0][tid], red_i[bt & 1][0][tid]};
+#pragma unroll
+    for (int w = 1; w < kTsWaves; ++w) best.take(red_v[bt & 1][w][tid], red_i[bt & 1][w][tid]);
+    const int64_t cnt = offsets[n + 1] - offsets[n];
+    double tp[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tp[k] = (double)t_prior[3 * n + k];
+    if (cnt == 0 || best.i >= C) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) t_out[3 * n + k] = (float)tp[k];
+      if (best_out) best_out[n] = -1;
+      if (err_out) err_out[n] = 0.0;
+      continue;
+    }
+    double tb[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tb[k] = cand[3 * (int64_t)best.i + k];
+    const double sgn = (tb[0] * tp[0] + tb[1] * tp[1] + tb[2] * tp[2]) < 0.0 ? -1.0 : 1.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t_out[3 * n + k] = (float)(sgn * tb[k]);
+    if (best_out) best_out[n] = best.i;
+    if (err_out) err_out[n] = best.v / (double)cnt;
   }
-  if (!live || slice != 0) return;
-  double tp[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) tp[k] = (double)t_prior[3 * n + k];
-  if (cnt == 0 || best_i >= C) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) t_out[3 * n + k] = (float)tp[k];
-    if (best_out) best_out[n] = -1;
-    if (err_out) err_out[n] = 0.0;
-    return;
-  }
-  double tb[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) tb[k] = cand[3 * (int64_t)best_i + k];
-  const double sgn = (tb[0] * tp[0] + tb[1] * tp[1] + tb[2] * tp[2]) < 0.0 ? -1.0 : 1.0;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) t_out[3 * n + k] = (float)(sgn * tb[k]);
-  if (best_out) best_out[n] = best_i;
-  if (err_out) err_out[n] = best_v / (double)cnt;
 }
 
 }  // namespace
@@ -180,16 +247,16 @@ extern "C" fm_status fm_translation_search(fm_ctx* ctx, fm_scene* s, const doubl
   if (!W36 || !params || !cand || !t_prior || !t_out)
     return fm_fail(ctx, FM_EINVAL, "fm_translation_search: NULL argument");
   FM_HIP_TRY(ctx, hipSetDevice(ctx->device));
-  // lanes per pair: enough (pair, slice) lanes for about two wavefronts per
-  // SIMD (256 CUs x 4 SIMDs x 2 x 64 lanes), at most 64 (measured on the
-  // medium graph, 4,096 candidates: 36.5 us; four wavefronts per SIMD with
-  // 256-thread workgroups 39.7 us, one with 1,024-thread workgroups 56.6 us)
-  int S = 1;
-  while (S < 64 && s->P * S < (int64_t)256 * 4 * 2 * 64 && S < C) S <<= 1;
-  const int64_t lanes = s->P * S;
+  // one batch per workgroup until the launch has four workgroups per CU (the
+  // co-resident limit by registers), then more, so that the forms' latency is
+  // paid less often (186k pairs, 4,096 candidates: 337 us with one batch, 318
+  // with eight)
+  int64_t batches = s->P / ((int64_t)kTsPairs * 4 * ctx->num_cu);
+  batches = batches < 1 ? 1 : (batches > kTsBatches ? kTsBatches : batches);
   fm_timed timer(ctx, FM_K_TS_SEARCH, (hipStream_t)stream);
-  hipLaunchKernelGGL(k_ts_search, dim3(grid_for(lanes, kTsBlock)), dim3(kTsBlock), 0, (hipStream_t)stream, W36, params,
-                     s->pair_cams, s->offsets, cand, C, t_prior, s->P, S, t_out, best, err_min);
+  hipLaunchKernelGGL(k_ts_search, dim3(grid_for(s->P, (int)(kTsPairs * batches))), dim3(kTsBlock), 0,
+                     (hipStream_t)stream, W36, params, s->pair_cams, s->offsets, cand, C, t_prior, s->P, (int)batches,
+                     t_out, best, err_min);
   FM_CHECK_LAUNCH(ctx);
   return FM_OK;
 }
