@@ -153,7 +153,8 @@ struct fm_scene {
   int ra_coop_blocks = 0;         // max co-resident blocks of the rotation loop
   // rotation initialisation workspace (Lanczos basis), grown on demand
   int64_t lz_cap = 0;             // doubles held by lz
-  double* lz = nullptr;           // basis [m+1, 3N], work vector, dots, tridiagonal, Ritz coefficients
+  double* lz = nullptr;           // basis rows past the LDS, the current vector, partial dots and norms
+  int lz_lds = 0;                 // LDS bytes a workgroup may take
   int lz_coop_blocks = 0;         // max co-resident blocks of the Lanczos kernel
 };
 

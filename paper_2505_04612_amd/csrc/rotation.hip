@@ -6,6 +6,8 @@
 // each side of the pair dL/dR as 3x3 row-major and three unused entries), so
 // the camera side shares its row sums and Gram-Schmidt adjoint.  Parameters
 // are (a1, a2) per camera, [N, 6].
+#include <algorithm>
+
 #include "fm_internal.h"
 
 #include <cmath>
@@ -408,346 +410,564 @@ __global__ __launch_bounds__(kSolveBlock) void k_ra_solve_cam(RaCamArgs a) {
 // which is x^T A x = sum_n |x_j - Q x_i|^2; the second-column problem uses
 // alpha A + beta diag(u_c u_c^T) with alpha = 1/P, beta = 1/N and u the
 // first columns.  The smallest eigenvector comes from Lanczos with full
-// (twice applied) classical Gram-Schmidt reorthogonalisation, the smallest
-// eigenpair of the tridiagonal matrix (Sturm bisection, inverse iteration)
-// and the Ritz vector.
+// reorthogonalisation, the smallest eigenpair of the tridiagonal matrix
+// (multisection on the Sturm count, twisted factorisation) and the Ritz
+// vector.
+//
+// A step is a chain of grid-wide reductions, so what bounds it is the number of
+// grid barriers and the memory rounds between them.  Each workgroup owns the
+// rows of consecutive cameras and keeps its rows of the basis in LDS (what
+// does not fit, in memory); it forms its rows of the operator's image and the
+// partial dots with its basis rows (one barrier: the dots' partials), then
+// updates its rows and their norm (one barrier: the new vector and the norm's
+// partials).  Before the dots, the two terms known without a reduction are
+// taken off: beta_{k-1} q_{k-1} and, as the diagonal entry varies little from
+// step to step, alpha_{k-1} q_k.  One pass of classical Gram-Schmidt then
+// leaves the vector orthogonal to rounding unless its norm falls below half
+// of what it was (the Daniel-Gragg-Kaufman-Stewart test); only then a second
+// pass runs.  (With the image itself, whose q_k part is several times the
+// rest, a single pass loses orthogonality by that factor every step.)  Every
+// workgroup holds the tridiagonal matrix and finds its eigenpair itself, so
+// that needs no barrier.
+//
+// Both columns, against the form with two unconditional passes, the basis in
+// memory, seven barriers a step, and one thread's bisection and pivoted inverse
+// iteration every 10 steps: 200 cameras, 4,849 pairs 6.52 -> 1.08 ms; 1,000
+// cameras 38.3 -> 4.7; 5,000 cameras, 209k pairs 166.5 -> 12.9.
+
+constexpr int kLzBlock = 512;           // threads per workgroup
+constexpr int kLzWaves = kLzBlock / 64;
+constexpr int kLzMaxBlocks = 160;       // workgroups of the automatic grid, at most
+constexpr int kLzMisc = 64 + kLzBlock;  // doubles of small LDS scratch
+// Lanczos steps between convergence checks, and the relative residual
+// bound |beta_k s_k| / |T| below which the Ritz pair is taken as converged.
+constexpr int kLzCheck = 10;
+constexpr int kLzMaxSteps = 4096;
+constexpr double kLzTol = 1e-11;
+// Steps and rows per workgroup up to which a workgroup's vectors and
+// tridiagonal matrix stay in LDS (the LDS variant; the other one keeps all of
+// them in memory).
+constexpr int kLzLdsSteps = 1024;
+constexpr int kLzLdsRows = 3072;
 
 struct LzArgs {
   const int32_t* cams;
   const float* Rrel;
   const int32_t* cam_ptr;
   const int32_t* cam_items;
-  const double* start;   // [n]
-  const double* u;       // [n] or null (first columns for the second problem)
-  double* V;             // [m + 1, n]
-  double* w;             // [n]
-  double* h;             // [m + 1] dots of the current step
-  double* part;          // [waves] partial sums
-  double* alpha;         // [m]
-  double* beta;          // [m]
-  double* s;             // [m] Ritz coefficients; also [3m] scratch after it
-  double* out;           // [n] Ritz vector
-  double* info;          // [2]: Ritz value, steps taken
+  const double* start;   // [2, n]
+  double* V;             // [m + 1 - lv, n] basis rows past the LDS
+  double* wbuf;          // [n] the current vector before its scaling
+  double* part_h;        // [blocks, lz_hrow(m)] partial dots
+  double* part_n;        // [blocks, kLzWaves] partial squared norms
+  double* gws;           // [blocks, lz_work(rows, m)] (the memory variant)
+  float* params;         // [N, 6]
+  double* info;          // [4] or null: Ritz value and steps of each column
   unsigned* bar;
   int64_t n;
-  int32_t N;
-  int32_t m;
-  double op_alpha, op_beta;
+  int32_t N, m;
+  int32_t nc;            // cameras per workgroup
+  int32_t lv;            // basis vectors held in LDS
+  double inv_P, inv_N;
 };
 
-// Sum over the grid of one double per thread, returned in every thread
-// (per-wavefront sums, then every workgroup adds them in the same order).
-__device__ inline double grid_allsum(double v, double* part, double* lds1, GridBar& gb, int64_t gwave, int64_t nwaves) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
-  if ((threadIdx.x & 63) == 0) part[gwave] = v;
-  grid_barrier(gb);
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int64_t k = 0; k < nwaves; ++k) t += part[k];
-    lds1[0] = t;
+// Row of a workgroup's partial dots: whole 128-byte lines, so that workgroups
+// on different XCDs never write to the same one.
+__host__ __device__ inline int64_t lz_hrow(int64_t m) { return (m + 2 + 15) / 16 * 16; }
+
+// Doubles of one workgroup's vectors and tridiagonal matrix.
+__host__ __device__ inline int64_t lz_work(int64_t rows, int64_t m) { return 3 * rows + 5 * m; }
+
+// Reciprocal by two Newton steps on the hardware estimate (about an ulp).
+__device__ inline double lz_rcp(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+
+// The value of lane `src` of every lane (uniform).
+__device__ inline double lane_d(double v, int src) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, src), hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Wave-wide reductions, the same in every lane: DPP inside the 16-lane rows,
+// then the four rows' values by lane reads (short chains: both are on the
+// steps' critical path).
+template <typename F>
+__device__ inline double wave_reduce_d(double v, F f) {
+  v = f(v, dpp_mov_d<0xB1>(v));    // quad_perm xor 1
+  v = f(v, dpp_mov_d<0x4E>(v));    // quad_perm xor 2
+  v = f(v, dpp_mov_d<0x141>(v));   // row_half_mirror
+  v = f(v, dpp_mov_d<0x140>(v));   // row_mirror
+  return f(f(lane_d(v, 0), lane_d(v, 16)), f(lane_d(v, 32), lane_d(v, 48)));
+}
+
+__device__ inline double wave_min_d(double v) {
+  return wave_reduce_d(v, [](double x, double y) { return fmin(x, y); });
+}
+
+__device__ inline double wave_sum_d(double v) {
+  return wave_reduce_d(v, [](double x, double y) { return x + y; });
+}
+
+// Smallest eigenpair of the symmetric tridiagonal matrix with diagonal
+// al [m] and off-diagonal be [m - 1], by a whole workgroup: s [m] receives
+// the unit eigenvector (its entries' sum made nonnegative), the eigenvalue is
+// returned in every thread.  dp, dm [m]: scratch.
+//   1. Multisection: four wavefronts evaluate the Sturm sequence of leading
+//      principal minors of T - x (a sign change means an eigenvalue below x)
+//      at 256 points of the interval, so each pass narrows it 257-fold.  The
+//      sequence has no division: one FMA per row on the critical path, both
+//      members scaled by a power of two every eight rows.
+//   2. Twice: the forward and backward LDL^T factorisations of T - theta (two
+//      lanes, one each), the twist with the smallest |gamma|, the eigenvector
+//      from their ratios, and the Rayleigh correction gamma_r / |z|^2.
+__device__ inline double lz_tridiag(const double* al, const double* be, int m, double* dp, double* dm, double* s,
+                                    int* misc) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double lo = INFINITY, hi = INFINITY;   // hi: of the negated upper bounds
+  for (int i = lane; i < m; i += 64) {
+    const double r = (i > 0 ? fabs(be[i - 1]) : 0.0) + (i + 1 < m ? fabs(be[i]) : 0.0);
+    lo = fmin(lo, al[i] - r);
+    hi = fmin(hi, -(al[i] + r));
   }
+  lo = wave_min_d(lo);
+  hi = -wave_min_d(hi);
+  // dm: squares of the off-diagonal entries, shifted to the row they enter
+  for (int i = threadIdx.x; i < m; i += kLzBlock) dm[i] = i > 0 ? be[i - 1] * be[i - 1] : 0.0;
   __syncthreads();
-  const double t = lds1[0];
-  __syncthreads();
-  return t;
-}
-
-// y = op(v) for camera c in every lane of its 16-lane row.
-__device__ inline void lz_apply(const LzArgs& a, const double* __restrict__ v, int64_t c, int l16, double y[3]) {
-  y[0] = y[1] = y[2] = 0.0;
-  const int lo = a.cam_ptr[c], hi = a.cam_ptr[c + 1];
-  double vc[3];
+  constexpr int kPts = 256;
+  constexpr double kPart = 1.0 / (kPts + 1);
+  for (int it = 0; it < 32 && hi - lo > 1e-15 * fmax(1.0, fabs(lo) + fabs(hi)); ++it) {
+    const double w = hi - lo;
+    if (wave < kPts / 64) {
+      const double x = lo + w * (kPart * (64 * wave + lane + 1));
+      int signs = 0;               // sign bit: a change so far
+      double p1 = 1.0, p2 = 0.0;   // minors i - 1 and i - 2
+      auto row = [&](double ai, double b2) {
+        const double p = fma(ai - x, p1, -(b2 * p2));
+        signs |= __double2hiint(p) ^ __double2hiint(p1);
+        p2 = p1;
+        p1 = p;
+      };
+      int i = 0;
+      for (; i + 8 <= m; i += 8) {
+        double av[8], bv[8];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) vc[k] = v[3 * c + k];
-  for (int q = lo + l16; q < hi; q += 16) {
-    const int item = a.cam_items[q];
-    const int64_t n = item >> 1;
-    const bool is_j = item & 1;
-    const int other = a.cams[2 * n + (is_j ? 0 : 1)];
-    double Q[3][3], vo[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) Q[r][k] = (double)a.Rrel[9 * n + 3 * r + k];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) vo[k] = v[3 * (int64_t)other + k];
-    if (is_j) {
-      // v_j - Q v_i
-#pragma unroll
-      for (int r = 0; r < 3; ++r) y[r] += vc[r] - (Q[r][0] * vo[0] + Q[r][1] * vo[1] + Q[r][2] * vo[2]);
-    } else {
-      // Q^T (Q v_i - v_j)
-      double t[3];
-#pragma unroll
-      for (int r = 0; r < 3; ++r) t[r] = Q[r][0] * vc[0] + Q[r][1] * vc[1] + Q[r][2] * vc[2] - vo[r];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) y[k] += Q[0][k] * t[0] + Q[1][k] * t[1] + Q[2][k] * t[2];
-    }
-  }
-#pragma unroll
-  for (int s = 8; s >= 1; s >>= 1)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) y[k] += __shfl_xor(y[k], s);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) y[k] *= a.op_alpha;
-  if (a.u) {
-    double uc[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) uc[k] = a.u[3 * c + k];
-    const double d = uc[0] * vc[0] + uc[1] * vc[1] + uc[2] * vc[2];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) y[k] += a.op_beta * uc[k] * d;
-  }
-}
-
-// Number of eigenvalues of the symmetric tridiagonal (alpha, beta) below x
-// (Sturm sequence of the LDL^T pivots).
-__device__ inline int sturm_count(const double* alpha, const double* beta, int m, double x) {
-  int cnt = 0;
-  double d = 1.0;
-  for (int i = 0; i < m; ++i) {
-    const double b2 = i > 0 ? beta[i - 1] * beta[i - 1] : 0.0;
-    d = alpha[i] - x - (i > 0 ? b2 / d : 0.0);
-    if (d == 0.0) d = -1e-300;
-    if (d < 0.0) ++cnt;
-  }
-  return cnt;
-}
-
-// Smallest eigenpair of the m x m symmetric tridiagonal matrix (one thread):
-// bisection on the Sturm count, then inverse iteration with a pivoted
-// tridiagonal solve.  s [m] receives the unit eigenvector; scratch [3m].
-__device__ inline double tridiag_smallest(const double* alpha, const double* beta, int m, double* s, double* scratch) {
-  double lo = alpha[0], hi = alpha[0];
-  for (int i = 0; i < m; ++i) {
-    const double r = (i > 0 ? fabs(beta[i - 1]) : 0.0) + (i + 1 < m ? fabs(beta[i]) : 0.0);
-    lo = fmin(lo, alpha[i] - r);
-    hi = fmax(hi, alpha[i] + r);
-  }
-  for (int it = 0; it < 200 && hi - lo > 1e-15 * fmax(1.0, fabs(lo) + fabs(hi)); ++it) {
-    const double mid = 0.5 * (lo + hi);
-    if (sturm_count(alpha, beta, m, mid) >= 1) hi = mid;
-    else lo = mid;
-  }
-  const double theta = 0.5 * (lo + hi);
-  const double sigma = theta - 1e-10 * fmax(1.0, fabs(theta));
-  // (T - sigma I) z = s by Gaussian elimination with partial pivoting
-  // (rows i and i+1 may swap; the factors have up to two superdiagonals)
-  double* u1 = scratch;          // first superdiagonal of U
-  double* u2 = scratch + m;      // second superdiagonal of U
-  double* dd = scratch + 2 * m;  // diagonal of U
-  for (int i = 0; i < m; ++i) s[i] = 1.0;
-  for (int iter = 0; iter < 3; ++iter) {
-    // factor and solve in one sweep: row i holds (dd[i], u1[i], u2[i])
-    double* rhs = s;
-    double cur_d = alpha[0] - sigma, cur_u1 = m > 1 ? beta[0] : 0.0, cur_u2 = 0.0;
-    double cur_r = rhs[0];
-    for (int i = 0; i < m; ++i) {
-      if (i + 1 < m) {
-        const double nb = beta[i];                         // sub-diagonal entry of row i+1
-        const double nd = alpha[i + 1] - sigma, nu1 = i + 2 < m ? beta[i + 1] : 0.0;
-        const double nr = rhs[i + 1];
-        if (fabs(cur_d) >= fabs(nb)) {
-          const double l = nb / (cur_d != 0.0 ? cur_d : 1e-300);
-          dd[i] = cur_d; u1[i] = cur_u1; u2[i] = cur_u2; rhs[i] = cur_r;
-          cur_d = nd - l * cur_u1;
-          cur_u1 = nu1 - l * cur_u2;
-          cur_u2 = 0.0;
-          cur_r = nr - l * cur_r;
-        } else {
-          const double l = cur_d / nb;
-          dd[i] = nb; u1[i] = nd; u2[i] = nu1; rhs[i] = nr;
-          const double od = cur_d, ou1 = cur_u1, ou2 = cur_u2, orr = cur_r;
-          (void)od;
-          cur_d = ou1 - l * nd;
-          cur_u1 = ou2 - l * nu1;
-          cur_u2 = 0.0;
-          cur_r = orr - l * nr;
+        for (int q = 0; q < 8; ++q) {
+          av[q] = al[i + q];
+          bv[q] = dm[i + q];
         }
-      } else {
-        dd[i] = cur_d != 0.0 ? cur_d : 1e-300; u1[i] = 0.0; u2[i] = 0.0; rhs[i] = cur_r;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) row(av[q], bv[q]);
+        const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+        p1 = ldexp(p1, e);
+        p2 = ldexp(p2, e);
+      }
+      for (; i < m; ++i) row(al[i], dm[i]);
+      const unsigned long long bal = __ballot(signs < 0);
+      if (lane == 0) misc[(it & 1) * 4 + wave] = bal ? 64 * wave + __builtin_ctzll(bal) : kPts;
+    }
+    __syncthreads();
+    int f = kPts;   // the first point above the smallest eigenvalue
+#pragma unroll
+    for (int q = 0; q < kPts / 64; ++q) f = min(f, misc[(it & 1) * 4 + q]);
+    const double nhi = f < kPts ? lo + w * (kPart * (f + 1)) : hi;
+    const double nlo = f > 0 ? lo + w * (kPart * f) : lo;
+    if (!(nhi - nlo < w)) break;
+    lo = nlo;
+    hi = nhi;
+  }
+  double theta = 0.5 * (lo + hi);
+  for (int round = 0; round < 2; ++round) {
+    __syncthreads();
+    if (wave == 0 && lane < 2) {
+      // lane 0 forward (rows 0, 1, ...), lane 1 backward (rows m - 1, ...); a
+      // pivot of exactly 0 becomes 1e-300
+      double* out = lane ? dm + (m - 1) : dp;
+      const double* av = lane ? al + (m - 1) : al;
+      const double* bv = lane ? be + (m - 2) : be;   // couples row q with row q + 1 in this direction
+      const int step = lane ? -1 : 1;
+      double d = av[0] - theta + 1e-300;
+      out[0] = d;
+      int q = 1;
+      auto row = [&](double ai, double b) {
+        d = fma(-(b * b), lz_rcp(d), ai - theta) + 1e-300;
+        return d;
+      };
+      for (; q + 4 <= m; q += 4) {
+        double a4[4], b4[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          a4[t] = av[(q + t) * step];
+          b4[t] = bv[(q + t - 1) * step];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) out[(q + t) * step] = row(a4[t], b4[t]);
+      }
+      for (; q < m; ++q) out[q * step] = row(av[q * step], bv[(q - 1) * step]);
+    }
+    __syncthreads();
+    // the twist: every wavefront finds it (smallest |gamma|, lowest index)
+    double g = INFINITY;
+    for (int i = lane; i < m; i += 64) g = fmin(g, fabs(dp[i] + dm[i] - (al[i] - theta)));
+    g = wave_min_d(g);
+    int r = 0;   // stays 0 if every gamma is NaN
+    for (int i0 = 0; i0 < m; i0 += 64) {
+      const int i = i0 + lane;
+      const unsigned long long at = __ballot(i < m && fabs(dp[i < m ? i : 0] + dm[i < m ? i : 0] - (al[i < m ? i : 0] - theta)) == g);
+      if (at) {
+        r = i0 + __builtin_ctzll(at);
+        break;
       }
     }
-    for (int i = m - 1; i >= 0; --i) {
-      double t = rhs[i];
-      if (i + 1 < m) t -= u1[i] * s[i + 1];
-      if (i + 2 < m) t -= u2[i] * s[i + 2];
-      s[i] = t / (dd[i] != 0.0 ? dd[i] : 1e-300);
+    const double gamma = dp[r] + dm[r] - (al[r] - theta);
+    __syncthreads();
+    for (int i = threadIdx.x; i < m; i += kLzBlock) {
+      dp[i] = i + 1 < m ? -be[i] * lz_rcp(dp[i]) : 0.0;
+      dm[i] = i > 0 ? -be[i - 1] * lz_rcp(dm[i]) : 0.0;
     }
-    double nrm = 0.0;
-    for (int i = 0; i < m; ++i) nrm += s[i] * s[i];
-    nrm = 1.0 / sqrt(nrm);
-    for (int i = 0; i < m; ++i) s[i] *= nrm;
+    __syncthreads();
+    if (wave == 0 && lane < 2) {
+      const int step = lane ? 1 : -1, count = lane ? m - 1 - r : r;
+      const double* ratio = (lane ? dm : dp) + r + step;
+      double* out = s + r + step;
+      double z = 1.0;
+      if (lane == 0) s[r] = 1.0;
+      int q = 0;
+      for (; q + 8 <= count; q += 8) {
+        double t8[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) t8[t] = ratio[(q + t) * step];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) out[(q + t) * step] = z *= t8[t];
+      }
+      for (; q < count; ++q) out[q * step] = z *= ratio[q * step];
+    }
+    __syncthreads();
+    double n2 = 0.0;
+    for (int i = lane; i < m; i += 64) n2 += s[i] * s[i];
+    n2 = wave_sum_d(n2);
+    theta += gamma / n2;
   }
+  double n2 = 0.0, sum = 0.0;
+  for (int i = lane; i < m; i += 64) {
+    n2 += s[i] * s[i];
+    sum += s[i];
+  }
+  n2 = wave_sum_d(n2);
+  sum = wave_sum_d(sum);
+  const double sc = (sum < 0.0 ? -1.0 : 1.0) / sqrt(n2);
+  __syncthreads();
+  for (int i = threadIdx.x; i < m; i += kLzBlock) s[i] *= sc;
+  __syncthreads();
   return theta;
 }
 
-// Lanczos steps between convergence checks, and the relative residual
-// bound |beta_k s_k| / |T| below which the Ritz pair is taken as converged.
-constexpr int kLzCheck = 10;
-constexpr int kLzMaxSteps = 4096;
-constexpr double kLzTol = 1e-11;
+// One entry of a camera's incidence list as the operator reads it.
+struct LzEntry {
+  int other;    // the pair's other camera; -1: none
+  int is_j;     // this camera is the pair's second one
+  float Q[9];
+};
 
-__global__ __launch_bounds__(kSolveBlock) void k_ra_lanczos(LzArgs a) {
+__device__ inline LzEntry lz_entry(const LzArgs& a, int q) {
+  LzEntry e;
+  const int item = a.cam_items[q];
+  const int64_t n = item >> 1;
+  e.is_j = item & 1;
+  e.other = a.cams[2 * n + (e.is_j ? 0 : 1)];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) e.Q[k] = a.Rrel[9 * n + k];
+  return e;
+}
+
+// This entry's term of (A v)_c, v_c = vc, v_other = vo, added to y.
+__device__ inline void lz_term(const LzEntry& e, const double vc[3], const double vo[3], double y[3]) {
+  double Q[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) Q[k] = (double)e.Q[k];
+  if (e.is_j) {
+    // v_j - Q v_i
+#pragma unroll
+    for (int r = 0; r < 3; ++r) y[r] += vc[r] - (Q[3 * r] * vo[0] + Q[3 * r + 1] * vo[1] + Q[3 * r + 2] * vo[2]);
+  } else {
+    // Q^T (Q v_i - v_j)
+    double t[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) t[r] = Q[3 * r] * vc[0] + Q[3 * r + 1] * vc[1] + Q[3 * r + 2] * vc[2] - vo[r];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) y[k] += Q[k] * t[0] + Q[3 + k] * t[1] + Q[6 + k] * t[2];
+  }
+}
+
+template <bool GL>
+__global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
+  extern __shared__ double lds[];
   GridBar gb = grid_bar(a.bar);
-  extern __shared__ double hs[];   // [m + 1] dots of the current step, then [1] broadcast
-  const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t gsize = (int64_t)gridDim.x * blockDim.x;
-  const int lane = threadIdx.x & 63;
-  const int64_t gwave = gtid >> 6, nwaves = gsize >> 6;
-  const int row = lane >> 4, l16 = lane & 15;
-  const int64_t n = a.n;
-  double* lds1 = hs + a.m + 1;
-  // q0 = start / |start|
-  double acc = 0.0;
-  for (int64_t i = gtid; i < n; i += gsize) acc += a.start[i] * a.start[i];
-  const double inv0 = 1.0 / sqrt(grid_allsum(acc, a.part, lds1, gb, gwave, nwaves));
-  for (int64_t i = gtid; i < n; i += gsize) a.V[i] = a.start[i] * inv0;
-  grid_barrier(gb);
-  int m = a.m;
-  bool have_s = false;
-  for (int k = 0; k < a.m; ++k) {
-    const double* q = a.V + (int64_t)k * n;
-    // w = op(q_k)
-    for (int64_t c0 = 4 * gwave; c0 < a.N; c0 += 4 * nwaves) {
-      const int64_t c = c0 + row;
-      if (c < a.N) {   // whole rows: the row exchanges stay within live rows
-        double y[3];
-        lz_apply(a, q, c, l16, y);
-        if (l16 < 3) a.w[3 * c + l16] = pick3d(y, l16);
-      }
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int B = gridDim.x, m = a.m, lv = GL ? 0 : a.lv;
+  const int rows = 3 * a.nc, ld = rows | 1;
+  const int64_t c0 = (int64_t)blockIdx.x * a.nc, row0 = 3 * c0;
+  const int nc = (int)(c0 >= a.N ? 0 : min((int64_t)a.nc, a.N - c0)), nr = 3 * nc;
+  double* hs = lds;                        // [m + 2] dots of the current pass
+  double* misc = hs + m + 2;               // [64]
+  double* red = misc + 64;                 // [kLzBlock]
+  const int64_t hrow = lz_hrow(m);
+  double* ws = GL ? a.gws + blockIdx.x * lz_work(rows, m) : misc + kLzMisc;
+  double* w = ws;                          // [rows] the next vector before its scaling
+  double* y = w + rows;                    // [rows] the operator's image, orthogonalised in place
+  double* u = y + rows;                    // [rows] first columns
+  double* al = u + rows;
+  double* be = al + m;
+  double* dp = be + m;
+  double* dm = dp + m;
+  double* sv = dm + m;                     // [m] Ritz coefficients
+  double* Vl = sv + m;                     // [lv, ld] basis rows (LDS variant)
+  auto vg = [&](int j) { return a.V + (int64_t)(j - lv) * a.n + row0; };
+  auto v_at = [&](int j, int r) { return j < lv ? Vl[(int64_t)j * ld + r] : vg(j)[r]; };
+
+  // sum_j coef[j] V[j][r], j < cnt, for this workgroup's rows: sixteen lanes
+  // per row; out(r, sum) is called in all of them
+  const int l16 = tid & 15;
+  auto combine = [&](const double* coef, int cnt, auto out) {
+    for (int r = tid >> 4; r < nr; r += kLzBlock / 16) {   // whole rows of lanes
+      double s0 = 0.0;
+      int j = l16;
+#pragma unroll 2
+      for (; j < min(cnt, lv); j += 16) s0 = fma(coef[j], Vl[(int64_t)j * ld + r], s0);
+#pragma unroll 4
+      for (; j < cnt; j += 16) s0 = fma(coef[j], vg(j)[r], s0);
+      s0 += dpp_mov_d<0xB1>(s0);
+      s0 += dpp_mov_d<0x4E>(s0);
+      s0 += dpp_mov_d<0x141>(s0);
+      s0 += dpp_mov_d<0x140>(s0);
+      out(r, s0);
     }
-    grid_barrier(gb);
-    // two passes of classical Gram-Schmidt against q_0 .. q_k
-    double alpha_k = 0.0;
-    bool stop = false;
-    for (int pass = 0; pass < 2; ++pass) {
-      for (int64_t j = gwave; j <= k; j += nwaves) {
-        const double* vj = a.V + j * n;
-        double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
-        int64_t i = lane;
-        for (; i + 192 < n; i += 256) {
-          d0 += vj[i] * a.w[i];
-          d1 += vj[i + 64] * a.w[i + 64];
-          d2 += vj[i + 128] * a.w[i + 128];
-          d3 += vj[i + 192] * a.w[i + 192];
-        }
-        for (; i < n; i += 64) d0 += vj[i] * a.w[i];
-        double d = (d0 + d1) + (d2 + d3);
+  };
+  // a wavefront's share of a squared norm out (its lanes' values v), and the
+  // total of all shares
+  auto norm_out = [&](double v) {
+    v = wave_sum_d(v);
+    if (lane == 0) store_wt(&a.part_n[(int64_t)blockIdx.x * kLzWaves + wave], v);
+  };
+  auto norm_in = [&]() {
+    double t = 0.0;
+    for (int i = tid; i < B * kLzWaves; i += kLzBlock) t += a.part_n[i];
+    t = wave_sum_d(t);
+    if (lane == 0) misc[16 + wave] = t;
+    __syncthreads();
+    t = 0.0;
 #pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) d += __shfl_xor(d, s);
-        if (lane == 0) a.h[j] = d;
+    for (int q = 0; q < kLzWaves; ++q) t += misc[16 + q];
+    return t;
+  };
+
+  // static data of the first 64 entries of the wavefront's first camera
+  LzEntry e0;
+  e0.other = -1;
+  if (wave < nc) {
+    const int q = a.cam_ptr[c0 + wave] + lane;
+    if (q < a.cam_ptr[c0 + wave + 1]) e0 = lz_entry(a, q);
+  }
+
+  for (int col = 0; col < 2; ++col) {
+    const double op_alpha = col ? a.inv_P : 1.0;
+    // q_0 = start / |start|
+    double acc = 0.0;
+    for (int r = tid; r < nr; r += kLzBlock) {
+      const double x = a.start[col * a.n + row0 + r];
+      w[r] = x;
+      store_wt(&a.wbuf[row0 + r], x);
+      acc += x * x;
+    }
+    norm_out(acc);
+    grid_barrier_wt(gb);
+    double inv = 1.0 / sqrt(norm_in());
+    double alpha = 0.0, b = 0.0, theta = 0.0;
+    int used = m;
+    bool have_s = false;
+    for (int k = 0; k < m; ++k) {
+      for (int r = tid; r < nr; r += kLzBlock) {
+        const double v = w[r] * inv;
+        if (k < lv)
+          Vl[(int64_t)k * ld + r] = v;
+        else
+          vg(k)[r] = v;
       }
-      grid_barrier(gb);
-      for (int j = threadIdx.x; j <= k; j += blockDim.x) hs[j] = a.h[j];
       __syncthreads();
-      alpha_k += hs[k];
-      // w_i -= sum_j h_j V[j][i], eight basis entries in flight per thread
-      double nrm = 0.0;
-      for (int64_t i = gtid; i < n; i += gsize) {
-        double s8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        int j = 0;
-        for (; j + 8 <= k + 1; j += 8) {
-          double v8[8];
+      // y = op(q_k) - alpha_{k-1} q_k - beta_{k-1} q_{k-1}
+      for (int cl = wave; cl < nc; cl += kLzWaves) {
+        const int lo = a.cam_ptr[c0 + cl], hi = a.cam_ptr[c0 + cl + 1];
+        double vc[3], t3[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-          for (int u = 0; u < 8; ++u) v8[u] = a.V[(int64_t)(j + u) * n + i];
+        for (int j = 0; j < 3; ++j) vc[j] = w[3 * cl + j] * inv;
+        for (int q = lo + lane; q < hi; q += 64) {
+          LzEntry e;
+          if (cl == wave && q == lo + lane)
+            e = e0;
+          else
+            e = lz_entry(a, q);
+          double vo[3];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) s8[u] += hs[j + u] * v8[u];
+          for (int j = 0; j < 3; ++j) vo[j] = a.wbuf[3 * (int64_t)e.other + j] * inv;
+          lz_term(e, vc, vo, t3);
         }
-        for (; j <= k; ++j) s8[0] += hs[j] * a.V[(int64_t)j * n + i];
-        const double wi = a.w[i] - (((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7])));
-        a.w[i] = wi;
-        nrm += wi * wi;
-      }
-      __syncthreads();   // hs is rewritten by the next pass
-      if (pass == 0) {
-        grid_barrier(gb);
-      } else {
-        const double b = sqrt(grid_allsum(nrm, a.part, lds1, gb, gwave, nwaves));
-        if (gtid == 0) {
-          a.alpha[k] = alpha_k;
-          a.beta[k] = b;
-        }
-        // an invariant subspace, the last step, or a converged Ritz pair
-        // (checked every kLzCheck steps by one thread; the decision is read
-        // by all after a barrier)
-        if (!(b > 1e-12 * fmax(1.0, fabs(alpha_k))) || k + 1 == a.m) {
-          stop = true;
-        } else if ((k + 1) % kLzCheck == 0) {
-          grid_barrier(gb);   // alpha, beta of this step visible
-          if (gtid == 0) {
-            const double theta = tridiag_smallest(a.alpha, a.beta, k + 1, a.s, a.s + a.m);
-            double tn = 0.0;
-            for (int i = 0; i <= k; ++i) tn = fmax(tn, fabs(a.alpha[i]) + 2.0 * fabs(a.beta[i]));
-            a.info[0] = theta;
-            a.h[a.m] = (fabs(b * a.s[k]) <= kLzTol * fmax(tn, 1e-300)) ? 1.0 : 0.0;
+        // totals in lanes 0, 4 and 8 (entries 0, 1, 2)
+        double b2[2], b1[1];
+        rs_stage_d<3, 3>(t3, b2, lane);
+        rs_stage_d<2, 2>(b2, b1, lane);
+        double t = b1[0];
+        t += dpp_mov_d<0x4E>(t);
+        t += dpp_mov_d<0xB1>(t);
+        t += __shfl_xor(t, 16);
+        t += __shfl_xor(t, 32);
+        if (lane == 0 || lane == 4 || lane == 8) {
+          const int r = 3 * cl + (lane >> 2);
+          t *= op_alpha;
+          if (col) {
+            const double d = u[3 * cl] * vc[0] + u[3 * cl + 1] * vc[1] + u[3 * cl + 2] * vc[2];
+            t += a.inv_N * u[r] * d;
           }
-          grid_barrier(gb);
-          stop = a.h[a.m] != 0.0;
-          have_s = stop;
+          t = fma(-alpha, v_at(k, r), t);
+          if (k > 0) t = fma(-b, v_at(k - 1, r), t);
+          y[r] = t;
         }
-        if (stop) {
-          m = k + 1;
-        } else {
-          const double inv = 1.0 / b;
-          double* qn = a.V + (int64_t)(k + 1) * n;
-          for (int64_t i = gtid; i < n; i += gsize) qn[i] = a.w[i] * inv;
+      }
+      __syncthreads();
+      double nrm2 = 0.0;
+      for (int pass = 0; pass < 2; ++pass) {
+        const double* src = pass ? w : y;
+        // partial dots with q_0 .. q_k and (entry k + 1) with the vector
+        // itself: eight lanes each
+        for (int j = tid >> 3; j <= k + 1; j += kLzBlock / 8) {
+          const int l8 = tid & 7;
+          double d = 0.0;
+          if (j < lv && j <= k) {
+            const double* vj = Vl + (int64_t)j * ld;
+            for (int r = l8; r < nr; r += 8) d = fma(vj[r], src[r], d);
+          } else {
+            const double* vj = j <= k ? vg(j) : src;
+#pragma unroll 4
+            for (int r = l8; r < nr; r += 8) d = fma(vj[r], src[r], d);
+          }
+          d += dpp_mov_d<0xB1>(d);
+          d += dpp_mov_d<0x4E>(d);
+          d += dpp_mov_d<0x141>(d);
+          if (l8 == 0) store_wt(&a.part_h[blockIdx.x * hrow + j], d);
         }
+        grid_barrier_wt(gb);
+        // the dots: threads over the entries and, while these are few, over
+        // interleaved parts of the workgroups
+        const int width = k + 2 <= 64 ? 64 : (k + 2 <= 128 ? 128 : (k + 2 <= 256 ? 256 : kLzBlock));
+        for (int j0 = 0; j0 <= k + 1; j0 += width) {
+          const int j = j0 + (tid & (width - 1)), parts = kLzBlock / width;
+          double t = 0.0;
+          if (j <= k + 1) {
+            const double* ph = a.part_h + j;
+            int q = tid / width;
+#pragma unroll 1
+            for (; q + 3 * parts < B; q += 4 * parts) {
+              const double p0 = ph[q * hrow], p1 = ph[(q + parts) * hrow], p2 = ph[(q + 2 * parts) * hrow],
+                           p3 = ph[(q + 3 * parts) * hrow];
+              t += (p0 + p1) + (p2 + p3);
+            }
+            double p[3];   // the rest's loads in flight together too
+#pragma unroll
+            for (int e = 0; e < 3; ++e) p[e] = q + e * parts < B ? ph[(q + e * parts) * hrow] : 0.0;
+            t += (p[0] + p[1]) + p[2];
+          }
+          if (parts > 1) {   // one round: width > k + 1
+            red[tid] = t;
+            __syncthreads();
+            if (tid < width) {
+              t = 0.0;
+              for (int e = 0; e < parts; ++e) t += red[e * width + tid];
+            }
+          }
+          if (tid < width && j <= k + 1) hs[j] = t;
+        }
+        __syncthreads();
+        acc = 0.0;
+        combine(hs, k + 1, [&](int r, double t) {
+          if (l16 != 0) return;
+          const double wr = src[r] - t;
+          w[r] = wr;
+          store_wt(&a.wbuf[row0 + r], wr);
+          acc = fma(wr, wr, acc);
+        });
+        norm_out(acc);
+        alpha += hs[k];
+        const double before = hs[k + 1];
+        grid_barrier_wt(gb);
+        nrm2 = norm_in();
+        if (!(nrm2 < 0.25 * before)) break;
+      }
+      b = sqrt(nrm2);
+      if (tid == 0) {
+        al[k] = alpha;
+        be[k] = b;
+      }
+      // an invariant subspace, the last step, or a converged Ritz pair
+      // (every workgroup takes the same decision from the same values)
+      bool stop = !(b > 1e-12 * fmax(1.0, fabs(alpha))) || k + 1 == m;
+      if (!stop && (k + 1) % kLzCheck == 0) {
+        __syncthreads();
+        theta = lz_tridiag(al, be, k + 1, dp, dm, sv, reinterpret_cast<int*>(misc));
+        double tn = INFINITY;
+        for (int i = lane; i <= k; i += 64) tn = fmin(tn, -(fabs(al[i]) + 2.0 * fabs(be[i])));
+        tn = -wave_min_d(tn);
+        stop = have_s = fabs(b * sv[k]) <= kLzTol * fmax(tn, 1e-300);
+      }
+      if (stop) {
+        used = k + 1;
+        break;
+      }
+      inv = 1.0 / b;
+    }
+    __syncthreads();
+    if (!have_s) theta = lz_tridiag(al, be, used, dp, dm, sv, reinterpret_cast<int*>(misc));
+    if (a.info && blockIdx.x == 0 && tid == 0) {
+      a.info[2 * col] = theta;
+      a.info[2 * col + 1] = (double)used;
+    }
+    // the Ritz vector, then per camera: c1 = x_c / |x_c| (first column); y_c
+    // normalised, made orthogonal to c1 and normalised again (second), the
+    // parameters being the rotation's first two columns (its third is c1 x c2
+    // by the 6D map)
+    combine(sv, used, [&](int r, double t) {
+      if (l16 == 0) y[r] = t;
+    });
+    __syncthreads();
+    for (int cl = tid; cl < nc; cl += kLzBlock) {
+      double v[3], e[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[k] = y[3 * cl + k];
+      double r = 1.0 / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+      if (col == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) u[3 * cl + k] = v[k] * r;
+        continue;
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        v[k] *= r;
+        e[k] = u[3 * cl + k];
+      }
+      const double d = v[0] * e[0] + v[1] * e[1] + v[2] * e[2];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[k] -= d * e[k];
+      r = 1.0 / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        a.params[6 * (c0 + cl) + k] = (float)e[k];
+        a.params[6 * (c0 + cl) + 3 + k] = (float)(v[k] * r);
       }
     }
-    if (stop) break;
-    grid_barrier(gb);
-  }
-  grid_barrier(gb);
-  if (gtid == 0) {
-    if (!have_s) a.info[0] = tridiag_smallest(a.alpha, a.beta, m, a.s, a.s + a.m);
-    a.info[1] = (double)m;
-  }
-  grid_barrier(gb);
-  for (int64_t i = gtid; i < n; i += gsize) {
-    double x = 0.0;
-    for (int j = 0; j < m; ++j) x += a.s[j] * a.V[(int64_t)j * n + i];
-    a.out[i] = x;
-  }
-}
-
-// c1 = x_c / |x_c| per camera (first columns); also copied to u for the
-// second problem.
-__global__ __launch_bounds__(kBlock) void k_ra_unit_rows(const double* __restrict__ x, int32_t N, double* __restrict__ u) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= N) return;
-  const double a = x[3 * c], b = x[3 * c + 1], d = x[3 * c + 2];
-  const double r = 1.0 / sqrt(a * a + b * b + d * d);
-  u[3 * c] = a * r;
-  u[3 * c + 1] = b * r;
-  u[3 * c + 2] = d * r;
-}
-
-// Second columns: y_c normalised, made orthogonal to c1 (Gram-Schmidt) and
-// normalised again; the parameters are (c1, c2), the rotation's first two
-// columns (its third is c1 x c2 by the 6D map).
-__global__ __launch_bounds__(kBlock) void k_ra_finish(const double* __restrict__ c1, const double* __restrict__ y,
-                                                      int32_t N, float* __restrict__ params) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= N) return;
-  double v[3], e[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    v[k] = y[3 * c + k];
-    e[k] = c1[3 * c + k];
-  }
-  double r = 1.0 / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) v[k] *= r;
-  const double d = v[0] * e[0] + v[1] * e[1] + v[2] * e[2];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) v[k] -= d * e[k];
-  r = 1.0 / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    params[6 * c + k] = (float)e[k];
-    params[6 * c + 3 + k] = (float)(v[k] * r);
+    // the second problem overwrites what other workgroups still read
+    if (col == 0) grid_barrier_wt(gb);
   }
 }
 
@@ -874,24 +1094,48 @@ extern "C" fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* s, const float* Rre
   const int64_t n = 3 * (int64_t)s->N;
   const int32_t m = steps < n ? steps : (int32_t)n;
   if (m > kLzMaxSteps) return fm_fail(ctx, FM_EINVAL, "fm_rotation_init: steps above %d", kLzMaxSteps);
-  const size_t lds_bytes = sizeof(double) * (kLzMaxSteps + 2);
   if (s->lz_coop_blocks <= 0) {
-    int per_cu = 0;
-    FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ra_lanczos, kSolveBlock, lds_bytes));
+    int lds_max = 0, per_cu = 0;
+    FM_HIP_TRY(ctx, hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
+    for (const void* k : {(const void*)k_ra_lanczos<false>, (const void*)k_ra_lanczos<true>})
+      FM_HIP_TRY(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
+    FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ra_lanczos<false>, kLzBlock, lds_max));
+    int per_cu_g = 0;
+    FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                        &per_cu_g, k_ra_lanczos<true>, kLzBlock, sizeof(double) * (kLzMaxSteps + 2 + kLzMisc)));
+    if (per_cu_g < per_cu) per_cu = per_cu_g;
     s->lz_coop_blocks = per_cu * ctx->num_cu;
+    s->lz_lds = lds_max;
     if (s->lz_coop_blocks <= 0) return fm_fail(ctx, FM_ECOOP, "cannot size the cooperative Lanczos kernel");
   }
-  // about one 16-lane row per camera, at most 16 workgroups (the solve is a
-  // chain of grid-wide reductions), at the co-resident limit
-  int64_t want = grid_for(n / 3 * 16, kSolveBlock);
-  if (want > 16) want = 16;
-  if (blocks > 0) want = blocks;
-  if (want < 1) want = 1;
+  // cameras per workgroup: one per wavefront on small graphs, else 16, 32 or a
+  // higher multiple of 16, so that a workgroup's rows are whole 128-byte lines
+  // (more workgroups make the barriers and the sums of partials dearer, fewer
+  // the operator and the basis products: 200 cameras 25 workgroups 1.08 ms, 13
+  // 1.23, 50 1.16; 1,000 cameras 63 workgroups 4.7 ms, 32 and 125 5.4; 5,000
+  // cameras 157 workgroups 12.9 ms, 105 14.7, 209 13.3)
+  int64_t nc = kLzWaves;
+  if (s->N > 64 * nc) nc = 16;
+  if (s->N > 64 * nc) nc = 32;
+  if (s->N > kLzMaxBlocks * nc) nc = ((int64_t)s->N + 16 * kLzMaxBlocks - 1) / (16 * kLzMaxBlocks) * 16;
+  int64_t want = blocks > 0 ? blocks : (s->N + nc - 1) / nc;
   if (want > s->lz_coop_blocks) want = s->lz_coop_blocks;
-  const int64_t waves = want * (kSolveBlock / 64);
-  // layout: V [(m+1) n] | w [n] | out [n] | c1 [n] | y [n] | h [m+2] | part [waves] | alpha [m] | beta [m] |
-  //         s [4m] | info [4]  (h [m+2]: the last slot carries the convergence decision)
-  const int64_t need = (int64_t)(m + 1) * n + 4 * n + (m + 2) + waves + 2 * (int64_t)m + 4 * (int64_t)m + 4;
+  if (want > s->N) want = s->N;
+  // a workgroup's vectors fit the LDS variant from this many workgroups on
+  const int64_t fit = (n + kLzLdsRows - 1) / kLzLdsRows;
+  if (want < fit && fit <= s->lz_coop_blocks) want = fit;
+  if (blocks > 0 || want * nc < s->N) nc = ((int64_t)s->N + want - 1) / want;
+  const int64_t rows = 3 * nc;
+  const int64_t head = m + 2 + kLzMisc;
+  const int64_t lds_doubles = s->lz_lds / (int64_t)sizeof(double);
+  const bool in_lds = m <= kLzLdsSteps && rows <= kLzLdsRows && head + lz_work(rows, m) <= lds_doubles;
+  int64_t lv = in_lds ? (lds_doubles - head - lz_work(rows, m)) / (rows | 1) : 0;
+  if (lv > m) lv = m;
+  const size_t lds_bytes = sizeof(double) * (head + (in_lds ? lz_work(rows, m) + lv * (rows | 1) : 0));
+  // workspace: V [(m - lv) n] | wbuf [n] | part_h [want lz_hrow(m)] | part_n [want kLzWaves] | gws,
+  // wbuf and part_h at whole 128-byte lines
+  const int64_t vpad = ((m - lv) * n + 15) / 16 * 16, wpad = (n + 15) / 16 * 16;
+  const int64_t need = vpad + wpad + want * (lz_hrow(m) + kLzWaves) + (in_lds ? 0 : want * lz_work(rows, m));
   if (need > s->lz_cap) {
     FM_HIP_TRY(ctx, hipDeviceSynchronize());
     (void)hipFree(s->lz);
@@ -903,41 +1147,21 @@ extern "C" fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* s, const float* Rre
     }
     s->lz_cap = need;
   }
-  double* V = s->lz;
-  double* w = V + (int64_t)(m + 1) * n;
-  double* out = w + n;
-  double* c1 = out + n;
-  double* y = c1 + n;
-  double* h = y + n;
-  double* part = h + (m + 2);
-  double* alpha = part + waves;
-  double* beta = alpha + m;
-  double* sv = beta + m;
-  double* inf = sv + 4 * (int64_t)m;
   LzArgs a;
   a.cams = s->pair_cams; a.Rrel = Rrel; a.cam_ptr = s->cam_ptr; a.cam_items = s->cam_items;
-  a.V = V; a.w = w; a.h = h; a.part = part; a.alpha = alpha; a.beta = beta; a.s = sv; a.bar = s->bar;
-  a.n = n; a.N = s->N; a.m = m;
+  a.start = start; a.params = params; a.info = info; a.bar = s->bar;
+  a.V = s->lz;
+  a.wbuf = a.V + vpad;
+  a.part_h = a.wbuf + wpad;
+  a.part_n = a.part_h + want * lz_hrow(m);
+  a.gws = a.part_n + want * kLzWaves;
+  a.n = n; a.N = s->N; a.m = m; a.nc = (int32_t)nc; a.lv = (int32_t)lv;
+  a.inv_P = 1.0 / (double)s->P; a.inv_N = 1.0 / (double)s->N;
   fm_timed timer(ctx, FM_K_RA_INIT, st);
-  for (int col = 0; col < 2; ++col) {
-    a.start = start + col * n;
-    a.u = col == 0 ? nullptr : c1;
-    a.op_alpha = col == 0 ? 1.0 : 1.0 / (double)s->P;
-    a.op_beta = col == 0 ? 0.0 : 1.0 / (double)s->N;
-    a.out = col == 0 ? out : y;
-    a.info = inf + 2 * col;
-    void* args[] = {&a};
-    FM_HIP_TRY(ctx, fm_bar_reset(s->bar, st));
-    hipError_t e = hipLaunchCooperativeKernel((const void*)k_ra_lanczos, dim3((unsigned)want), dim3(kSolveBlock), args,
-                                              lds_bytes, st);
-    if (e != hipSuccess) return fm_fail(ctx, FM_ECOOP, "cooperative launch failed: %s", hipGetErrorString(e));
-    if (col == 0) {
-      hipLaunchKernelGGL(k_ra_unit_rows, dim3(grid_for(s->N, kBlock)), dim3(kBlock), 0, st, out, s->N, c1);
-      FM_CHECK_LAUNCH(ctx);
-    }
-  }
-  hipLaunchKernelGGL(k_ra_finish, dim3(grid_for(s->N, kBlock)), dim3(kBlock), 0, st, c1, y, s->N, params);
-  FM_CHECK_LAUNCH(ctx);
-  if (info) FM_HIP_TRY(ctx, hipMemcpyAsync(info, inf, sizeof(double) * 4, hipMemcpyDeviceToDevice, st));
+  void* args[] = {&a};
+  FM_HIP_TRY(ctx, fm_bar_reset(s->bar, st));
+  hipError_t e = hipLaunchCooperativeKernel(in_lds ? (const void*)k_ra_lanczos<false> : (const void*)k_ra_lanczos<true>,
+                                            dim3((unsigned)want), dim3(kLzBlock), args, lds_bytes, st);
+  if (e != hipSuccess) return fm_fail(ctx, FM_ECOOP, "cooperative launch failed: %s", hipGetErrorString(e));
   return FM_OK;
 }
