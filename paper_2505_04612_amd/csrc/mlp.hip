@@ -2,19 +2,19 @@
 // (ReLU, ReLU, sigmoid) whose 64x64 layer runs on MFMA (float16 operands,
 // float32 accumulation), forward and backward.
 //
-// MFMA layouts (one wavefront, lane l, r = l % 16, q = l / 16), both with
+// MFMA layouts (one wavefront, lane l, r = l % 16, q = l / 16), all with
 // the 16x16 float32 result D[4q + j][r] in four registers:
 //   v_mfma_f32_16x16x32_f16 (gfx950): operand A (16 x 32, M x K) holds
 //     A[r][8q + j] in its 8 halves, operand B (32 x 16) holds B[8q + j][r];
-//     used where the contraction runs over the 64 hidden units (the
-//     forward's 64x64 layer, the backward's dh1 = dh2 W2): two per 16x16
-//     output tile;
+//     used where the contraction runs over the hidden units (the forward's
+//     second and third layers, the backward's dh1 = dh2 W2);
 //   v_mfma_f32_16x16x16_f16: A[r][4q + j], B[4q + j][r]; used for the
-//     backward's dW2, whose contraction runs over a 16-match tile, and for
-//     the forward's 64 -> 1 layer, whose operand B is the transposed 64x64
-//     layer's result as it stands (units along 4q + j, matches along r).
+//     backward's dW2, whose contraction runs over a 16-match tile;
+//   v_mfma_f32_16x16x4_f32: A[r][q], B[q][r]; used for the forward's first
+//     layer, whose contraction runs over the three features.  It is exactly
+//     the chain of float32 FMAs over k = 0..3 from the start value.
 // A tile is 16 matches; lanes r = 0..15 of each quarter q address one match
-// (operand A) or one output unit (result).
+// (operand B) or one output unit (operand A).
 #include <mutex>
 
 #include "fm_internal.h"
@@ -22,6 +22,7 @@
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4a __attribute__((ext_vector_type(4), aligned(4)));   // in the caller's arrays: any float alignment
 
 constexpr int kHid = 64;
 // gradient entries: W2 (64x64), b2, W3, b3, W1 (64x3), b1
@@ -33,6 +34,8 @@ struct MlpPtrs {
 
 __device__ inline f4 mfma16(h4 a, h4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0); }
 __device__ inline f4 mfma32(h8 a, h8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+__device__ inline f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -60,99 +63,183 @@ __device__ inline void load_x(const float* feats, int64_t m, const MlpLds& s, fl
   for (int c = 0; c < 3; ++c) x[c] = (feats[m * 3 + c] - s.mean[c]) * s.rstd[c];
 }
 
-// Blocks of 4 wavefronts walk the 16-match tiles in block-uniform steps (so
-// block barriers are safe); tile = step * 4 * gridDim + 4 * block + wave.
+// ReLU and rounding to float16 of four float32 values (rounding first: the
+// same values, half the instructions).
+__device__ inline h4 relu_h4(f4 c) {
+  h4 h = {(_Float16)c[0], (_Float16)c[1], (_Float16)c[2], (_Float16)c[3]};
+  return __builtin_elementwise_max(h, h4{});
+}
+
+__device__ inline h8 join(h4 a, h4 b) { return h8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]}; }
+
+constexpr int kFwdWaves = 4;      // wavefronts per workgroup of the forward
+constexpr int kFwdMatches = 64;   // matches per wavefront and step: four tiles
+constexpr int kFwdPair = 2;       // tiles evaluated together
+
+// Each wavefront takes 64 matches (four tiles) per step; the sigmoid and the
+// output are one match per lane.
+//
+// All three layers run on MFMA, each one's result being the next one's operand
+// B as it stands.  The first layer's float32 MFMA has the features as k = 2, 1,
+// 0 (k = 3: zeros) and the bias as start value, the FMA chain of a plain
+// evaluation; its operand A is so ordered that lane (q, r) receives units
+// 8q .. 8q + 7 of each half of the layer.  The last layer has W3's float16 high
+// and low parts in rows 4i and 4i + 1 of operand A, so that every quarter of
+// the lanes holds the tile's z3 and lane l can take match l's.
+//
+// Bound by issue: per 64 matches 56 MFMAs take 1,150 cycles of a SIMD and some
+// 260 VALU instructions 1,100 more (a VALU instruction of another wavefront
+// delays running MFMAs by its own cycles, measured; 16 bytes per match move).
+// 2.94M matches, per call: 78 us with the first layer on the VALU and one tile
+// at a time, 47 one tile at a time, 44 with two tiles together (four: 49).
 // KEEP: also store each match's 128 FP16 activations to act (what the
 // backward reads back); the plain forward is instantiated without that code.
 template <bool KEEP>
-__global__ __launch_bounds__(256, 4) void k_mlp_forward(int64_t M, const float* __restrict__ feats, MlpPtrs w,
-                                                     float out_scale, float* __restrict__ out,
-                                                     _Float16* __restrict__ act) {
-  __shared__ MlpLds s;
+__global__ __launch_bounds__(64 * kFwdWaves, 3) void k_mlp_forward(int64_t M, const float* __restrict__ feats,
+                                                                   MlpPtrs w, float out_scale,
+                                                                   float* __restrict__ out,
+                                                                   _Float16* __restrict__ act) {
+  // layer 2's operand A in lane order, [kk][nt][lane]
+  __shared__ h8 W2s[2][4][64];
   // per-wavefront staging of the kept activations: rows padded by 16 bytes,
   // so that the 16 rows a store instruction touches start in different banks
   constexpr int kTstRow = 2 * kHid + 8;
-  __shared__ __attribute__((aligned(16))) _Float16 Tst[4][16][kTstRow];
-  load_lds(w, s);
+  __shared__ __attribute__((aligned(16))) _Float16 Tst[KEEP ? kFwdWaves : 1][16][kTstRow];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
-  // layer-2 operand B[k][n] = W2[n][k] for k-tile kk (32 inputs), n-tile nt
-  h8 B[2][4];
+  for (int k = threadIdx.x; k < kHid * kHid / 4; k += 64 * kFwdWaves) {
+    const int o = k >> 4, i = 4 * (k & 15);   // unit i = 32 kk + 8 q + j
+    const f4 v = *reinterpret_cast<const f4a*>(w.W2 + o * kHid + i);
+    h4* dst = reinterpret_cast<h4*>(&W2s[i >> 5][o >> 4][16 * (i >> 3 & 3) + (o & 15)]) + (i >> 2 & 1);
+    *dst = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+  }
+  // layer 1, MFMA (kk, h): row 4i + j is unit 32 kk + 8 i + 4 h + j, k is
+  // feature 2 - k
+  float A1[2][2];
+  f4 C1[2][2], b2[4];
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) B[kk][nt][j] = (_Float16)w.W2[(16 * nt + r) * kHid + 32 * kk + 8 * q + j];
-  // output-layer operand A3[n][k] for units k of n-tile nt: row 0 holds W3
-  // (as float16 high and low parts, so the products keep float32
-  // precision), rows 1..15 are zero; lane (q, r) holds A3[r][4q + j]
-  h4 W3h[4], W3l[4];
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float w3 = r == 0 ? w.W3[16 * nt + 4 * q + j] : 0.0f;
-      W3h[nt][j] = (_Float16)w3;
-      W3l[nt][j] = (_Float16)(w3 - (float)W3h[nt][j]);
+    for (int h = 0; h < 2; ++h) {
+      A1[kk][h] = q < 3 ? w.W1[3 * (32 * kk + 8 * (r >> 2) + 4 * h + (r & 3)) + 2 - q] : 0.0f;
+      C1[kk][h] = *reinterpret_cast<const f4a*>(w.b1 + 32 * kk + 8 * q + 4 * h);
     }
-  const int64_t ntiles = (M + 15) / 16;
-  for (int64_t base = (int64_t)blockIdx.x * 4; base < ntiles; base += (int64_t)gridDim.x * 4) {
-    const int64_t tile = base + wave;
-    if (tile >= ntiles) continue;   // no block barrier below
-    const int64_t m = tile * 16 + r;
-    const bool ok = m < M;
-    float x[3];
-    load_x(feats, ok ? m : M - 1, s, x);
-    h8 A[2];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
+  for (int nt = 0; nt < 4; ++nt) b2[nt] = *reinterpret_cast<const f4a*>(w.b2 + 16 * nt + 4 * q);
+  // row r: W3's high part (r % 4 = 0), low part (r % 4 = 1) or zero; entry (q, j)
+  // of half kk is unit 16 (2 kk + j / 4) + 4 q + j % 4, as layer 2 leaves them
+  h8 A3[2];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = 32 * kk + 8 * q + j;
-        const float z = fmaf(s.W1[3 * k], x[0], fmaf(s.W1[3 * k + 1], x[1], fmaf(s.W1[3 * k + 2], x[2], s.b1[k])));
-        A[kk][j] = (_Float16)fmaxf(z, 0.0f);
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float w3 = w.W3[16 * (2 * kk + (j >> 2)) + 4 * q + (j & 3)];
+      const _Float16 hi = (_Float16)w3, lo = (_Float16)(w3 - (float)hi);
+      A3[kk][j] = (r & 3) == 0 ? hi : ((r & 3) == 1 ? lo : (_Float16)0.0f);
+    }
+  const float b3 = w.b3[0];
+  const int fc = q < 3 ? 2 - q : 0;   // this lane's feature (k = 3 takes zeros)
+  const float mean = w.mean[fc], rstd = 1.0f / w.std[fc];
+  __syncthreads();
+  h8 A2[2][4];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) A2[kk][nt] = W2s[kk][nt][lane];
+  const int64_t groups = (M + kFwdMatches - 1) / kFwdMatches, stride = (int64_t)gridDim.x * kFwdWaves;
+  // the step's features, one per lane and tile, from one address (only the
+  // last step checks the end: past it, match M - 1's)
+  float fv[4];
+  auto load = [&](int64_t g, float (&f)[4]) {
+    const float* p = feats + (g * kFwdMatches + r) * 3 + fc;
+    if ((g + 1) * kFwdMatches <= M) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) f[t] = p[48 * t];
+    } else {
+      const int left = (int)(M - 1 - g * kFwdMatches) - r;   // < 64
+#pragma unroll
+      for (int t = 0; t < 4; ++t) f[t] = p[3 * min(16 * t, left)];
+    }
+  };
+  int64_t g = (int64_t)blockIdx.x * kFwdWaves + wave;
+  if (g >= groups) return;   // no workgroup barrier below
+  load(g, fv);
+  for (; g < groups; g += stride) {
+    const int64_t m0 = g * kFwdMatches;
+    const int left = (int)min(M - m0, (int64_t)kFwdMatches);   // matches of this step
+    _Float16* ap = KEEP ? act + (m0 + q) * 128 + 8 * r : nullptr;
+    float fn[4];
+    load(g + stride < groups ? g + stride : g, fn);   // the next step's, ahead
+    float z = 0.0f;   // this lane's match: tile q
+    // two tiles together, layer by layer: one's MFMAs run while the other's
+    // results are rounded
+#pragma unroll
+    for (int t0 = 0; t0 < 4; t0 += kFwdPair) {
+      h8 H1[kFwdPair][2], H2[kFwdPair][2];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        f4 c[kFwdPair][2];
+#pragma unroll
+        for (int p = 0; p < kFwdPair; ++p) {
+          const float x = q < 3 ? (fv[t0 + p] - mean) * rstd : 0.0f;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) c[p][h] = mfma4(A1[kk][h], x, C1[kk][h]);
+        }
+#pragma unroll
+        for (int p = 0; p < kFwdPair; ++p) H1[p][kk] = join(relu_h4(c[p][0]), relu_h4(c[p][1]));
       }
-    // layer 2 transposed (W2 as operand A, the tile's layer-1 activations as
-    // operand B): C[nt][j] = z2 of unit 16 nt + 4q + j, match 16 tile + r,
-    // which after bias, ReLU and rounding to float16 is operand B of the
-    // output layer's 16x16x16 MFMA as it stands (units along 4q + j)
-    f4 Z = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    h4 h[4];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f4 C = f4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int kk = 0; kk < 2; ++kk) {   // units 32 kk .. 32 kk + 31
+        f4 c[2][kFwdPair];
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) C = mfma32(B[kk][nt], A[kk], C);
+        for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) h[nt][j] = (_Float16)fmaxf(C[j] + s.b2[16 * nt + 4 * q + j], 0.0f);
-      Z = mfma16(W3h[nt], h[nt], Z);
-      Z = mfma16(W3l[nt], h[nt], Z);
-    }
-    // the tile's activations (16 rows of 128 halves: one contiguous 4 KB
-    // block of act) through this wavefront's LDS rows, then written with
-    // consecutive 16-byte stores; LDS operations of a wavefront complete in
-    // order, the fences keep the compiler from reordering them
-    if constexpr (KEEP) {
-      _Float16* T = &Tst[wave][0][0];
+          for (int p = 0; p < kFwdPair; ++p) c[n][p] = mfma32(A2[0][2 * kk + n], H1[p][0], f4{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) *reinterpret_cast<h8*>(T + r * kTstRow + 32 * kk + 8 * q) = A[kk];
+        for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) *reinterpret_cast<h4*>(T + r * kTstRow + 64 + 16 * nt + 4 * q) = h[nt];
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          for (int p = 0; p < kFwdPair; ++p) c[n][p] = mfma32(A2[1][2 * kk + n], H1[p][1], c[n][p]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = lane + 64 * i, row = c >> 4, col = 8 * (c & 15);
-        const int64_t mr = tile * 16 + row;
-        if (mr < M) *reinterpret_cast<h8*>(act + mr * 128 + col) = *reinterpret_cast<const h8*>(T + row * kTstRow + col);
+        for (int p = 0; p < kFwdPair; ++p)
+          H2[p][kk] = join(relu_h4(c[0][p] + b2[2 * kk]), relu_h4(c[1][p] + b2[2 * kk + 1]));
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int p = 0; p < kFwdPair; ++p) {
+        const f4 Z = mfma32(A3[1], H2[p][1], mfma32(A3[0], H2[p][0], f4{0.0f, 0.0f, 0.0f, 0.0f}));
+        z = q == t0 + p ? Z[0] + Z[1] : z;
+      }
+      // a tile's activations (16 rows of 128 halves: one contiguous 4 KB
+      // block of act) through this wavefront's LDS rows, then written with
+      // consecutive 16-byte stores; LDS operations of a wavefront complete in
+      // order, the fences keep the compiler from reordering them
+      if constexpr (KEEP) {
+#pragma unroll
+        for (int p = 0; p < kFwdPair; ++p) {
+          _Float16* T = &Tst[wave][0][0];
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk) {
+            *reinterpret_cast<h8*>(T + r * kTstRow + 32 * kk + 8 * q) = H1[p][kk];
+            const h8 v = H2[p][kk];
+            *reinterpret_cast<h4*>(T + r * kTstRow + kHid + 32 * kk + 4 * q) = h4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<h4*>(T + r * kTstRow + kHid + 32 * kk + 16 + 4 * q) = h4{v[4], v[5], v[6], v[7]};
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = 4 * i + q, t = t0 + p;
+            if (row < left - 16 * t)
+              *reinterpret_cast<h8*>(ap + (16 * t + 4 * i) * 128) =
+                  *reinterpret_cast<const h8*>(T + row * kTstRow + 8 * r);
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+      }
     }
-    // Z[j] = row 4q + j of A3 H2^T: row 0 (lanes q = 0, register 0) is z3 of
-    // match 16 tile + r; the sigmoid on the hardware 2^x and reciprocal
-    // (~1 ulp each)
-    const float e = __builtin_amdgcn_exp2f(-(Z[0] + s.b3) * kLog2e);
-    if (q == 0 && ok) out[m] = out_scale * __builtin_amdgcn_rcpf(1.0f + e);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) fv[t] = fn[t];
+    // the sigmoid on the hardware 2^x and reciprocal (~1 ulp each)
+    const float e = __builtin_amdgcn_exp2f(-(z + b3) * kLog2e);
+    if (lane < left) out[m0 + lane] = out_scale * __builtin_amdgcn_rcpf(1.0f + e);
   }
 }
 
@@ -485,10 +572,10 @@ static fm_status mlp_ptrs(fm_ctx* ctx, const fm_mlp* w, MlpPtrs& p) {
   return FM_OK;
 }
 
-static unsigned mlp_blocks(fm_ctx* ctx, int64_t M, int per_cu = 2) {
+static unsigned mlp_blocks(fm_ctx* ctx, int64_t M) {
   const int64_t tiles = (M + 15) / 16;
   int64_t b = (tiles + 3) / 4;
-  const int64_t cap = (int64_t)ctx->num_cu * per_cu;
+  const int64_t cap = (int64_t)ctx->num_cu * 2;
   return (unsigned)(b < cap ? (b > 0 ? b : 1) : cap);
 }
 
@@ -502,14 +589,15 @@ extern "C" fm_status fm_mlp_forward(fm_ctx* ctx, int64_t M, const float* feats, 
   if (M == 0) return FM_OK;
   if (!feats || !out) return fm_fail(ctx, FM_EINVAL, "fm_mlp_forward: NULL feats or out");
   FM_HIP_TRY(ctx, hipSetDevice(ctx->device));
-  // four workgroups of four wavefronts per CU: the forward kernel's register
-  // use allows four wavefronts per SIMD, and its per-tile chain (feature load,
-  // layer 1 from LDS, MFMA, epilogue) needs them to hide its latency
+  // three workgroups per CU: what the registers let be resident
+  const int64_t groups = (M + kFwdMatches - 1) / kFwdMatches, cap = 3 * (int64_t)ctx->num_cu;
+  const int64_t want = (groups + kFwdWaves - 1) / kFwdWaves;
+  const dim3 grid((unsigned)(want < cap ? want : cap)), block(64 * kFwdWaves);
   if (act)
-    hipLaunchKernelGGL(k_mlp_forward<true>, dim3(mlp_blocks(ctx, M, 4)), dim3(256), 0, (hipStream_t)stream, M, feats,
+    hipLaunchKernelGGL(k_mlp_forward<true>, grid, block, 0, (hipStream_t)stream, M, feats,
                        p, out_scale, out, (_Float16*)act);
   else
-    hipLaunchKernelGGL(k_mlp_forward<false>, dim3(mlp_blocks(ctx, M, 4)), dim3(256), 0, (hipStream_t)stream, M, feats,
+    hipLaunchKernelGGL(k_mlp_forward<false>, grid, block, 0, (hipStream_t)stream, M, feats,
                        p, out_scale, out, (_Float16*)nullptr);
   FM_CHECK_LAUNCH(ctx);
   return FM_OK;
