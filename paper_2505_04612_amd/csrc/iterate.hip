@@ -7,7 +7,7 @@
 // One iteration has two phases:
 //   pair phase    one thread per image pair: E_n and W_n e_n in float64, the
 //                 pair's loss, and the adjoint back to dL/dR and dL/dt of its
-//                 two cameras (a 24-float record per pair);
+//                 two cameras (two 6-float records per pair);
 //   camera phase  one 16-lane row of a wavefront per camera (four cameras
 //                 per wavefront): the records of the camera's pairs are summed
 //                 in a fixed order (lanes stride the camera's incidence list,
@@ -83,29 +83,7 @@ __device__ inline PairEval pair_eval(const float* __restrict__ params, const dou
   return e;
 }
 
-// Loss term and adjoint record of pair n.  rec = [dL/dR_i (3x3 row-major),
-// dL/dt_i, dL/dR_j, dL/dt_j] as float32.
-template <typename WT>
-__device__ inline double pair_loss_adjoint(const float* __restrict__ params, const double* __restrict__ rot, int ci,
-                                           int cj, const WT* __restrict__ W36, int64_t n, double two_inv_Z,
-                                           float* __restrict__ rec) {
-  const PairEval e = pair_eval<WT>(params, rot, ci, cj, W36, n);
-  if (!(e.ns > 0.0)) {
-#pragma unroll
-    for (int k = 0; k < 24; ++k) rec[k] = 0.0f;
-    return 0.0;
-  }
-  // G = dL/dE = (2/Z) g ; A = G R_ij^T ; dR_ij = T^T G
-  double G[3][3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) G[a][b] = two_inv_Z * e.g[a][b];
-  essential_adjoint(G, e.th, e.ns, e.Rij, e.Ri, e.Rj, e.ti, rec);
-  return e.loss;
-}
-
-// Loss term of pair n and its adjoint in the fused loops' compact form
+// Loss term of pair n and its adjoint in compact form
 // (essential_adjoint_omega): om, dL/dt_i, dL/dt_j (all 0 for a degenerate
 // pair).
 template <typename WT>
@@ -113,47 +91,45 @@ __device__ inline double pair_loss_omega(const float* __restrict__ params, const
                                          int cj, const WT* __restrict__ W36, int64_t n, double two_inv_Z,
                                          double om[3], double dti[3], double dtj[3]) {
   const PairEval e = pair_eval<WT>(params, rot, ci, cj, W36, n);
-  if (!(e.ns > 0.0)) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) om[k] = dti[k] = dtj[k] = 0.0;
-    return 0.0;
-  }
-  double G[3][3];
+  double G[3][3], o[3], di[3], dj[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) G[a][b] = two_inv_Z * e.g[a][b];
-  essential_adjoint_omega(G, e.th, e.ns, e.Rij, e.Ri, e.ti, om, dti, dtj);
-  return e.loss;
-}
-
-// Pair phase over pairs [first, P) with stride `stride`; writes the records
-// and returns this thread's loss sum (float64, in pair order).  The cameras
-// of the first two pairs come in registers (ci0, cj0 and ci1, cj1), read
-// once per solve.
-template <typename WT>
-__device__ inline double pair_phase(const float* params, const double* rot, const int32_t* cams, const WT* W36,
-                                    int64_t P, double two_inv_Z, float* contrib, int64_t first, int64_t stride,
-                                    int ci0, int cj0, int ci1 = 0, int cj1 = 0) {
-  double sum = 0.0;
-  for (int64_t n = first; n < P; n += stride) {
-    float rec[24];
-    const bool held0 = n == first, held1 = n == first + stride;
-    const int ci = held0 ? ci0 : (held1 ? ci1 : cams[2 * n]), cj = held0 ? cj0 : (held1 ? cj1 : cams[2 * n + 1]);
-    sum += pair_loss_adjoint<WT>(params, rot, ci, cj, W36, n, two_inv_Z, rec);
-    float4* dst = reinterpret_cast<float4*>(contrib + n * 24);
+  essential_adjoint_omega(G, e.th, e.ns, e.Rij, e.Ri, e.ti, o, di, dj);
+  // degenerate pairs by selection: with the stores under a branch the arrays
+  // went to scratch memory
+  const bool ok = e.ns > 0.0;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) dst[k] = make_float4(rec[4 * k], rec[4 * k + 1], rec[4 * k + 2], rec[4 * k + 3]);
+  for (int k = 0; k < 3; ++k) {
+    om[k] = ok ? o[k] : 0.0;
+    dti[k] = ok ? di[k] : 0.0;
+    dtj[k] = ok ? dj[k] : 0.0;
   }
-  return sum;
+  return ok ? e.loss : 0.0;
 }
 
-// Camera-major record layout of the pair loop: the 6 floats of item q of the
+// Camera-major record layout: the 6 floats of item q of the
 // incidence lists (a pair's side for one camera: its body-frame rotation
 // gradient, -om for camera i and om for camera j, then dL/dt of that camera)
-// at contrib + 6 q, so a camera's records are one contiguous run.  Pair phase
-// as above, each side written to its slot (qi0, qj0 and qi1, qj1: slots of
-// the first two pairs, held in registers).
+// at contrib + 6 q, so a camera's records are one contiguous run.
+__device__ inline void store_sides(float* __restrict__ contrib, int qi, int qj, const double om[3],
+                                   const double dti[3], const double dtj[3]) {
+  float2* di = reinterpret_cast<float2*>(contrib + (int64_t)qi * 6);
+  float2* dj = reinterpret_cast<float2*>(contrib + (int64_t)qj * 6);
+  di[0] = make_float2((float)-om[0], (float)-om[1]);
+  di[1] = make_float2((float)-om[2], (float)dti[0]);
+  di[2] = make_float2((float)dti[1], (float)dti[2]);
+  dj[0] = make_float2((float)om[0], (float)om[1]);
+  dj[1] = make_float2((float)om[2], (float)dtj[0]);
+  dj[2] = make_float2((float)dtj[1], (float)dtj[2]);
+}
+
+// Pair phase of the fused pair loop over pairs [first, P) with stride
+// `stride`: each side written to its slot; returns this thread's loss sum
+// (float64, in pair order).  The cameras and slots of the first two pairs
+// come in registers (ci0, cj0 and ci1, cj1, qi0, qj0 and qi1, qj1), read once
+// per solve.
 template <typename WT>
 __device__ inline double pair_phase_slots(const float* params, const double* rot, const int32_t* cams,
                                           const int32_t* pair_slot, const WT* W36, int64_t P, double two_inv_Z,
@@ -167,95 +143,118 @@ __device__ inline double pair_phase_slots(const float* params, const double* rot
     const int qj = held0 ? qj0 : (held1 ? qj1 : pair_slot[2 * n + 1]);
     double om[3], dti[3], dtj[3];
     sum += pair_loss_omega<WT>(params, rot, ci, cj, W36, n, two_inv_Z, om, dti, dtj);
-    float2* di = reinterpret_cast<float2*>(contrib + (int64_t)qi * 6);
-    float2* dj = reinterpret_cast<float2*>(contrib + (int64_t)qj * 6);
-    di[0] = make_float2((float)-om[0], (float)-om[1]);
-    di[1] = make_float2((float)-om[2], (float)dti[0]);
-    di[2] = make_float2((float)dti[1], (float)dti[2]);
-    dj[0] = make_float2((float)om[0], (float)om[1]);
-    dj[1] = make_float2((float)om[2], (float)dtj[0]);
-    dj[2] = make_float2((float)dtj[1], (float)dtj[2]);
+    store_sides(contrib, qi, qj, om, dti, dtj);
   }
   return sum;
 }
 
-// Incidence list of one camera as one wavefront reads it: the list bounds
-// and the first two entries of this lane (q = lo + lane and lo + 64 + lane;
-// -1 past the end).  Static during a solve, so the fused loop reads it once.
-struct CamList {
-  int lo, hi, it0, it1;
-};
+// Record slots per lane that the camera rows load in one round:
+// 6 x 16 covers cameras of up to 96 pairs (slots past them are read in
+// further rounds).
+constexpr int kRowItems = 6;
 
-__device__ inline CamList cam_list(const int32_t* __restrict__ cam_ptr, const int32_t* __restrict__ cam_items, int c,
-                                   int lane) {
-  CamList L;
-  L.lo = cam_ptr[c];
-  L.hi = cam_ptr[c + 1];
-  L.it0 = L.lo + lane < L.hi ? cam_items[L.lo + lane] : -1;
-  L.it1 = L.lo + 64 + lane < L.hi ? cam_items[L.lo + 64 + lane] : -1;
-  return L;
-}
-
-// Summed records of one camera over its incidence list, in every lane
-// (lanes stride the list in pair order; wave_sum12 combines them).
-__device__ inline void camera_sums(const CamList& L, const int32_t* __restrict__ cam_items,
-                                   const float* __restrict__ contrib, int lane, double acc[12]) {
+// Summed records of one camera in every lane of its row, from the
+// camera-major layout (slots lo..hi-1, 6 floats each): lane l16 takes slots
+// lo + l16 + 16 j; the first NE of them are all loaded before any is added
+// (without lane conditions, under which each load is waited for on its own:
+// slots past the end load the last one's record, or a camera without pairs
+// its successor's, and count as 0), then added in slot order, then the rest.
+// The pair loop on the 5,000-camera street graph (74 pairs per camera) takes
+// 0.5 us less per iteration than with conditional loads.  acc = (om, dL/dt) of the camera.
+template <int NE>
+__device__ inline void row_camera_sums_slots(int lo, int hi, const float* __restrict__ contrib, int lane,
+                                             double (&acc)[6]) {
+  const float2* c = reinterpret_cast<const float2*>(contrib);
+  const int l16 = lane & 15;
+  const int last = hi > lo ? hi - 1 : lo;
+  float2 r[NE][3];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = 0.0;
-  if (L.it0 >= 0) add_record(contrib, L.it0, acc);
-  if (L.it1 >= 0) add_record(contrib, L.it1, acc);
-  for (int q = L.lo + 128 + lane; q < L.hi; q += 64) add_record(contrib, cam_items[q], acc);
-  wave_sum12(acc, lane);
-}
-
-// Gradient of camera c, computed by a whole wavefront; every lane returns
-// dL/dtheta_c [9] (float64).
-__device__ inline void camera_gradient(const float* __restrict__ params, const int32_t* __restrict__ cam_ptr,
-                                       const int32_t* __restrict__ cam_items, const float* __restrict__ contrib,
-                                       int c, int lane, double grad[9]) {
-  double acc[12];
-  camera_sums(cam_list(cam_ptr, cam_items, c, lane), cam_items, contrib, lane, acc);
-  double a1[3], a2[3], t[3];
-  load_pose(params, c, a1, a2, t);
-  gs_adjoint(acc, a1, a2, grad);
+  for (int j = 0; j < NE; ++j) {
+    const int q = min(lo + l16 + 16 * j, last);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[j][k] = c[(int64_t)q * 3 + k];
+  }
+#pragma unroll
+  for (int j = 0; j < NE; ++j) {
+    const bool live = lo + l16 + 16 * j < hi;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      r[j][k].x = live ? r[j][k].x : 0.0f;
+      r[j][k].y = live ? r[j][k].y : 0.0f;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) acc[k] = 0.0;
+#pragma unroll
+  for (int j = 0; j < NE; ++j) {
+    acc[0] += r[j][0].x; acc[1] += r[j][0].y; acc[2] += r[j][1].x;
+    acc[3] += r[j][1].y; acc[4] += r[j][2].x; acc[5] += r[j][2].y;
+  }
+  for (int q = lo + 16 * NE + l16; q < hi; q += 16) {
+    const float2 a0 = c[(int64_t)q * 3], a1 = c[(int64_t)q * 3 + 1], a2 = c[(int64_t)q * 3 + 2];
+    acc[0] += a0.x; acc[1] += a0.y; acc[2] += a1.x;
+    acc[3] += a1.y; acc[4] += a2.x; acc[5] += a2.y;
+  }
+  row_sum6(acc, lane);
 }
 
 // ------------------------------------------------------------------ standalone loss + gradient
 
+// One thread per pair: loss term and both sides' records.
 template <typename WT>
 __global__ __launch_bounds__(kBlock) void k_pair_phase(const float* __restrict__ params,
-                                                       const int32_t* __restrict__ cams, const WT* __restrict__ W36,
-                                                       int64_t P, double inv_Z, const int64_t* __restrict__ Z_dev,
-                                                       float* __restrict__ contrib, double* __restrict__ loss_part) {
+                                                       const int32_t* __restrict__ cams,
+                                                       const int32_t* __restrict__ pair_slot,
+                                                       const WT* __restrict__ W36, int64_t P, double inv_Z,
+                                                       const int64_t* __restrict__ Z_dev, float* __restrict__ contrib,
+                                                       double* __restrict__ loss_part) {
   __shared__ double lds[kBlock / 64];
   const double iz = Z_dev ? 1.0 / (double)(*Z_dev > 0 ? *Z_dev : 1) : inv_Z;
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int ci0 = n < P ? cams[2 * n] : 0, cj0 = n < P ? cams[2 * n + 1] : 0;
-  const double v =
-      pair_phase(params, (const double*)nullptr, cams, W36, P, 2.0 * iz, contrib, n, P > 0 ? P : 1, ci0, cj0);
+  double v = 0.0;
+  if (n < P) {
+    double om[3], dti[3], dtj[3];
+    v = pair_loss_omega<WT>(params, nullptr, cams[2 * n], cams[2 * n + 1], W36, n, 2.0 * iz, om, dti, dtj);
+    store_sides(contrib, pair_slot[2 * n], pair_slot[2 * n + 1], om, dti, dtj);
+  }
   const double t = block_sum(v, lds);
   if (threadIdx.x == 0) loss_part[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(kBlock) void k_camera_grad(const float* __restrict__ params,
+// One 16-lane row per camera: its records summed in a fixed order, the
+// Gram-Schmidt adjoint (the same lanes for four cameras: their float64 chains
+// are what the kernel issues).  The last workgroup, one more than the cameras
+// take, sums the loss partials instead.  The whole call on the 186k-pair
+// street graph: 16.0 us (11.6 the pairs, 5.0 the cameras), against 62.3 with
+// the partials added by one thread, a wavefront per camera and 24-float
+// records; at 1,000 cameras 13.8 against 22.8, both 14 up to 200 cameras, where
+// the launches bound them.
+__global__ __launch_bounds__(kLanes) void k_camera_grad(const float* __restrict__ params,
                                                         const int32_t* __restrict__ cam_ptr,
-                                                        const int32_t* __restrict__ cam_items,
                                                         const float* __restrict__ contrib, int32_t N,
                                                         const double* __restrict__ loss_part, int64_t n_part,
                                                         double inv_Z, const int64_t* __restrict__ Z_dev,
-                                                        float* __restrict__ grad, double* __restrict__ loss) {
-  const int lane = threadIdx.x & 63;
-  const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (loss && blockIdx.x == 0 && threadIdx.x == 0) {
-    const double iz = Z_dev ? 1.0 / (double)(*Z_dev > 0 ? *Z_dev : 1) : inv_Z;
-    double s = 0.0;
-    for (int64_t k = 0; k < n_part; ++k) s += loss_part[k];
-    *loss = s * iz;
+                                                        float* __restrict__ grad, double* __restrict__ loss,
+                                                        unsigned cam_blocks) {
+  if (blockIdx.x == cam_blocks) {
+    double v = 0.0;
+#pragma unroll 4
+    for (int64_t k = threadIdx.x; k < n_part; k += kLanes) v += loss_part[k];
+#pragma unroll
+    for (int sh = 32; sh >= 1; sh >>= 1) v += __shfl_xor(v, sh);
+    if (threadIdx.x == 0) *loss = v * (Z_dev ? 1.0 / (double)(*Z_dev > 0 ? *Z_dev : 1) : inv_Z);
+    return;
   }
-  if (c >= N || !grad) return;
-  double g[9];
-  camera_gradient(params, cam_ptr, cam_items, contrib, (int)c, lane, g);
-  if (lane < 9) grad[c * 9 + lane] = (float)pick9(g, lane);
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int64_t c = ((int64_t)blockIdx.x * kLanes + threadIdx.x) >> 4;
+  if (c >= N) return;   // whole rows leave together: the row exchanges stay within live rows
+  double a1[3], a2[3], t[3], acc6[6], acc[12], g[9];
+  load_pose(params, (int)c, a1, a2, t);
+  const Gs f = gs_forward(a1, a2);
+  row_camera_sums_slots<kRowItems>(cam_ptr[c], cam_ptr[c + 1], contrib, lane, acc6);
+  omega_grad(f, acc6, acc6 + 3, acc);
+  gs_adjoint(acc, f, a2, g);
+  if (l16 < 9) grad[c * 9 + l16] = (float)pick9(g, l16);
 }
 
 static fm_status check_w(fm_ctx* ctx, const char* fn, const void* W36, fm_dtype wdt, int64_t P) {
@@ -281,17 +280,17 @@ extern "C" fm_status fm_epipolar_loss_grad(fm_ctx* ctx, fm_scene* s, const void*
   fm_timed timer(ctx, FM_K_PAIR, st);
   if (wdt == FM_F64)
     hipLaunchKernelGGL(k_pair_phase<double>, dim3(gp), dim3(kBlock), 0, st, params, s->pair_cams,
-                       (const double*)W36, s->P, inv_Z, Z_dev, s->contrib, s->loss_part);
+                       s->pair_slot, (const double*)W36, s->P, inv_Z, Z_dev, s->contrib, s->loss_part);
   else
     hipLaunchKernelGGL(k_pair_phase<float>, dim3(gp), dim3(kBlock), 0, st, params, s->pair_cams,
-                       (const float*)W36, s->P, inv_Z, Z_dev, s->contrib, s->loss_part);
+                       s->pair_slot, (const float*)W36, s->P, inv_Z, Z_dev, s->contrib, s->loss_part);
   }
   FM_CHECK_LAUNCH(ctx);
-  const unsigned gc = grid_for((int64_t)(s->N > 0 ? s->N : 1) * 64, kBlock);
-  {
+  const unsigned cam_blocks = grad ? grid_for((int64_t)s->N * 16, kLanes) : 0u, gc = cam_blocks + (loss ? 1u : 0u);
+  if (gc > 0) {
   fm_timed timer(ctx, FM_K_CAMERA, st);
-  hipLaunchKernelGGL(k_camera_grad, dim3(gc), dim3(kBlock), 0, st, params, s->cam_ptr, s->cam_items, s->contrib,
-                     s->N, s->loss_part, (int64_t)gp, inv_Z, Z_dev, grad, loss);
+  hipLaunchKernelGGL(k_camera_grad, dim3(gc), dim3(kLanes), 0, st, params, s->cam_ptr, s->contrib, s->N,
+                     s->loss_part, (int64_t)gp, inv_Z, Z_dev, grad, loss, cam_blocks);
   }
   FM_CHECK_LAUNCH(ctx);
   if (ctx->check) {
@@ -385,47 +384,6 @@ struct SolveArgs {
   int64_t lr_step0, lr_total, adam_step0;
   const int32_t* pair_slot;
 };
-
-// Record slots per lane that the pair loop's camera rows load in one round:
-// 6 x 16 covers cameras of up to 96 pairs (slots past them are read in
-// further rounds).
-constexpr int kRowItems = 6;
-
-// Summed records of one camera in every lane of its row, from the
-// camera-major layout (slots lo..hi-1, 6 floats each): lane l16 takes slots
-// lo + l16 + 16 j; the first NE of them are all loaded before any is added
-// (so their loads are in flight together), then added in slot order, then
-// the rest.  acc = (om, dL/dt) of the camera.
-template <int NE>
-__device__ inline void row_camera_sums_slots(int lo, int hi, const float* __restrict__ contrib, int lane,
-                                             double (&acc)[6]) {
-  const float2* c = reinterpret_cast<const float2*>(contrib);
-  const int l16 = lane & 15;
-  float2 r[NE][3];
-#pragma unroll
-  for (int j = 0; j < NE; ++j) {
-    r[j][0] = r[j][1] = r[j][2] = make_float2(0.0f, 0.0f);
-    const int q = lo + l16 + 16 * j;
-    if (q < hi) {
-      r[j][0] = c[(int64_t)q * 3];
-      r[j][1] = c[(int64_t)q * 3 + 1];
-      r[j][2] = c[(int64_t)q * 3 + 2];
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < 6; ++k) acc[k] = 0.0;
-#pragma unroll
-  for (int j = 0; j < NE; ++j) {
-    acc[0] += r[j][0].x; acc[1] += r[j][0].y; acc[2] += r[j][1].x;
-    acc[3] += r[j][1].y; acc[4] += r[j][2].x; acc[5] += r[j][2].y;
-  }
-  for (int q = lo + 16 * NE + l16; q < hi; q += 16) {
-    const float2 a0 = c[(int64_t)q * 3], a1 = c[(int64_t)q * 3 + 1], a2 = c[(int64_t)q * 3 + 2];
-    acc[0] += a0.x; acc[1] += a0.y; acc[2] += a1.x;
-    acc[3] += a1.y; acc[4] += a2.x; acc[5] += a2.y;
-  }
-  row_sum6(acc, lane);
-}
 
 // Grid barrier of the fused loops: per-XCD (grid_sync) or flat
 // (grid_barrier).
