@@ -220,12 +220,14 @@ __global__ __launch_bounds__(kSolveBlock) void k_fo_solve(FoSolveArgs a) {
   for (int64_t c = gwave; c < a.N; c += nwaves) fo_store_rot<false>(a.rot, c, a.params[c * 9 + kq], lane);
   grid_barrier(gb);
   // static data of the first 64 incidence entries of this wavefront's first
-  // camera (one per lane: the entry and both cameras), read once
-  int item0 = 0, ci0 = 0, cj0 = 0;
+  // camera (one per lane: the entry and both cameras) and its slot range, read
+  // once
+  int item0 = 0, ci0 = 0, cj0 = 0, lo0 = 0, hi0 = 0;
   if (gwave < a.N) {
-    const int lo = a.cam_ptr[gwave], hi = a.cam_ptr[gwave + 1];
-    if (lo + lane < hi) {
-      item0 = a.cam_items[lo + lane];
+    lo0 = a.cam_ptr[gwave];
+    hi0 = a.cam_ptr[gwave + 1];
+    if (lo0 + lane < hi0) {
+      item0 = a.cam_items[lo0 + lane];
       ci0 = a.cams[2 * (item0 >> 1)];
       cj0 = a.cams[2 * (item0 >> 1) + 1];
     }
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_fo_solve(FoSolveArgs a) {
     // the loop bound is uniform over the wavefront, so the wavefront sums
     // run with every lane present
     for (int64_t c = gwave; c < a.N; c += nwaves) {
-      const int lo = a.cam_ptr[c], hi = a.cam_ptr[c + 1];
+      const int lo = c == gwave ? lo0 : a.cam_ptr[c], hi = c == gwave ? hi0 : a.cam_ptr[c + 1];
       const float p0 = pr[c * 9 + kq];
       float mq = a.m[c * 9 + kq], vq = a.v[c * 9 + kq];
       const float f0 = fr[c];

@@ -18,9 +18,17 @@
 // of magnitude below |W| |e|^2, so float32 would cancel most of its digits.
 #include "fm_internal.h"
 
+// Compact Gram of one pair held in registers (indexed like a pointer to it).
 template <typename WT>
-__device__ inline double load_w(const WT* p, int k) {
-  return (double)p[k];
+struct GramRegs {
+  WT v[36];
+  __device__ const WT& operator[](int k) const { return v[k]; }
+};
+
+template <typename WT>
+__device__ inline void load_gram(const WT* __restrict__ w, GramRegs<WT>& g) {
+#pragma unroll
+  for (int k = 0; k < 36; ++k) g.v[k] = w[k];
 }
 
 // Loss term of pair n and what its adjoint needs: E_n at the current poses
@@ -32,9 +40,9 @@ struct PairEval {
   double ns, loss;
 };
 
-template <typename WT>
+template <typename W>
 __device__ inline PairEval pair_eval(const float* __restrict__ params, const double* __restrict__ rot, int ci, int cj,
-                                     const WT* __restrict__ W36, int64_t n) {
+                                     const W& w) {
   PairEval e;
   double a1[3], a2[3], tj[3], E[3][3];
   if (rot) {
@@ -58,7 +66,6 @@ __device__ inline PairEval pair_eval(const float* __restrict__ params, const dou
   // g = W e with W_{(ab),(cd)} = W36[6 q(a,c) + q(b,d)]: walk the index
   // pairs (a, c) and read only the 6-entry row q(a,c) of the compact Gram
   // for each, so few Gram values are live at once
-  const WT* Wn = W36 + n * 36;
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -69,7 +76,7 @@ __device__ inline PairEval pair_eval(const float* __restrict__ params, const dou
     for (int c = 0; c < 3; ++c) {
       double row[6];
 #pragma unroll
-      for (int k = 0; k < 6; ++k) row[k] = (double)Wn[6 * mono_q(a, c) + k];
+      for (int k = 0; k < 6; ++k) row[k] = (double)w[6 * mono_q(a, c) + k];
 #pragma unroll
       for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -86,11 +93,11 @@ __device__ inline PairEval pair_eval(const float* __restrict__ params, const dou
 // Loss term of pair n and its adjoint in compact form
 // (essential_adjoint_omega): om, dL/dt_i, dL/dt_j (all 0 for a degenerate
 // pair).
-template <typename WT>
+template <typename W>
 __device__ inline double pair_loss_omega(const float* __restrict__ params, const double* __restrict__ rot, int ci,
-                                         int cj, const WT* __restrict__ W36, int64_t n, double two_inv_Z,
-                                         double om[3], double dti[3], double dtj[3]) {
-  const PairEval e = pair_eval<WT>(params, rot, ci, cj, W36, n);
+                                         int cj, const W& w, double two_inv_Z, double om[3], double dti[3],
+                                         double dtj[3]) {
+  const PairEval e = pair_eval(params, rot, ci, cj, w);
   double G[3][3], o[3], di[3], dj[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a)
@@ -142,7 +149,7 @@ __device__ inline double pair_phase_slots(const float* params, const double* rot
     const int qi = held0 ? qi0 : (held1 ? qi1 : pair_slot[2 * n]);
     const int qj = held0 ? qj0 : (held1 ? qj1 : pair_slot[2 * n + 1]);
     double om[3], dti[3], dtj[3];
-    sum += pair_loss_omega<WT>(params, rot, ci, cj, W36, n, two_inv_Z, om, dti, dtj);
+    sum += pair_loss_omega(params, rot, ci, cj, W36 + n * 36, two_inv_Z, om, dti, dtj);
     store_sides(contrib, qi, qj, om, dti, dtj);
   }
   return sum;
@@ -214,7 +221,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_phase(const float* __restrict__
   double v = 0.0;
   if (n < P) {
     double om[3], dti[3], dtj[3];
-    v = pair_loss_omega<WT>(params, nullptr, cams[2 * n], cams[2 * n + 1], W36, n, 2.0 * iz, om, dti, dtj);
+    v = pair_loss_omega(params, nullptr, cams[2 * n], cams[2 * n + 1], W36 + n * 36, 2.0 * iz, om, dti, dtj);
     store_sides(contrib, pair_slot[2 * n], pair_slot[2 * n + 1], om, dti, dtj);
   }
   const double t = block_sum(v, lds);
@@ -576,18 +583,22 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
   const int64_t NR = (int64_t)a.N * 9;
   const int64_t slots = nwaves < a.N ? nwaves : a.N;   // wavefronts with a camera
   // static data of the first 64 incidence entries of this wavefront's first
-  // camera (one per lane: the pair, the camera's side, both cameras), read
-  // once, so that each iteration's loads of that pass (poses, rotations,
-  // Gram) all depend on registers only and are in flight together
-  int n0 = -1, side0 = 0, ci0 = 0, cj0 = 0;
+  // camera (one per lane: the camera's side, both cameras, the pair's Gram)
+  // and the camera's slot range, read once, so that each iteration's loads of
+  // that pass (poses, rotations) depend on registers only and are in flight
+  // together (100 iterations at 200 cameras: 527 us, 533 with the Gram and
+  // the range read in each)
+  int side0 = 0, ci0 = 0, cj0 = 0, lo0 = 0, hi0 = 0;
+  GramRegs<WT> w0{};
   if (gwave < a.N) {
-    const int lo = a.cam_ptr[gwave], hi = a.cam_ptr[gwave + 1];
-    if (lo + lane < hi) {
-      const int item = a.cam_items[lo + lane];
-      n0 = item >> 1;
+    lo0 = a.cam_ptr[gwave];
+    hi0 = a.cam_ptr[gwave + 1];
+    if (lo0 + lane < hi0) {
+      const int item = a.cam_items[lo0 + lane];
       side0 = item & 1;
-      ci0 = a.cams[2 * n0];
-      cj0 = a.cams[2 * n0 + 1];
+      ci0 = a.cams[2 * (item >> 1)];
+      cj0 = a.cams[2 * (item >> 1) + 1];
+      load_gram(W36 + (int64_t)(item >> 1) * 36, w0);
     }
   }
   // rotations of the initial parameters (buffer 0)
@@ -629,7 +640,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
     // the loop bound is uniform over the wavefront, so the wavefront sums
     // run with every lane present
     for (int64_t c = gwave; c < a.N; c += nwaves) {
-      const int lo = a.cam_ptr[c], hi = a.cam_ptr[c + 1];
+      const int lo = c == gwave ? lo0 : a.cam_ptr[c], hi = c == gwave ? hi0 : a.cam_ptr[c + 1];
       // the camera's own parameters and moments (lanes 9..63 read entry 8;
       // m and v are read and written by this wavefront alone) and their
       // Gram-Schmidt, needed by the adjoint below: from registers for the
@@ -657,20 +668,25 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
       double acc6[6], acc[12], lsum = 0.0;
 #pragma unroll
       for (int j = 0; j < 6; ++j) acc6[j] = 0.0;
-      for (int q = lo + lane; q < hi; q += 64) {
-        const bool first = c == gwave && q == lo + lane;
-        const int item = first ? 0 : a.cam_items[q];
-        const int64_t n = first ? n0 : item >> 1;
-        const int side = first ? side0 : item & 1;
-        const int ci = first ? ci0 : a.cams[2 * n], cj = first ? cj0 : a.cams[2 * n + 1];
+      auto add_pair = [&](int ci, int cj, int side, const auto& w) {
         double om[3], dti[3], dtj[3];
-        const double l = pair_loss_omega<WT>(pr, rr, ci, cj, W36, n, 2.0 * iz, om, dti, dtj);
+        const double l = pair_loss_omega(pr, rr, ci, cj, w, 2.0 * iz, om, dti, dtj);
         if (side == 0) lsum += l;   // each pair's loss once, from its first camera
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
           acc6[j] += (double)(float)(side ? om[j] : -om[j]);
           acc6[3 + j] += (double)(float)(side ? dtj[j] : dti[j]);
         }
+      };
+      int q = lo + lane;
+      if (first_cam) {
+        if (q < hi) add_pair(ci0, cj0, side0, w0);
+        q += 64;
+      }
+      for (; q < hi; q += 64) {
+        const int item = a.cam_items[q];
+        const int64_t n = item >> 1;
+        add_pair(a.cams[2 * n], a.cams[2 * n + 1], item & 1, W36 + n * 36);
       }
       lwave += wave_sum6_loss(acc6, lsum, lane);
       omega_grad(f, acc6, acc6 + 3, acc);

@@ -320,11 +320,13 @@ __global__ __launch_bounds__(kSolveBlock) void k_ra_solve_cam(RaCamArgs a) {
   for (int64_t c = gwave; c < a.N; c += nwaves) ra_store_rot(a.rot, c, a.params[6 * c + kq], 0, lane, true);
   grid_barrier(gb);
   // static data of the first 64 incidence entries of this wavefront's first
-  // camera (one per lane), read once for the launch
+  // camera (one per lane) and its slot range, read once for the launch
   RaEntry e0{};
+  int lo0 = 0, hi0 = 0;
   if (gwave < a.N) {
-    const int lo = a.cam_ptr[gwave], hi = a.cam_ptr[gwave + 1];
-    if (lo + lane < hi) e0 = ra_entry(a, lo + lane);
+    lo0 = a.cam_ptr[gwave];
+    hi0 = a.cam_ptr[gwave + 1];
+    if (lo0 + lane < hi0) e0 = ra_entry(a, lo0 + lane);
   }
   StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
   for (int k = 0; k < a.K; ++k) {
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_ra_solve_cam(RaCamArgs a) {
     // the loop bound is uniform over the wavefront, so the wavefront sums
     // run with every lane present
     for (int64_t c = gwave; c < a.N; c += nwaves) {
-      const int lo = a.cam_ptr[c], hi = a.cam_ptr[c + 1];
+      const int lo = c == gwave ? lo0 : a.cam_ptr[c], hi = c == gwave ? hi0 : a.cam_ptr[c + 1];
       const float p0 = pr[6 * c + kq];
       float mq = a.m[6 * c + kq], vq = a.v[6 * c + kq];
       double acc[12];

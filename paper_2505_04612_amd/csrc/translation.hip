@@ -20,13 +20,11 @@ constexpr int kTaMaxRuns = 64;
 // The L1 term of eq. global-translation-objective for one pair, float64, from
 // s = o_j - o_i: u = s/|s|, |u - d|_1.  With `g` it also writes
 // dL/ds = (I - u u^T) sign(u - d) * invP / |s| (sign(0) = 0).  A pair whose
-// centres coincide has no direction: term and record are 0.
+// centres coincide has no direction: term and record are 0, by selection (a
+// branch would keep the chains of several runs from overlapping).
 __device__ inline double ta_term(const double s[3], const double d[3], double invP, double* g) {
   const double ns = sqrt(s[0] * s[0] + s[1] * s[1] + s[2] * s[2]);
-  if (!(ns > 0.0)) {
-    if (g) g[0] = g[1] = g[2] = 0.0;
-    return 0.0;
-  }
+  const bool ok = ns > 0.0;
   const double r = 1.0 / ns;
   double u[3], sg[3], term = 0.0, ug = 0.0;
 #pragma unroll
@@ -39,9 +37,9 @@ __device__ inline double ta_term(const double s[3], const double d[3], double in
   }
   if (g) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) g[k] = (sg[k] - u[k] * ug) * r;
+    for (int k = 0; k < 3; ++k) g[k] = ok ? (sg[k] - u[k] * ug) * r : 0.0;
   }
-  return term;
+  return ok ? term : 0.0;
 }
 
 __device__ inline double ta_term_at(const float* __restrict__ oi, const float* __restrict__ oj, const double d[3]) {
@@ -373,7 +371,7 @@ struct TaCamArgs {
 // cameras and the pair's direction.
 struct TaEntry {
   int item, ci, cj;
-  float d[3];
+  float dx, dy, dz;
 };
 
 __device__ inline TaEntry ta_entry(const TaCamArgs& a, int q) {
@@ -382,8 +380,9 @@ __device__ inline TaEntry ta_entry(const TaCamArgs& a, int q) {
   const int64_t n = e.item >> 1;
   e.ci = a.cams[2 * n];
   e.cj = a.cams[2 * n + 1];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) e.d[k] = a.dirs[3 * n + k];
+  e.dx = a.dirs[3 * n];
+  e.dy = a.dirs[3 * n + 1];
+  e.dz = a.dirs[3 * n + 2];
   return e;
 }
 
@@ -396,7 +395,7 @@ __device__ inline TaEntry ta_entry(const TaCamArgs& a, int q) {
 template <int G>
 __device__ inline void ta_cam_group(const TaCamArgs& a, const float* __restrict__ pr, float* __restrict__ pw,
                                     int64_t c, int lo, int hi, int lane, int r0, double lr, double bc1, double bc2,
-                                    double* wl, bool cached, const TaEntry& e0) {
+                                    double* wl, bool cached, TaEntry e0) {
   const int64_t run_stride = (int64_t)a.N * 3;
   // this lane's own coordinate (lanes past 3G repeat the last one)
   const int l3 = lane < 3 * G ? lane : 3 * G - 1;
@@ -409,15 +408,13 @@ __device__ inline void ta_cam_group(const TaCamArgs& a, const float* __restrict_
 #pragma unroll
   for (int g = 0; g < G; ++g) ls[g] = 0.0;
   for (int q = lo + lane; q < hi; q += 64) {
-    TaEntry e;
-    if (cached && q == lo + lane)
-      e = e0;
-    else
-      e = ta_entry(a, q);
-    const int item = e.item, ci = e.ci, cj = e.cj;
-    double d[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) d[k] = (double)e.d[k];
+    // (selected in registers: the entry chosen by a branch goes to scratch)
+    const bool held = cached && q == lo + lane;
+    TaEntry e{};
+    if (!held) e = ta_entry(a, q);
+    const int item = held ? e0.item : e.item, ci = held ? e0.ci : e.ci, cj = held ? e0.cj : e.cj;
+    const float dx = held ? e0.dx : e.dx, dy = held ? e0.dy : e.dy, dz = held ? e0.dz : e.dz;
+    const double d[3] = {(double)dx, (double)dy, (double)dz};
     float oi[G][3], oj[G][3];
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -470,11 +467,15 @@ __global__ __launch_bounds__(kSolveBlock) void k_ta_solve_cam(TaCamArgs a) {
   const int64_t RS = (int64_t)a.runs * a.part_stride;
   double* wl = a.trace ? wloss[wv] : nullptr;
   // static data of the first 64 incidence entries of this wavefront's first
-  // camera (one per lane), read once for the launch
-  TaEntry e0{0, 0, 0, {0.0f, 0.0f, 0.0f}};
+  // camera (one per lane) and its slot range, read once for the launch (100
+  // iterations of four runs at 200 cameras: 480 us with this and ta_term's
+  // selection, 497 before)
+  TaEntry e0{};
+  int lo0 = 0, hi0 = 0;
   if (gwave < a.N) {
-    const int lo = a.cam_ptr[gwave], hi = a.cam_ptr[gwave + 1];
-    if (lo + lane < hi) e0 = ta_entry(a, lo + lane);
+    lo0 = a.cam_ptr[gwave];
+    hi0 = a.cam_ptr[gwave + 1];
+    if (lo0 + lane < hi0) e0 = ta_entry(a, lo0 + lane);
   }
   StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
   for (int k = 0; k < a.K; ++k) {
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_ta_solve_cam(TaCamArgs a) {
     // the loop bound is uniform over the wavefront, so the wavefront sums
     // run with every lane present
     for (int64_t c = gwave; c < a.N; c += nwaves) {
-      const int lo = a.cam_ptr[c], hi = a.cam_ptr[c + 1];
+      const int lo = c == gwave ? lo0 : a.cam_ptr[c], hi = c == gwave ? hi0 : a.cam_ptr[c + 1];
       int r0 = 0;
       for (; r0 + 4 <= a.runs; r0 += 4) ta_cam_group<4>(a, pr, pw, c, lo, hi, lane, r0, lr, bc1, bc2, wl, c == gwave, e0);
       if (r0 + 2 <= a.runs) {
