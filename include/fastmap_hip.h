@@ -229,10 +229,10 @@ typedef struct {
  * between iterations.  Two loops, same results up to the order of the float64
  * sums: pair by pair (a per-pair phase writes the records, a per-camera phase
  * sums them and steps Adam, grid-wide barriers between the two), or, for
- * graphs below 131,072 pairs when cfg->blocks is 0, camera by camera (one
+ * graphs below 81,920 pairs when cfg->blocks is 0, camera by camera (one
  * wavefront per camera evaluates each of its pairs, so every pair is
- * evaluated from both ends, and one grid barrier per iteration; cfg->blocks
- * < 0 selects this loop at any size).  params, m, v [N,9] float32 are
+ * evaluated from both ends, and waits for its neighbours' parameters instead
+ * of a grid barrier; cfg->blocks < 0 selects this loop at any size).  params, m, v [N,9] float32 are
  * updated in place.  loss_trace [K] double receives L before each update
  * (NULL = not written).  `cfg` is a host pointer. */
 fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* scene, const void* W36, fm_dtype wdtype,
@@ -242,8 +242,8 @@ fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* scene, const void* W36, fm_dt
 
 /* Failed grid barriers of the persistent launches (fm_epipolar_solve,
  * fm_translation_solve, fm_rotation_solve, fm_rotation_init) on this scene
- * since the last call (host value in *failures), then cleared.  A barrier wait is
- * bounded (about a second); if it expires, the launch stops at once and its
+ * since the last call (host value in *failures), then cleared.  A wait (at
+ * a barrier, or for a neighbour's parameters) is bounded; if it expires, the launch stops at once and its
  * results are invalid.  Synchronises the device.  Not expected to be nonzero:
  * the cooperative launch makes every workgroup resident. */
 fm_status fm_solve_barrier_failures(fm_ctx* ctx, fm_scene* scene, int64_t* failures);

@@ -40,6 +40,9 @@ constexpr int kSolveBlock = 512;
 // workgroups make each grid barrier dearer); translation (4 runs) 5.20 ->
 // 4.63, rotation 6.08 -> 5.05, focal 9.39 -> 7.34 going from 512 to 256.
 constexpr int kCamBlock = 256;
+// Words of a camera's mailbox record in the epipolar camera loop: nine parameters,
+// padded to one 128-byte line.
+constexpr int kMailWords = 16;
 
 // Workgroup size and count of a camera-by-camera loop compiled for up to
 // kSolveBlock threads (one wavefront per camera): kCamBlock-thread
@@ -138,6 +141,7 @@ struct fm_scene {
   double* rot = nullptr;          // [2, N, 9] rotations of the current poses (fused solve; two buffers)
   float* params_alt = nullptr;    // [N, 10] second parameter buffer of the camera loops ([N, 9] poses, then [N] focal scales)
   int64_t loss_part_cap = 0;
+  unsigned long long* mail = nullptr;   // [2, N, kMailWords] mailboxes of the epipolar camera loop
   unsigned* bar = nullptr;        // [kBarWords] grid barriers of the persistent loops (layout at kBarWords)
   int coop_blocks = 0;            // max co-resident workgroups of the fused pair loop (kSolveBlock threads)
   int coop_blocks_cam = 0;        // max co-resident workgroups of the fused camera loop (kCamBlock threads)
@@ -556,11 +560,14 @@ __device__ inline double* trace_row(double* part, int64_t slots, int k) {
   return part + (int64_t)(k % (2 * kTraceBatch)) * slots;
 }
 
-// After the barrier of iteration k: the batch it ends, if it ends one (every
-// kTraceBatch iterations, and at the launch's last, K - 1).
+// Whether iteration k ends a batch (every kTraceBatch iterations, and the
+// launch's last, K - 1).
+__device__ inline bool trace_due(int k, int K) { return (k + 1) % kTraceBatch == 0 || k + 1 == K; }
+
+// After the barrier of iteration k: the batch it ends, if it ends one.
 __device__ inline void trace_batch(double* part, int64_t slots, int k, int K, double scale, double* __restrict__ trace,
                                    int64_t gwave, int64_t nwaves, int lane) {
-  if ((k + 1) % kTraceBatch != 0 && k + 1 != K) return;
+  if (!trace_due(k, K)) return;
   const int k0 = k - k % kTraceBatch;
   for (int64_t g = k0 + gwave; g <= k; g += nwaves) {
     const double* p = trace_row(part, slots, (int)g);
@@ -652,34 +659,36 @@ struct StepSched {
 // arithmetic is float64, the stored moments float32.  The bias corrections
 // are applied as products with their reciprocals (uniform over a step, so
 // the persistent loops compute them once per iteration).
-__device__ inline float adam_update(float p, float g, float& m, float& v, double lr, double b1, double b2,
-                                    double eps, double bc1, double bc2) {
+__device__ inline float adam_update_inv(float p, float g, float& m, float& v, double lr, double b1, double b2,
+                                        double eps, double ib1, double ib2) {
   const double md = b1 * (double)m + (1.0 - b1) * (double)g;
   const double vd = b2 * (double)v + (1.0 - b2) * (double)g * (double)g;
   m = (float)md;
   v = (float)vd;
-  const double ib1 = 1.0 / bc1, ib2 = 1.0 / bc2;
   return (float)((double)p - lr * (md * ib1) / (sqrt(vd * ib2) + eps));
+}
+__device__ inline float adam_update(float p, float g, float& m, float& v, double lr, double b1, double b2,
+                                    double eps, double bc1, double bc2) {
+  return adam_update_inv(p, g, m, v, lr, b1, b2, eps, 1.0 / bc1, 1.0 / bc2);
 }
 
 // Pair count below which the epipolar persistent loop runs camera by camera
 // when the caller leaves the grid automatic (the translation and rotation
 // loops, whose pair terms are cheaper, always do): one wavefront
 // per camera evaluates each of its pairs, so every pair is evaluated twice
-// but an iteration needs one grid barrier and no record round trip.  Above
-// it, where one wavefront per camera leaves the high-degree cameras'
-// wavefronts long and the rest idle, the pair loop wins.  Measured with the
-// epipolar loop, float64 Grams, per iteration (camera vs pair loop): 200
-// cameras / 4.9k pairs 10.5 vs 16.1 us; banded graphs 1,000 / 24.7k 12.3 vs
-// 33.4, 2,500 / 124k 34.3 vs 39.9, 5,000 / 249k 47.1 vs 50.7; the 5,000-camera
-// street graph (185k pairs, uneven degrees) 44.3 vs 41.0.
-constexpr int64_t kCamLoopMaxPairs = 131072;
+// but an iteration has no grid barrier and no record round trip.  Above
+// it, where a wavefront has several cameras and passes of 64 pairs to go
+// through, the pair loop wins.  Measured with float32 Grams, us per iteration
+// (camera vs the better pair grid), street graphs of cameras / pairs: 200 /
+// 4.5k 3.4 vs 8.5; 1,000 / 24k 6.2 vs 12.8; 1,000 / 41k 9.5 vs 13.5;
+// 1,500 / 59k 14.1 vs 13.9; 2,500 / 68k 12.0 vs 14.8; 2,000 / 80k 11.8 vs 15.5;
+// 5,000 / 95k 18.8 vs 15.6; 2,500 / 97k 21.2 vs 15.8; 3,000 / 110k 20.1 vs 17.1.
+constexpr int64_t kCamLoopMaxPairs = 81920;
 
-// Workgroup count from which the fused epipolar loops synchronise with the
+// Workgroup count from which the fused pair loop synchronises with the
 // per-XCD grid_sync instead of the flat grid_barrier.  Per iteration, flat
-// vs per-XCD: large street graph, pair loop at 192 workgroups 37.0 vs
-// 29.2 us; camera loop at 256 workgroups 38.2 vs 35.9 us; medium helix
-// scene, camera loop at 25 workgroups 9.75 vs 11.15 us, pair loop at 16 and
+// vs per-XCD, when they were fitted: large street graph, pair loop at 192
+// workgroups 37.0 vs 29.2 us; medium helix scene, pair loop at 16 and
 // 64 workgroups 14.9 vs 17.2 and 15.5 vs 17.3 us (the second level of
 // notification costs more than the fences it saves on small grids).
 constexpr int64_t kXcdSyncMinBlocks = 128;
@@ -795,6 +804,57 @@ __device__ inline void grid_barrier_t(GridBar& gb) {
 __device__ inline void grid_barrier(GridBar& gb) { grid_barrier_t<false>(gb); }
 __device__ inline void grid_barrier_wt(GridBar& gb) { grid_barrier_t<true>(gb); }
 
+// Mailboxes of the camera loops: what a camera's wavefront needs of another
+// camera it takes from that camera's record, which carries the iteration it is
+// for, so that a wavefront waits for its own neighbours only and for nothing
+// but the values themselves (no wait for stores to drain, no count, no
+// generation, no cache invalidation).  A record is `stride` words of 64 bits,
+// each a float32 and the iteration's tag: a word is read and written whole, so
+// a matching tag vouches for its value whatever the order in which the words
+// arrive.  Two records per camera, alternated by iteration: a camera's wavefront
+// overwrites the record of iteration k - 1 when it publishes iteration k + 1,
+// after it took every neighbour's iteration k, which each published after it had
+// taken iteration k - 1 (pairs are listed at both of their cameras).  Tags
+// start at 1 and only grow within a launch; fm_mail_reset clears those
+// an earlier launch left.
+using MailWord = unsigned long long;
+
+__device__ inline void mail_put(MailWord* w, float v, unsigned tag) {
+  __hip_atomic_store(w, ((MailWord)tag << 32) | (MailWord)__float_as_uint(v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The first W words of `rec` (any readable record in lanes without `need`)
+// once all of them carry `tag` in every lane that needs them; every lane of
+// the wavefront calls it.  The wait is bounded as bar_reach's is: if it
+// expires or another workgroup has raised the launch's failure flag, `dead`
+// is set and no later call of this wavefront waits.
+template <int W>
+__device__ inline void mail_take(unsigned* __restrict__ bar, const MailWord* rec, unsigned tag, bool need,
+                                 float (&v)[W], bool& dead) {
+  for (unsigned it = 1;; ++it) {
+    MailWord w[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) w[k] = __hip_atomic_load(rec + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned off = 0u;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      off |= (unsigned)(w[k] >> 32) ^ tag;
+      v[k] = __uint_as_float((unsigned)w[k]);
+    }
+    if (!__any(need & (off != 0u)) || dead) return;
+    if (it % 256 == 0 && (it / 256 >= kBarSpinOuter || bar_load(bar + 64) != 0u)) {
+      dead = true;
+      if (__lane_id() == 0) {
+        __hip_atomic_fetch_add(bar + 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(bar + 96, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      return;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
 // XCD of the running workgroup (hardware register XCC_ID, bits 3:0), and
 // after xcd_register the number of the launch's workgroups on it, the number
 // of XCDs that hold any, and the opening values of the next grid_sync: the
@@ -875,3 +935,5 @@ __device__ inline void grid_sync(unsigned* __restrict__ bar, XcdSync& xs) {
 // the launch's failure flag before a persistent launch (iterate.hip); every
 // launch that uses grid_barrier or grid_sync needs it.
 hipError_t fm_bar_reset(unsigned* bar, hipStream_t st);
+// The same, and the tags of `words` mailbox words.
+hipError_t fm_mail_reset(unsigned* bar, MailWord* mail, int64_t words, hipStream_t st);

@@ -16,6 +16,8 @@
 //                 Adam to one parameter each.
 // The float64 quadratic form matters: near a minimum e^T W e is many orders
 // of magnitude below |W| |e|^2, so float32 would cancel most of its digits.
+#include <type_traits>
+
 #include "fm_internal.h"
 
 // Compact Gram of one pair held in registers (indexed like a pointer to it).
@@ -40,28 +42,10 @@ struct PairEval {
   double ns, loss;
 };
 
+// From the poses in e.Ri, e.ti, e.Rj and tj.
 template <typename W>
-__device__ inline PairEval pair_eval(const float* __restrict__ params, const double* __restrict__ rot, int ci, int cj,
-                                     const W& w) {
-  PairEval e;
-  double a1[3], a2[3], tj[3], E[3][3];
-  if (rot) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      e.ti[k] = (double)params[(int64_t)ci * 9 + 6 + k];
-      tj[k] = (double)params[(int64_t)cj * 9 + 6 + k];
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      e.Ri[k / 3][k % 3] = rot[(int64_t)ci * 9 + k];
-      e.Rj[k / 3][k % 3] = rot[(int64_t)cj * 9 + k];
-    }
-  } else {
-    load_pose(params, ci, a1, a2, e.ti);
-    gs_matrix(gs_forward(a1, a2), e.Ri);
-    load_pose(params, cj, a1, a2, tj);
-    gs_matrix(gs_forward(a1, a2), e.Rj);
-  }
+__device__ inline void pair_terms(PairEval& e, const double tj[3], const W& w) {
+  double E[3][3];
   e.ns = pair_essential(e.Ri, e.ti, e.Rj, tj, e.Rij, e.th, E);
   // g = W e with W_{(ab),(cd)} = W36[6 q(a,c) + q(b,d)]: walk the index
   // pairs (a, c) and read only the 6-entry row q(a,c) of the compact Gram
@@ -87,17 +71,39 @@ __device__ inline PairEval pair_eval(const float* __restrict__ params, const dou
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) e.loss = fma(E[a][b], e.g[a][b], e.loss);
+}
+
+template <typename W>
+__device__ inline PairEval pair_eval(const float* __restrict__ params, const double* __restrict__ rot, int ci, int cj,
+                                     const W& w) {
+  PairEval e;
+  double a1[3], a2[3], tj[3];
+  if (rot) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      e.ti[k] = (double)params[(int64_t)ci * 9 + 6 + k];
+      tj[k] = (double)params[(int64_t)cj * 9 + 6 + k];
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      e.Ri[k / 3][k % 3] = rot[(int64_t)ci * 9 + k];
+      e.Rj[k / 3][k % 3] = rot[(int64_t)cj * 9 + k];
+    }
+  } else {
+    load_pose(params, ci, a1, a2, e.ti);
+    gs_matrix(gs_forward(a1, a2), e.Ri);
+    load_pose(params, cj, a1, a2, tj);
+    gs_matrix(gs_forward(a1, a2), e.Rj);
+  }
+  pair_terms(e, tj, w);
   return e;
 }
 
-// Loss term of pair n and its adjoint in compact form
+// Loss term of an evaluated pair and its adjoint in compact form
 // (essential_adjoint_omega): om, dL/dt_i, dL/dt_j (all 0 for a degenerate
 // pair).
-template <typename W>
-__device__ inline double pair_loss_omega(const float* __restrict__ params, const double* __restrict__ rot, int ci,
-                                         int cj, const W& w, double two_inv_Z, double om[3], double dti[3],
-                                         double dtj[3]) {
-  const PairEval e = pair_eval(params, rot, ci, cj, w);
+__device__ inline double pair_adjoint(const PairEval& e, double two_inv_Z, double om[3], double dti[3],
+                                      double dtj[3]) {
   double G[3][3], o[3], di[3], dj[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a)
@@ -114,6 +120,13 @@ __device__ inline double pair_loss_omega(const float* __restrict__ params, const
     dtj[k] = ok ? dj[k] : 0.0;
   }
   return ok ? e.loss : 0.0;
+}
+
+template <typename W>
+__device__ inline double pair_loss_omega(const float* __restrict__ params, const double* __restrict__ rot, int ci,
+                                         int cj, const W& w, double two_inv_Z, double om[3], double dti[3],
+                                         double dtj[3]) {
+  return pair_adjoint(pair_eval(params, rot, ci, cj, w), two_inv_Z, om, dti, dtj);
 }
 
 // Camera-major record layout: the 6 floats of item q of the
@@ -347,7 +360,7 @@ extern "C" fm_status fm_adam_step(fm_ctx* ctx, int64_t n, float* p, const float*
 // Re-arms the barriers before a launch: counts, generations and XCD
 // registrations start at 0, and the launch's failure flag is cleared (a
 // launch that ended on a failed barrier leaves it set).
-__global__ void k_bar_reset(unsigned* __restrict__ bar) {
+__device__ inline void bar_clear(unsigned* __restrict__ bar) {
   if (threadIdx.x == 0) {
     bar[0] = 0u;
     bar[32] = 0u;
@@ -363,8 +376,23 @@ __global__ void k_bar_reset(unsigned* __restrict__ bar) {
   }
 }
 
+__global__ void k_bar_reset(unsigned* __restrict__ bar) { bar_clear(bar); }
+
 hipError_t fm_bar_reset(unsigned* bar, hipStream_t st) {
   hipLaunchKernelGGL(k_bar_reset, dim3(1), dim3(64), 0, st, bar);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(kBlock) void k_mail_reset(unsigned* __restrict__ bar, MailWord* __restrict__ mail,
+                                                       int64_t words) {
+  if (blockIdx.x == 0) bar_clear(bar);
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < words) mail[k] = 0;
+}
+
+hipError_t fm_mail_reset(unsigned* bar, MailWord* mail, int64_t words, hipStream_t st) {
+  hipLaunchKernelGGL(k_mail_reset, dim3(grid_for(words > 0 ? words : 1, kBlock)), dim3(kBlock), 0, st, bar, mail,
+                     words);
   return hipGetLastError();
 }
 
@@ -507,20 +535,21 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
 // lane evaluates one of the camera's pairs (its loss and the adjoint for the
 // camera's own side, so every pair is evaluated twice, once from each end),
 // the wavefront sums them in a fixed order and lanes 0..8 take the Adam
-// step.  With no pair records to exchange, an iteration needs one grid
-// barrier instead of two; the parameters and rotations a wavefront reads of
-// other cameras are double-buffered by iteration parity so that each camera
-// updates its own without a second barrier.
+// step.  The parameters of the other cameras come from their mailboxes
+// (mail_take), so an iteration has no grid barrier and leaves the caches
+// alone: 100 iterations at 200 cameras 377 us, 527 with parameters and
+// rotations exchanged through a grid barrier.  What is left is one
+// wavefront's chain of float64 arithmetic (about 2.4 us an iteration) and the
+// way of a store to another XCD's load.
 struct CamSolveArgs {
-  float* params;       // buffer 0 (the caller's)
-  float* params_alt;   // buffer 1 [N, 9]
+  float* params;
   float* m;
   float* v;
   const int32_t* cams;
   const void* W36;
   const int32_t* cam_ptr;
   const int32_t* cam_items;
-  double* rot;         // [2, N, 9]
+  MailWord* mail;      // [2, N, kMailWords]
   double* loss_part;   // [2 kTraceBatch, min(N, wavefronts)]
   double* loss_trace;
   unsigned* bar;
@@ -546,32 +575,30 @@ __device__ inline Gs cam_gs(float p0, double a2[3]) {
   return gs_forward(a1, a2);
 }
 
-// Rotation of an already formed Gram-Schmidt, stored by lanes 0..8 at
-// rot[c] (written through to memory if WTS).
-template <bool WTS>
-__device__ inline void cam_store_gs(double* __restrict__ rot, int64_t c, const Gs& f, int lane) {
-  double R[3][3];
-  gs_matrix(f, R);
-  if (lane < 9) {
-    double rv = R[0][0];
-#pragma unroll
-    for (int j = 1; j < 9; ++j) rv = (lane == j) ? R[j / 3][j % 3] : rv;
-    if constexpr (WTS)
-      store_wt(&rot[c * 9 + lane], rv);
-    else
-      rot[c * 9 + lane] = rv;
+// Incidence entry lo + q0 + lane of camera c and the camera's slot range; in
+// lanes past the end (`live` false) the last entry, and for a camera without
+// pairs or past N entry 0, so that what they point at can be read.
+struct CamSlot {
+  int lo, hi, item, other;
+  bool live;
+};
+
+__device__ inline CamSlot cam_slot(const CamSolveArgs& a, int64_t c, int q0, int lane) {
+  CamSlot s{0, 0, 0, 0, false};
+  if (c < a.N) {
+    s.lo = a.cam_ptr[c];
+    s.hi = a.cam_ptr[c + 1];
+    if (s.lo < s.hi) {
+      const int q = s.lo + q0 + lane;
+      s.live = q < s.hi;
+      s.item = a.cam_items[s.live ? q : s.hi - 1];
+      s.other = a.cams[(int64_t)s.item ^ 1];
+    }
   }
+  return s;
 }
 
-// Rotation of the parameters p0 held by lanes 0..5 of the wavefront, stored
-// by lanes 0..8 at rot[c] (written through to memory if WTS).
-template <bool WTS>
-__device__ inline void cam_store_rot(double* __restrict__ rot, int64_t c, float p0, int lane) {
-  double a2[3];
-  cam_store_gs<WTS>(rot, c, cam_gs(p0, a2), lane);
-}
-
-template <typename WT, bool XS>
+template <typename WT>
 __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
   const double iz = a.Z_dev ? 1.0 / (double)(*a.Z_dev > 0 ? *a.Z_dev : 1) : a.inv_Z;
   const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -580,36 +607,23 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
   const int64_t gwave = gtid >> 6, nwaves = gsize >> 6;
   const int kq = lane < 9 ? lane : 8;
   const WT* W36 = reinterpret_cast<const WT*>(a.W36);
-  const int64_t NR = (int64_t)a.N * 9;
+  const int64_t NM = (int64_t)a.N * kMailWords;
   const int64_t slots = nwaves < a.N ? nwaves : a.N;   // wavefronts with a camera
-  // static data of the first 64 incidence entries of this wavefront's first
-  // camera (one per lane: the camera's side, both cameras, the pair's Gram)
-  // and the camera's slot range, read once, so that each iteration's loads of
-  // that pass (poses, rotations) depend on registers only and are in flight
-  // together (100 iterations at 200 cameras: 527 us, 533 with the Gram and
-  // the range read in each)
-  int side0 = 0, ci0 = 0, cj0 = 0, lo0 = 0, hi0 = 0;
-  GramRegs<WT> w0{};
-  if (gwave < a.N) {
-    lo0 = a.cam_ptr[gwave];
-    hi0 = a.cam_ptr[gwave + 1];
-    if (lo0 + lane < hi0) {
-      const int item = a.cam_items[lo0 + lane];
-      side0 = item & 1;
-      ci0 = a.cams[2 * (item >> 1)];
-      cj0 = a.cams[2 * (item >> 1) + 1];
-      load_gram(W36 + (int64_t)(item >> 1) * 36, w0);
-    }
-  }
-  // rotations of the initial parameters (buffer 0)
+  // first records (buffer 0, tag 1)
   for (int64_t c = gwave; c < a.N; c += nwaves) {
     const float p0 = a.params[c * 9 + kq];
-    cam_store_rot<false>(a.rot, c, p0, lane);
+    if (lane < 9) mail_put(a.mail + c * kMailWords + lane, p0, 1u);
   }
+  // static data, read once: this lane's first two incidence entries of the
+  // wavefront's first camera and the Gram of the first of them, the lane's
+  // first entry of the wavefront's second camera, both cameras' slot ranges
+  const CamSlot s0 = cam_slot(a, gwave, 0, lane), s1 = cam_slot(a, gwave, 64, lane),
+                n0 = cam_slot(a, gwave + nwaves, 0, lane);
+  GramRegs<WT> w0{};
+  if (s0.live) load_gram(W36 + (int64_t)(s0.item >> 1) * 36, w0);
   // the wavefront's first camera stays in registers for the launch: its
   // parameters, Adam moments and their Gram-Schmidt, carried from one
-  // iteration's update to the next instead of reloaded (after the barrier's
-  // invalidation) and recomputed; its moments are stored once at the end
+  // iteration's update to the next
   const bool own = gwave < a.N;
   float p_own = 0.0f, m_own = 0.0f, v_own = 0.0f;
   double a2_own[3] = {0.0, 1.0, 0.0};
@@ -621,56 +635,51 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
     f_own = cam_gs(p_own, a2_own);
   }
   GridBar gb = grid_bar(a.bar);
-  XcdSync xs = {};
-  if constexpr (XS)
-    xs = xcd_register(gb);
-  else
-    grid_barrier(gb);
+  bool dead = false;
   StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
   for (int k = 0; k < a.K; ++k) {
-    const int rb = k & 1;
-    const float* pr = rb ? a.params_alt : a.params;
-    float* pw = rb ? a.params : a.params_alt;
-    const double* rr = a.rot + rb * NR;
-    double* rw = a.rot + (rb ^ 1) * NR;
-    const double frac = sch.frac;
-    const double bc1 = 1.0 - sch.p1, bc2 = 1.0 - sch.p2;
+    const MailWord* in = a.mail + (k & 1) * NM;
+    MailWord* out = a.mail + ((k & 1) ^ 1) * NM;
+    const unsigned tag = (unsigned)k + 1u;
+    // the step's scalars before the wait (pinned there: sunk to their use
+    // they would follow it)
+    double lr = (lane < 6 ? a.lr_rot : a.lr_t) * sch.frac, ib1 = 1.0 / (1.0 - sch.p1), ib2 = 1.0 / (1.0 - sch.p2);
     sch.next();
+    asm volatile("" : "+v"(lr), "+v"(ib1), "+v"(ib2));
     double lwave = 0.0;   // in lane kLossLane: the wavefront's loss
-    // the loop bound is uniform over the wavefront, so the wavefront sums
-    // run with every lane present
-    for (int64_t c = gwave; c < a.N; c += nwaves) {
-      const int lo = c == gwave ? lo0 : a.cam_ptr[c], hi = c == gwave ? hi0 : a.cam_ptr[c + 1];
-      // the camera's own parameters and moments (lanes 9..63 read entry 8;
-      // m and v are read and written by this wavefront alone) and their
-      // Gram-Schmidt, needed by the adjoint below: from registers for the
-      // first camera, else loaded and formed ahead of the pair evaluations
-      // (so that it overlaps their loads)
-      const bool first_cam = c == gwave;
-      float p0, mq, vq;
-      double a2[3], g[9];
-      Gs f;
-      if (first_cam) {
-        p0 = p_own;
-        mq = m_own;
-        vq = v_own;
+    // one camera: its parameters and moments
+    // (lanes 9..63 hold entry 8; no other wavefront reads or writes them in
+    // memory) and their Gram-Schmidt f.  All 64 lanes take part.
+    auto camera = [&](auto first_cam, int64_t c, const CamSlot& held, float& p0, float& mq, float& vq,
+                      const double (&a2)[3], const Gs& f) {
+      double g[9], R[3][3], t[3];
+      gs_matrix(f, R);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) a2[j] = a2_own[j];
-        f = f_own;
-      } else {
-        p0 = pr[c * 9 + kq];
-        mq = a.m[c * 9 + kq];
-        vq = a.v[c * 9 + kq];
-        f = cam_gs(p0, a2);
-      }
+      for (int j = 0; j < 3; ++j) t[j] = (double)__shfl(p0, 6 + j);
       // this camera's side of each of its pairs: body-frame rotation
       // gradient (om for camera j, -om for camera i) and dL/dt
       double acc6[6], acc[12], lsum = 0.0;
 #pragma unroll
       for (int j = 0; j < 6; ++j) acc6[j] = 0.0;
-      auto add_pair = [&](int ci, int cj, int side, const auto& w) {
-        double om[3], dti[3], dtj[3];
-        const double l = pair_loss_omega(pr, rr, ci, cj, w, 2.0 * iz, om, dti, dtj);
+      auto add_pair = [&](int side, const float (&po)[9], const auto& w) {
+        const double o1[3] = {(double)po[0], (double)po[1], (double)po[2]};
+        const double o2[3] = {(double)po[3], (double)po[4], (double)po[5]};
+        double Ro[3][3], tj[3], om[3], dti[3], dtj[3];
+        gs_matrix(gs_forward(o1, o2), Ro);
+        PairEval e;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const double to = (double)po[6 + j];
+          e.ti[j] = side ? to : t[j];
+          tj[j] = side ? t[j] : to;
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            e.Ri[j][i] = side ? Ro[j][i] : R[j][i];
+            e.Rj[j][i] = side ? R[j][i] : Ro[j][i];
+          }
+        }
+        pair_terms(e, tj, w);
+        const double l = pair_adjoint(e, 2.0 * iz, om, dti, dtj);
         if (side == 0) lsum += l;   // each pair's loss once, from its first camera
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
@@ -678,66 +687,54 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
           acc6[3 + j] += (double)(float)(side ? dtj[j] : dti[j]);
         }
       };
-      int q = lo + lane;
-      if (first_cam) {
-        if (q < hi) add_pair(ci0, cj0, side0, w0);
-        q += 64;
+      float po[9];
+      if (first_cam.value && s0.lo < s0.hi) {
+        mail_take(a.bar, in + (int64_t)s0.other * kMailWords, tag, s0.live, po, dead);
+        if (s0.live) add_pair(s0.item & 1, po, w0);
       }
-      for (; q < hi; q += 64) {
-        const int item = a.cam_items[q];
-        const int64_t n = item >> 1;
-        add_pair(a.cams[2 * n], a.cams[2 * n + 1], item & 1, W36 + n * 36);
+      // entries from memory, the first of these passes' held in `held`; the
+      // Grams are on their way during the wait
+      for (int q0 = first_cam.value ? 64 : 0; held.lo + q0 < held.hi; q0 += 64) {
+        const CamSlot e = q0 == (first_cam.value ? 64 : 0) ? held : cam_slot(a, c, q0, lane);
+        GramRegs<WT> w;
+        load_gram(W36 + (int64_t)(e.item >> 1) * 36, w);
+        mail_take(a.bar, in + (int64_t)e.other * kMailWords, tag, e.live, po, dead);
+        if (e.live) add_pair(e.item & 1, po, w);
       }
       lwave += wave_sum6_loss(acc6, lsum, lane);
       omega_grad(f, acc6, acc6 + 3, acc);
       gs_adjoint(acc, f, a2, g);
-      const double lr = (lane < 6 ? a.lr_rot : a.lr_t) * frac;
-      const float pq = adam_update(p0, (float)pick9(g, kq), mq, vq, lr, a.b1, a.b2, a.eps, bc1, bc2);
-      // what other workgroups read (parameters, rotations, loss partials)
-      // is written through to memory on the flat barrier's path; the Adam
-      // moments stay with this wavefront
+      p0 = adam_update_inv(p0, (float)pick9(g, kq), mq, vq, lr, a.b1, a.b2, a.eps, ib1, ib2);
+      if (lane < 9) mail_put(out + c * kMailWords + lane, p0, tag + 1u);
+    };
+    if (own) {
+      camera(std::true_type{}, gwave, s1, p_own, m_own, v_own, a2_own, f_own);
+      f_own = cam_gs(p_own, a2_own);
+    }
+    for (int64_t c = gwave + nwaves; c < a.N; c += nwaves) {
+      float p0 = a.params[c * 9 + kq], mq = a.m[c * 9 + kq], vq = a.v[c * 9 + kq];
+      double a2[3];
+      const Gs f = cam_gs(p0, a2);
+      camera(std::false_type{}, c, c == gwave + nwaves ? n0 : cam_slot(a, c, 0, lane), p0, mq, vq, a2, f);
       if (lane < 9) {
-        if constexpr (XS)
-          pw[c * 9 + lane] = pq;
-        else
-          store_wt(&pw[c * 9 + lane], pq);
-        if (!first_cam) {
-          a.m[c * 9 + lane] = mq;
-          a.v[c * 9 + lane] = vq;
-        }
-      }
-      if (first_cam) {
-        p_own = pq;
-        m_own = mq;
-        v_own = vq;
-        f_own = cam_gs(pq, a2_own);
-        cam_store_gs<!XS>(rw, c, f_own, lane);
-      } else {
-        cam_store_rot<!XS>(rw, c, pq, lane);
+        a.params[c * 9 + lane] = p0;
+        a.m[c * 9 + lane] = mq;
+        a.v[c * 9 + lane] = vq;
       }
     }
-    if (a.loss_trace && lane == kLossLane && gwave < slots) {
-      double* lp = trace_row(a.loss_part, slots, k) + gwave;
-      if constexpr (XS)
-        *lp = lwave;
-      else
-        store_wt(lp, lwave);
+    if (a.loss_trace) {
+      if (lane == kLossLane && gwave < slots) store_wt(trace_row(a.loss_part, slots, k) + gwave, lwave);
+      if (trace_due(k, a.K)) {
+        grid_barrier_wt(gb);
+        trace_batch(a.loss_part, slots, k, a.K, iz, a.loss_trace, gwave, nwaves, lane);
+      }
     }
-    if constexpr (XS)
-      grid_sync(a.bar, xs);
-    else
-      grid_barrier_wt(gb);
-    if (a.loss_trace) trace_batch(a.loss_part, slots, k, a.K, iz, a.loss_trace, gwave, nwaves, lane);
   }
-  // the first camera's moments, kept in registers during the launch
+  // the first camera's values, kept in registers during the launch
   if (own && lane < 9) {
+    a.params[gwave * 9 + lane] = p_own;
     a.m[gwave * 9 + lane] = m_own;
     a.v[gwave * 9 + lane] = v_own;
-  }
-  // after an odd number of iterations the latest parameters are in buffer 1
-  if (a.K & 1) {
-    for (int64_t c = gwave; c < a.N; c += nwaves)
-      if (lane < 9) a.params[c * 9 + lane] = a.params_alt[c * 9 + lane];
   }
 }
 
@@ -764,10 +761,7 @@ static bool occ_min(K kernel, int block, int& per_cu) {
 
 int fm_solve_coop_blocks(fm_ctx* ctx, bool cam) {
   int per_cu = 1 << 20;
-  const bool ok = cam ? occ_min(k_solve_cam<double, false>, kCamBlock, per_cu) &&
-                            occ_min(k_solve_cam<float, false>, kCamBlock, per_cu) &&
-                            occ_min(k_solve_cam<double, true>, kCamBlock, per_cu) &&
-                            occ_min(k_solve_cam<float, true>, kCamBlock, per_cu)
+  const bool ok = cam ? occ_min(k_solve_cam<double>, kCamBlock, per_cu) && occ_min(k_solve_cam<float>, kCamBlock, per_cu)
                       : occ_min(k_solve<double, false>, kSolveBlock, per_cu) &&
                             occ_min(k_solve<float, false>, kSolveBlock, per_cu) &&
                             occ_min(k_solve<double, true>, kSolveBlock, per_cu) &&
@@ -775,14 +769,10 @@ int fm_solve_coop_blocks(fm_ctx* ctx, bool cam) {
   return ok ? per_cu * ctx->num_cu : 0;
 }
 
-// Instantiation of a fused loop (camera or pair loop) for the Gram dtype
-// and the barrier kind (per-XCD from kXcdSyncMinBlocks workgroups on).
-static const void* loop_kernel(bool cam, fm_dtype wdt, int64_t blocks) {
+// Instantiation of the pair loop for the Gram dtype and the barrier kind
+// (per-XCD from kXcdSyncMinBlocks workgroups on).
+static const void* pair_loop_kernel(fm_dtype wdt, int64_t blocks) {
   const bool xs = blocks >= kXcdSyncMinBlocks;
-  if (cam) {
-    if (wdt == FM_F64) return xs ? (const void*)k_solve_cam<double, true> : (const void*)k_solve_cam<double, false>;
-    return xs ? (const void*)k_solve_cam<float, true> : (const void*)k_solve_cam<float, false>;
-  }
   if (wdt == FM_F64) return xs ? (const void*)k_solve<double, true> : (const void*)k_solve<double, false>;
   return xs ? (const void*)k_solve<float, true> : (const void*)k_solve<float, false>;
 }
@@ -829,35 +819,41 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   a.lr_step0 = cfg->lr_step0; a.lr_total = cfg->lr_total_steps; a.adam_step0 = cfg->adam_step0;
   a.pair_slot = s->pair_slot;
   void* args[] = {&a};
-  hipLaunchKernelGGL(k_bar_reset, dim3(1), dim3(64), 0, (hipStream_t)stream, s->bar);
-  FM_CHECK_LAUNCH(ctx);
   // automatic grid below kCamLoopMaxPairs, or cfg->blocks < 0: the
-  // camera-centric loop, one barrier per iteration; a forced workgroup count
+  // camera-centric loop, no barrier in an iteration; a forced workgroup count
   // or a larger graph runs the pair loop
-  int64_t want_cam = grid_for((int64_t)s->N * 64, kCamBlock);
+  // (workgroups of two wavefronts while they fit one to a CU: the wavefronts'
+  // scattered reads of the mailboxes spread over twice as many CUs: 100
+  // iterations at 200 cameras 417 us against 433, at 500 677 against 926;
+  // past a workgroup per CU four are better, at 1,000 612 against 673)
+  const int cam_threads = ((int64_t)s->N + 1) / 2 <= ctx->num_cu ? kCamBlock / 2 : kCamBlock;
+  int64_t want_cam = grid_for((int64_t)s->N * 64, cam_threads);
   if (want_cam > s->coop_blocks_cam) want_cam = s->coop_blocks_cam;
   if ((cfg->blocks < 0 || (cfg->blocks == 0 && s->P < kCamLoopMaxPairs)) &&
-      2 * kTraceBatch * want_cam * (kCamBlock / 64) <= s->loss_part_cap) {
+      2 * kTraceBatch * want_cam * (cam_threads / 64) <= s->loss_part_cap) {
     CamSolveArgs ca;
-    ca.params = params; ca.params_alt = s->params_alt; ca.m = m; ca.v = v;
+    ca.params = params; ca.m = m; ca.v = v;
     ca.cams = s->pair_cams; ca.W36 = W36; ca.cam_ptr = s->cam_ptr; ca.cam_items = s->cam_items;
-    ca.rot = s->rot; ca.loss_part = s->loss_part; ca.loss_trace = loss_trace; ca.bar = s->bar; ca.Z_dev = Z_dev;
+    ca.mail = s->mail; ca.loss_part = s->loss_part; ca.loss_trace = loss_trace; ca.bar = s->bar; ca.Z_dev = Z_dev;
     ca.inv_Z = inv_Z; ca.P = s->P; ca.N = s->N; ca.K = K;
     ca.lr_rot = a.lr_rot; ca.lr_t = a.lr_t; ca.log_frac = a.log_frac;
     ca.b1 = a.b1; ca.b2 = a.b2; ca.eps = a.eps;
     ca.lr_step0 = a.lr_step0; ca.lr_total = a.lr_total; ca.adam_step0 = a.adam_step0;
     void* cargs[] = {&ca};
+    FM_HIP_TRY(ctx, fm_mail_reset(s->bar, s->mail, 2 * (int64_t)s->N * kMailWords, (hipStream_t)stream));
     {
     fm_timed timer(ctx, FM_K_SOLVE, (hipStream_t)stream);
-    hipError_t e = hipLaunchCooperativeKernel(loop_kernel(true, wdt, want_cam), dim3((unsigned)want_cam),
-                                              dim3(kCamBlock), cargs, 0, (hipStream_t)stream);
+    const void* kernel = wdt == FM_F64 ? (const void*)k_solve_cam<double> : (const void*)k_solve_cam<float>;
+    hipError_t e = hipLaunchCooperativeKernel(kernel, dim3((unsigned)want_cam), dim3(cam_threads), cargs, 0,
+                                              (hipStream_t)stream);
     if (e != hipSuccess) return fm_fail(ctx, FM_ECOOP, "cooperative launch failed: %s", hipGetErrorString(e));
     }
     return solve_checks(ctx, s, params, loss_trace, K, (hipStream_t)stream);
   }
+  FM_HIP_TRY(ctx, fm_bar_reset(s->bar, (hipStream_t)stream));
   {
   fm_timed timer(ctx, FM_K_SOLVE, (hipStream_t)stream);
-  hipError_t e = hipLaunchCooperativeKernel(loop_kernel(false, wdt, want), dim3((unsigned)want), dim3(kSolveBlock),
+  hipError_t e = hipLaunchCooperativeKernel(pair_loop_kernel(wdt, want), dim3((unsigned)want), dim3(kSolveBlock),
                                             args, 0, (hipStream_t)stream);
   if (e != hipSuccess) return fm_fail(ctx, FM_ECOOP, "cooperative launch failed: %s", hipGetErrorString(e));
   }

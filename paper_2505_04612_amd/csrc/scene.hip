@@ -306,6 +306,7 @@ static void scene_free(fm_scene* s) {
   (void)hipFree(s->loss_part);
   (void)hipFree(s->rot);
   (void)hipFree(s->params_alt);
+  (void)hipFree(s->mail);
   (void)hipFree(s->bar);
   (void)hipFree(s->ta_rec);
   (void)hipFree(s->ta_part);
@@ -479,6 +480,7 @@ extern "C" fm_status fm_scene_create(fm_ctx* ctx, int64_t P, int64_t M, int32_t 
   SCENE_TRY(hipMalloc(&s->loss_part, sizeof(double) * s->loss_part_cap));
   SCENE_TRY(hipMalloc(&s->rot, sizeof(double) * 9 * 2 * (N > 0 ? N : 1)));
   SCENE_TRY(hipMalloc(&s->params_alt, sizeof(float) * 10 * (N > 0 ? N : 1)));
+  SCENE_TRY(hipMalloc(&s->mail, sizeof(MailWord) * 2 * kMailWords * (N > 0 ? N : 1)));
   SCENE_TRY(hipMalloc(&s->bar, sizeof(unsigned) * kBarWords));
   SCENE_TRY(hipMemsetAsync(s->bar, 0, sizeof(unsigned) * kBarWords, st));
   SCENE_TRY(hipStreamSynchronize(st));
