@@ -151,6 +151,7 @@ struct fm_scene {
   void* ta_rec = nullptr;         // [ta_runs_cap, P] float4 per-pair records: dL/ds and the pair's L1 term
   double* ta_part = nullptr;      // [2, ta_runs_cap, ta_part_cap] per-workgroup loss partials
   float* ta_alt = nullptr;        // [ta_runs_cap, N, 3] second centre buffer of the camera loop
+  unsigned long long* ta_mail = nullptr;   // [2, N, 3 ta_runs_cap rounded up to lines] mailboxes of the camera loop
   double* ta_stats = nullptr;     // [ta_runs_cap, 4] centroid and mean norm of each run
   int ta_coop_blocks = 0;         // max co-resident blocks of the translation loop
   int fo_coop_blocks = 0;         // max co-resident blocks of the focal loop
@@ -680,9 +681,10 @@ __device__ inline float adam_update(float p, float g, float& m, float& v, double
 // it, where a wavefront has several cameras and passes of 64 pairs to go
 // through, the pair loop wins.  Measured with float32 Grams, us per iteration
 // (camera vs the better pair grid), street graphs of cameras / pairs: 200 /
-// 4.5k 3.4 vs 8.5; 1,000 / 24k 6.2 vs 12.8; 1,000 / 41k 9.5 vs 13.5;
-// 1,500 / 59k 14.1 vs 13.9; 2,500 / 68k 12.0 vs 14.8; 2,000 / 80k 11.8 vs 15.5;
-// 5,000 / 95k 18.8 vs 15.6; 2,500 / 97k 21.2 vs 15.8; 3,000 / 110k 20.1 vs 17.1.
+// 4.5k 3.3 vs 8.5; 1,000 / 24k 4.8 vs 12.8; 1,000 / 41k 7.3 vs 13.5;
+// 2,500 / 68k 10.9 vs 14.8; 2,000 / 80k 11.1 vs 15.5; and, with 8-byte reads of
+// the mailboxes, 5,000 / 95k 18.8 vs 15.6; 2,500 / 97k 21.2 vs 15.8; 3,000 / 110k
+// 20.1 vs 17.1.  Dense graphs: 100 / 5k 4.9 vs 10.3, 400 / 60k 14.9 vs 19.7.
 constexpr int64_t kCamLoopMaxPairs = 81920;
 
 // Workgroup count from which the fused pair loop synchronises with the
@@ -711,6 +713,8 @@ constexpr int kBarWords = kBarTop + 32;
 
 // s_waitcnt vmcnt(0) (expcnt and lgkmcnt left at their maxima)
 constexpr int kWaitVmcnt0 = 0x0F70;
+// cache policy of a buffer load: sc1
+constexpr int kLoadSc1 = 16;
 
 __device__ inline unsigned bar_load(unsigned* w) {
   return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -824,25 +828,34 @@ __device__ inline void mail_put(MailWord* w, float v, unsigned tag) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The first W words of `rec` (any readable record in lanes without `need`)
-// once all of them carry `tag` in every lane that needs them; every lane of
-// the wavefront calls it.  The wait is bounded as bar_reach's is: if it
-// expires or another workgroup has raised the launch's failure flag, `dead`
+// The first W words of the record at byte `off` (a multiple of 16) of the
+// iteration's `bytes` bytes of records once all of them carry `tag` in every
+// lane that needs them; lanes without `need` name any record; every lane of the
+// wavefront calls it, and a record is readable to the next 16 bytes.  Read as
+// 16-byte loads of two words each, past the caches (sc1, as an agent-scope
+// atomic load): what the large graphs are bound by is the number of these
+// requests, about 100 per ns over the card.  The wait is bounded as bar_reach's is: if
+// it expires or another workgroup has raised the launch's failure flag, `dead`
 // is set and no later call of this wavefront waits.
 template <int W>
-__device__ inline void mail_take(unsigned* __restrict__ bar, const MailWord* rec, unsigned tag, bool need,
-                                 float (&v)[W], bool& dead) {
+__device__ inline void mail_take(unsigned* __restrict__ bar, MailWord* in, unsigned bytes, unsigned off, unsigned tag,
+                                 bool need, float (&v)[W], bool& dead) {
+  using u32x4 = unsigned __attribute__((ext_vector_type(4)));
+  constexpr int L = (W + 1) / 2;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(in, 0, (int)bytes, 0x00020000);
   for (unsigned it = 1;; ++it) {
-    MailWord w[W];
+    // (read anew in every round: the builtin alone may be hoisted)
+    asm volatile("" ::: "memory");
+    u32x4 w[L];
 #pragma unroll
-    for (int k = 0; k < W; ++k) w[k] = __hip_atomic_load(rec + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned off = 0u;
+    for (int k = 0; k < L; ++k) w[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 16u * k), 0, kLoadSc1);
+    unsigned diff = 0u;
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-      off |= (unsigned)(w[k] >> 32) ^ tag;
-      v[k] = __uint_as_float((unsigned)w[k]);
+      diff |= (k & 1 ? w[k / 2].w : w[k / 2].y) ^ tag;
+      v[k] = __uint_as_float(k & 1 ? w[k / 2].z : w[k / 2].x);
     }
-    if (!__any(need & (off != 0u)) || dead) return;
+    if (!__any(need & (diff != 0u)) || dead) return;
     if (it % 256 == 0 && (it / 256 >= kBarSpinOuter || bar_load(bar + 64) != 0u)) {
       dead = true;
       if (__lane_id() == 0) {

@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
 // the wavefront sums them in a fixed order and lanes 0..8 take the Adam
 // step.  The parameters of the other cameras come from their mailboxes
 // (mail_take), so an iteration has no grid barrier and leaves the caches
-// alone: 100 iterations at 200 cameras 377 us, 527 with parameters and
+// alone: 100 iterations at 200 cameras 361 us, 527 with parameters and
 // rotations exchanged through a grid barrier.  What is left is one
 // wavefront's chain of float64 arithmetic (about 2.4 us an iteration) and the
 // way of a store to another XCD's load.
@@ -608,6 +608,8 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
   const int kq = lane < 9 ? lane : 8;
   const WT* W36 = reinterpret_cast<const WT*>(a.W36);
   const int64_t NM = (int64_t)a.N * kMailWords;
+  constexpr unsigned kRecord = kMailWords * sizeof(MailWord);
+  const unsigned mail_bytes = (unsigned)a.N * kRecord;
   const int64_t slots = nwaves < a.N ? nwaves : a.N;   // wavefronts with a camera
   // first records (buffer 0, tag 1)
   for (int64_t c = gwave; c < a.N; c += nwaves) {
@@ -638,7 +640,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
   bool dead = false;
   StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
   for (int k = 0; k < a.K; ++k) {
-    const MailWord* in = a.mail + (k & 1) * NM;
+    MailWord* in = a.mail + (k & 1) * NM;
     MailWord* out = a.mail + ((k & 1) ^ 1) * NM;
     const unsigned tag = (unsigned)k + 1u;
     // the step's scalars before the wait (pinned there: sunk to their use
@@ -689,7 +691,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
       };
       float po[9];
       if (first_cam.value && s0.lo < s0.hi) {
-        mail_take(a.bar, in + (int64_t)s0.other * kMailWords, tag, s0.live, po, dead);
+        mail_take(a.bar, in, mail_bytes, (unsigned)s0.other * kRecord, tag, s0.live, po, dead);
         if (s0.live) add_pair(s0.item & 1, po, w0);
       }
       // entries from memory, the first of these passes' held in `held`; the
@@ -698,7 +700,7 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
         const CamSlot e = q0 == (first_cam.value ? 64 : 0) ? held : cam_slot(a, c, q0, lane);
         GramRegs<WT> w;
         load_gram(W36 + (int64_t)(e.item >> 1) * 36, w);
-        mail_take(a.bar, in + (int64_t)e.other * kMailWords, tag, e.live, po, dead);
+        mail_take(a.bar, in, mail_bytes, (unsigned)e.other * kRecord, tag, e.live, po, dead);
         if (e.live) add_pair(e.item & 1, po, w);
       }
       lwave += wave_sum6_loss(acc6, lsum, lane);
@@ -821,16 +823,20 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   void* args[] = {&a};
   // automatic grid below kCamLoopMaxPairs, or cfg->blocks < 0: the
   // camera-centric loop, no barrier in an iteration; a forced workgroup count
-  // or a larger graph runs the pair loop
+  // or a larger graph (also one
+  // whose records a buffer descriptor does not span) runs the pair loop
   // (workgroups of two wavefronts while they fit one to a CU: the wavefronts'
   // scattered reads of the mailboxes spread over twice as many CUs: 100
   // iterations at 200 cameras 417 us against 433, at 500 677 against 926;
-  // past a workgroup per CU four are better, at 1,000 612 against 673)
+  // past a workgroup per CU four are better, at 1,000 612 against 673: all with
+  // 8-byte reads)
   const int cam_threads = ((int64_t)s->N + 1) / 2 <= ctx->num_cu ? kCamBlock / 2 : kCamBlock;
   int64_t want_cam = grid_for((int64_t)s->N * 64, cam_threads);
   if (want_cam > s->coop_blocks_cam) want_cam = s->coop_blocks_cam;
+  if (want_cam > ctx->num_cu) want_cam = ctx->num_cu;
   if ((cfg->blocks < 0 || (cfg->blocks == 0 && s->P < kCamLoopMaxPairs)) &&
-      2 * kTraceBatch * want_cam * (cam_threads / 64) <= s->loss_part_cap) {
+      2 * kTraceBatch * want_cam * (cam_threads / 64) <= s->loss_part_cap &&
+      (int64_t)s->N * kMailWords * (int64_t)sizeof(MailWord) <= INT32_MAX) {
     CamSolveArgs ca;
     ca.params = params; ca.m = m; ca.v = v;
     ca.cams = s->pair_cams; ca.W36 = W36; ca.cam_ptr = s->cam_ptr; ca.cam_items = s->cam_items;

@@ -312,6 +312,7 @@ static void scene_free(fm_scene* s) {
   (void)hipFree(s->ta_part);
   (void)hipFree(s->ta_stats);
   (void)hipFree(s->ta_alt);
+  (void)hipFree(s->ta_mail);
   (void)hipFree(s->lz);
   delete s;
 }

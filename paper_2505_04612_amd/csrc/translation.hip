@@ -527,6 +527,197 @@ __global__ __launch_bounds__(kSolveBlock) void k_ta_solve_cam(TaCamArgs a) {
   }
 }
 
+// The camera loop of graphs with a wavefront for every camera (ta_mail_fits):
+// the other cameras' centres come from their mailboxes (mail_take) instead of
+// through a grid barrier (100 iterations of four runs at 200 cameras 344 us
+// against 484, of one run 233 against 387).
+struct TaMailArgs {
+  float* centres;    // [runs, N, 3]
+  float* m;
+  float* v;
+  const int32_t* cams;
+  const float* dirs;
+  const int32_t* cam_ptr;
+  const int32_t* cam_items;
+  MailWord* mail;    // [2, N, stride]: a camera's centres, runs x 3
+  int64_t stride;
+  double* part;      // [2 kTraceBatch, runs, N]
+  double* trace;
+  unsigned* bar;
+  int32_t N;
+  int32_t runs;
+  int32_t K;
+  double invP, lr, log_frac, b1, b2, eps;
+  int64_t lr_step0, lr_total, adam_step0;
+};
+
+// Words of a camera's mailbox record: whole 128-byte lines.
+inline int64_t ta_mail_stride(int32_t runs) { return (3 * (int64_t)runs + 15) & ~(int64_t)15; }
+
+// Incidence entry q (or, past the camera's last one, that one, so that what
+// it points at can be read) with the pair's direction.
+struct TaMailEntry {
+  int item, other;
+  float dx, dy, dz;
+  bool live;
+};
+
+__device__ inline TaMailEntry ta_mail_entry(const TaMailArgs& a, int q, int hi) {
+  TaMailEntry e;
+  e.live = q < hi;
+  e.item = a.cam_items[e.live ? q : hi - 1];
+  e.other = a.cams[(int64_t)e.item ^ 1];
+  const int64_t n = e.item >> 1;
+  e.dx = a.dirs[3 * n];
+  e.dy = a.dirs[3 * n + 1];
+  e.dz = a.dirs[3 * n + 2];
+  return e;
+}
+
+// One iteration's records and scalars.
+struct TaMailStep {
+  MailWord* in;
+  MailWord* out;
+  unsigned bytes, tag;
+  double lr, ib1, ib2;
+};
+
+// Camera c for runs r0 .. r0 + G - 1 (as ta_cam_group); e0 holds the entries
+// of its first 64 pairs.  All 64 lanes take part.
+template <int G>
+__device__ inline void ta_mail_group(const TaMailArgs& a, const TaMailStep& st, int64_t c, int lo, int hi,
+                                     const TaMailEntry& e0, int lane, int r0, int k, bool& dead) {
+  const int64_t run_stride = (int64_t)a.N * 3;
+  // this lane's own coordinate (lanes past 3G repeat the last one); no other
+  // wavefront reads or writes the camera's values in memory
+  const int l3 = lane < 3 * G ? lane : 3 * G - 1;
+  const int64_t own = (r0 + l3 / 3) * run_stride + c * 3 + l3 % 3;
+  const float p0 = a.centres[own];
+  float mq = a.m[own], vq = a.v[own];
+  double o[G][3], acc[12], ls[G];
+#pragma unroll
+  for (int j = 0; j < 12; ++j) acc[j] = 0.0;
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    ls[g] = 0.0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) o[g][j] = (double)__shfl(p0, 3 * g + j);
+  }
+  for (int q0 = lo; q0 < hi; q0 += 64) {
+    TaMailEntry e = e0;
+    if (q0 > lo) e = ta_mail_entry(a, q0 + lane, hi);
+    const double d[3] = {(double)e.dx, (double)e.dy, (double)e.dz};
+    float w[3 * G];
+    mail_take(a.bar, st.in, st.bytes, (unsigned)(e.other * a.stride + 3 * r0) * (unsigned)sizeof(MailWord), st.tag,
+              e.live, w, dead);
+    if (e.live) {
+      const bool second = e.item & 1;
+      const double sgn = second ? 1.0 : -1.0, first = second ? 0.0 : 1.0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        double sv[3], gr[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const double x = (double)w[3 * g + j];
+          sv[j] = second ? o[g][j] - x : x - o[g][j];
+        }
+        const double term = ta_term(sv, d, a.invP, gr);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) acc[3 * g + j] += sgn * (double)(float)gr[j];
+        ls[g] += first * (double)(float)term;
+      }
+    }
+  }
+  wave_sum12(acc, lane);
+  double gl = acc[0];
+#pragma unroll
+  for (int j = 1; j < 3 * G; ++j) gl = (l3 == j) ? acc[j] : gl;
+  const float pq = adam_update_inv(p0, (float)gl, mq, vq, st.lr, a.b1, a.b2, a.eps, st.ib1, st.ib2);
+  if (lane < 3 * G) {
+    mail_put(st.out + c * a.stride + 3 * r0 + lane, pq, st.tag + 1u);
+    a.centres[own] = pq;
+    a.m[own] = mq;
+    a.v[own] = vq;
+  }
+  if (a.trace) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      double t = ls[g];
+#pragma unroll
+      for (int sh = 32; sh >= 1; sh >>= 1) t += __shfl_xor(t, sh);
+      if (lane == 0) store_wt(a.part + ((int64_t)(k % (2 * kTraceBatch)) * a.runs + r0 + g) * a.N + c, t);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kCamBlock) void k_ta_solve_mail(TaMailArgs a) {
+  GridBar gb = grid_bar(a.bar);
+  const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int lane = threadIdx.x & 63;
+  const bool own = c < a.N;
+  // first record (buffer 0, tag 1), and the first 64 entries, read once
+  int lo = 0, hi = 0;
+  TaMailEntry e0{};
+  if (own) {
+    for (int i = lane; i < 3 * a.runs; i += 64)
+      mail_put(a.mail + c * a.stride + i, a.centres[(i / 3) * (int64_t)a.N * 3 + c * 3 + i % 3], 1u);
+    lo = a.cam_ptr[c];
+    hi = a.cam_ptr[c + 1];
+    if (lo < hi) e0 = ta_mail_entry(a, lo + lane, hi);
+  }
+  const int64_t NM = (int64_t)a.N * a.stride;
+  bool dead = false;
+  StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
+  for (int k = 0; k < a.K; ++k) {
+    TaMailStep st{a.mail + (k & 1) * NM,
+                  a.mail + ((k & 1) ^ 1) * NM,
+                  (unsigned)(NM * (int64_t)sizeof(MailWord)),
+                  (unsigned)k + 1u,
+                  a.lr * sch.frac,
+                  1.0 / (1.0 - sch.p1),
+                  1.0 / (1.0 - sch.p2)};
+    sch.next();
+    // (formed here, before the waits: sunk to their use they would follow them)
+    asm volatile("" : "+v"(st.lr), "+v"(st.ib1), "+v"(st.ib2));
+    if (own) {
+      int r0 = 0;
+      for (; r0 + 4 <= a.runs; r0 += 4) ta_mail_group<4>(a, st, c, lo, hi, e0, lane, r0, k, dead);
+      if (r0 + 2 <= a.runs) {
+        ta_mail_group<2>(a, st, c, lo, hi, e0, lane, r0, k, dead);
+        r0 += 2;
+      }
+      if (r0 < a.runs) ta_mail_group<1>(a, st, c, lo, hi, e0, lane, r0, k, dead);
+    }
+    if (a.trace && trace_due(k, a.K)) {
+      grid_barrier_wt(gb);
+      // one wavefront per iteration of the batch and run
+      const int k0 = k - k % kTraceBatch;
+      for (int64_t g = c; g < (int64_t)(k + 1 - k0) * a.runs; g += nwaves) {
+        const int kk = k0 + (int)(g / a.runs), r = (int)(g % a.runs);
+        const double* p = a.part + ((int64_t)(kk % (2 * kTraceBatch)) * a.runs + r) * a.N;
+        double t = 0.0;
+#pragma unroll 4
+        for (int64_t q = lane; q < a.N; q += 64) t += p[q];
+#pragma unroll
+        for (int sh = 32; sh >= 1; sh >>= 1) t += __shfl_xor(t, sh);
+        if (lane == 0) a.trace[(int64_t)r * a.K + kk] = t * a.invP;
+      }
+    }
+  }
+}
+
+// Whether the mailbox loop runs: every camera has a wavefront of its own, one to
+// a SIMD, and the cameras have at most 192 pairs on average.  Past that the
+// passes of 64 pairs, each waiting for requests that the caches do not serve,
+// cost more than the barrier: us per iteration, mailbox against barrier, for
+// four runs (one run) at 1,000 cameras of 20 pairs 3.4 against 7.8, of 78
+// 6.0 against 8.9 (3.1, 7.3), of 200 10.7 against 10.8 (5.4, 8.2), at 300
+// cameras of 298 9.6 against 9.0, at 800 of 350 15.2 against 12.8 (8.2, 8.3).
+inline bool ta_mail_fits(const fm_scene* s, int num_cu) {
+  return s->N <= num_cu * (kCamBlock / 64) && s->P <= 96 * (int64_t)s->N;
+}
+
 // ------------------------------------------------------------------ merge of runs
 
 // Centroid and mean distance to it of each run's centres (one workgroup per
@@ -660,18 +851,25 @@ fm_status ta_reserve(fm_ctx* ctx, fm_scene* s, int runs) {
   (void)hipFree(s->ta_part);
   (void)hipFree(s->ta_stats);
   (void)hipFree(s->ta_alt);
+  (void)hipFree(s->ta_mail);
   s->ta_rec = nullptr;
   s->ta_part = nullptr;
   s->ta_stats = nullptr;
   s->ta_alt = nullptr;
+  s->ta_mail = nullptr;
   s->ta_runs_cap = 0;
   const int64_t P1 = s->P > 0 ? s->P : 1;
   const int64_t N1 = s->N > 0 ? s->N : 1;
-  // loss partials: two sets (the camera loop alternates them by iteration)
+  // loss partials: two sets (the camera loop alternates them by iteration), or
+  // the mailbox loop's rows of two trace batches
+  const bool mail = ta_mail_fits(s, ctx->num_cu);
+  int64_t parts = 2 * part;
+  if (mail && parts < 2 * kTraceBatch * N1) parts = 2 * kTraceBatch * N1;
   if (hipMalloc(&s->ta_rec, sizeof(float4) * runs * P1) != hipSuccess ||
-      hipMalloc(&s->ta_part, sizeof(double) * 2 * runs * part) != hipSuccess ||
+      hipMalloc(&s->ta_part, sizeof(double) * runs * parts) != hipSuccess ||
       hipMalloc(&s->ta_stats, sizeof(double) * 4 * runs) != hipSuccess ||
-      hipMalloc(&s->ta_alt, sizeof(float) * 3 * runs * N1) != hipSuccess) {
+      hipMalloc(&s->ta_alt, sizeof(float) * 3 * runs * N1) != hipSuccess ||
+      (mail && hipMalloc(&s->ta_mail, sizeof(MailWord) * 2 * ta_mail_stride(runs) * N1) != hipSuccess)) {
     (void)hipGetLastError();
     return fm_fail(ctx, FM_ENOMEM, "translation workspace for %d runs: allocation failed", runs);
   }
@@ -776,6 +974,25 @@ extern "C" fm_status fm_translation_solve(fm_ctx* ctx, fm_scene* s, const float*
   a.b1 = cfg->beta1; a.b2 = cfg->beta2; a.eps = cfg->eps;
   a.lr_step0 = cfg->lr_step0; a.lr_total = cfg->lr_total_steps; a.adam_step0 = cfg->adam_step0;
   void* args[] = {&a};
+  if (cfg->blocks <= 0 && ta_mail_fits(s, ctx->num_cu)) {
+    TaMailArgs ma;
+    ma.centres = centres; ma.m = m; ma.v = v;
+    ma.cams = s->pair_cams; ma.dirs = dirs; ma.cam_ptr = s->cam_ptr; ma.cam_items = s->cam_items;
+    ma.mail = s->ta_mail; ma.stride = ta_mail_stride(runs); ma.part = s->ta_part; ma.trace = loss_trace;
+    ma.bar = s->bar;
+    ma.N = s->N; ma.runs = runs; ma.K = K;
+    ma.invP = a.invP; ma.lr = a.lr; ma.log_frac = a.log_frac; ma.b1 = a.b1; ma.b2 = a.b2; ma.eps = a.eps;
+    ma.lr_step0 = a.lr_step0; ma.lr_total = a.lr_total; ma.adam_step0 = a.adam_step0;
+    void* margs[] = {&ma};
+    FM_HIP_TRY(ctx, fm_mail_reset(s->bar, s->ta_mail, 2 * (int64_t)s->N * ma.stride, st));
+    // two wavefronts a workgroup while these fit one to a CU
+    const int threads = ((int64_t)s->N + 1) / 2 <= ctx->num_cu ? kCamBlock / 2 : kCamBlock;
+    fm_timed timer(ctx, FM_K_TA_SOLVE, st);
+    hipError_t e = hipLaunchCooperativeKernel((const void*)k_ta_solve_mail, dim3(grid_for((int64_t)s->N * 64, threads)),
+                                              dim3(threads), margs, 0, st);
+    if (e != hipSuccess) return fm_fail(ctx, FM_ECOOP, "cooperative launch failed: %s", hipGetErrorString(e));
+    return FM_OK;
+  }
   FM_HIP_TRY(ctx, fm_bar_reset(s->bar, st));
   if (cfg->blocks <= 0) {
     // automatic grid: the camera loop, one wavefront per camera up to the
