@@ -917,11 +917,16 @@ __device__ inline XcdSync xcd_register(GridBar& gb) {
 // nothing in a workgroup that is not split across CUs; only the agent-scope
 // invalidation clears it).  As in grid_barrier, counts and generations only
 // grow within a launch.
-__device__ inline void grid_sync(unsigned* __restrict__ bar, XcdSync& xs) {
+// `early` issues loads of data no workgroup writes during the launch: in the
+// wavefronts that have nothing to do with the exchange they run during the
+// wait, in the first one after it.
+template <typename F>
+__device__ inline void grid_sync(unsigned* __restrict__ bar, XcdSync& xs, F&& early) {
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
   unsigned f = 0u;
   if (threadIdx.x == 0) f = bar_load(bar + 64);
   __syncthreads();
+  if (threadIdx.x >= 64) early();
   if (threadIdx.x == 0 && f == 0u) {
     unsigned* xc = bar + kBarXcdCount + 32 * xs.x;
     unsigned* xg = bar + kBarXcdGen + 32 * xs.x;
@@ -942,6 +947,10 @@ __device__ inline void grid_sync(unsigned* __restrict__ bar, XcdSync& xs) {
   xs.tnext += xs.nact;
   xs.gnext += 1u;
   __syncthreads();
+  if (threadIdx.x < 64) early();
+}
+__device__ inline void grid_sync(unsigned* __restrict__ bar, XcdSync& xs) {
+  grid_sync(bar, xs, [] {});
 }
 
 // Clears the counts, generations and registrations of the grid barriers and

@@ -149,19 +149,24 @@ __device__ inline void store_sides(float* __restrict__ contrib, int qi, int qj, 
 // `stride`: each side written to its slot; returns this thread's loss sum
 // (float64, in pair order).  The cameras and slots of the first two pairs
 // come in registers (ci0, cj0 and ci1, cj1, qi0, qj0 and qi1, qj1), read once
-// per solve.
-template <typename WT>
+// per solve; with kHold the first pair's Gram too (w0).
+template <bool kHold, typename WT>
 __device__ inline double pair_phase_slots(const float* params, const double* rot, const int32_t* cams,
                                           const int32_t* pair_slot, const WT* W36, int64_t P, double two_inv_Z,
                                           float* contrib, int64_t first, int64_t stride, int ci0, int cj0, int ci1,
-                                          int cj1, int qi0, int qj0, int qi1, int qj1) {
-  double sum = 0.0;
-  for (int64_t n = first; n < P; n += stride) {
-    const bool held0 = n == first, held1 = n == first + stride;
+                                          int cj1, int qi0, int qj0, int qi1, int qj1, const GramRegs<WT>& w0) {
+  double sum = 0.0, om[3], dti[3], dtj[3];
+  if constexpr (kHold) {
+    if (first < P) {
+      sum += pair_loss_omega(params, rot, ci0, cj0, w0, two_inv_Z, om, dti, dtj);
+      store_sides(contrib, qi0, qj0, om, dti, dtj);
+    }
+  }
+  for (int64_t n = kHold ? first + stride : first; n < P; n += stride) {
+    const bool held0 = !kHold && n == first, held1 = n == first + stride;
     const int ci = held0 ? ci0 : (held1 ? ci1 : cams[2 * n]), cj = held0 ? cj0 : (held1 ? cj1 : cams[2 * n + 1]);
     const int qi = held0 ? qi0 : (held1 ? qi1 : pair_slot[2 * n]);
     const int qj = held0 ? qj0 : (held1 ? qj1 : pair_slot[2 * n + 1]);
-    double om[3], dti[3], dtj[3];
     sum += pair_loss_omega(params, rot, ci, cj, W36 + n * 36, two_inv_Z, om, dti, dtj);
     store_sides(contrib, qi, qj, om, dti, dtj);
   }
@@ -420,14 +425,16 @@ struct SolveArgs {
   const int32_t* pair_slot;
 };
 
-// Grid barrier of the fused loops: per-XCD (grid_sync) or flat
-// (grid_barrier).
-template <bool XS>
-__device__ inline void loop_sync(GridBar& gb, XcdSync& xs) {
-  if constexpr (XS)
-    grid_sync(gb.bar, xs);
-  else
+// Grid barrier of the pair loop: per-XCD (grid_sync) or flat (grid_barrier);
+// `early` loads what no workgroup writes, during the wait where that can be.
+template <bool XS, typename F>
+__device__ inline void loop_sync(GridBar& gb, XcdSync& xs, F&& early) {
+  if constexpr (XS) {
+    grid_sync(gb.bar, xs, early);
+  } else {
     grid_barrier(gb);
+    early();
+  }
 }
 
 template <typename WT, bool XS>
@@ -447,6 +454,17 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
   const int64_t g1 = gtid + gsize;
   const int ci1 = g1 < a.P ? a.cams[2 * g1] : 0, cj1 = g1 < a.P ? a.cams[2 * g1 + 1] : 0;
   const int qi1 = g1 < a.P ? a.pair_slot[2 * g1] : 0, qj1 = g1 < a.P ? a.pair_slot[2 * g1 + 1] : 0;
+  // the float32 Gram of the thread's first pair is loaded ahead of its pair
+  // phase, in the wait of the barrier before it (186k pairs: 19.2 us an
+  // iteration, 19.8 without; held through the launch it spills, 19.5; a
+  // float64 Gram does not fit the registers)
+  constexpr bool kHold = sizeof(WT) == 4;
+  GramRegs<WT> w0{};
+  auto load_first = [&] {
+    if constexpr (kHold)
+      if (gtid < a.P) load_gram(W36 + gtid * 36, w0);
+  };
+  load_first();
   // cameras 4 gwave + row, then strided by 4 nwaves
   const int row = lane >> 4, l16 = lane & 15, base = lane & ~15;
   const int64_t c_first = 4 * gwave + row, c_stride = 4 * nwaves;
@@ -458,14 +476,14 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
   for (int k = 0; k < a.K; ++k) {
     // iteration 0 runs Gram-Schmidt per pair; later iterations read the
     // rotations the camera phase stored with the updated parameters
-    const double v = pair_phase_slots<WT>(a.params, k > 0 ? a.rot : nullptr, a.cams, a.pair_slot, W36, a.P,
+    const double v = pair_phase_slots<kHold, WT>(a.params, k > 0 ? a.rot : nullptr, a.cams, a.pair_slot, W36, a.P,
                                                 2.0 * iz, a.contrib, gtid, gsize, ci0, cj0, ci1, cj1, qi0, qj0, qi1,
-                                                qj1);
+                                                qj1, w0);
     if (a.loss_trace) {
       const double t = block_sum(v, lds);
       if (threadIdx.x == 0) trace_row(a.loss_part, gridDim.x, k)[blockIdx.x] = t;
     }
-    loop_sync<XS>(gb, xs);
+    loop_sync<XS>(gb, xs, [] {});
     if (a.loss_trace) trace_batch(a.loss_part, gridDim.x, k, a.K, iz, a.loss_trace, gwave, nwaves, lane);
     const double frac = sch.frac;
     const double bc1 = 1.0 - sch.p1, bc2 = 1.0 - sch.p2;
@@ -527,7 +545,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
         a.rot[c * 9 + l16] = rv;
       }
     }
-    loop_sync<XS>(gb, xs);
+    loop_sync<XS>(gb, xs, load_first);
   }
 }
 
