@@ -493,9 +493,9 @@ fm_status fm_pose_change(fm_ctx* ctx, fm_scene* scene, const float* params_a, co
 
 /* fm_mlp_backward without any allocation, for callers that cannot allocate
  * device memory (code under HIP graph capture, serving loops, harnesses
- * that forbid hipMalloc): the same gradients, with the per-wavefront
- * gradient slots in a static device array of the library (512 slots of 4,481
- * floats, 9.2 MB, held by each GPU the library runs on until the process
+ * that forbid hipMalloc): the same gradients, with the workgroups'
+ * gradient slots in a static device array of the library (128 slots of 4,481
+ * floats, 2.3 MB, held by each GPU the library runs on until the process
  * ends) instead of a context workspace that grows on demand.  The launch is
  * capped at 128 workgroups of four wavefronts, so any M is accepted; up to
  * 8,192 matches it is fm_mlp_backward's launch and the results are

@@ -243,19 +243,36 @@ __global__ __launch_bounds__(64 * kFwdWaves, 3) void k_mlp_forward(int64_t M, co
   }
 }
 
+template <int CTRL>
+__device__ inline float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
 // Backward of sum_m dout[m] * sigmoid(z3[m]) from the stored activations.
-// Each wavefront accumulates its gradient contributions in registers and
-// writes them to its own slot of `part` [waves, kG_N]; k_mlp_reduce adds the
-// slots in a fixed order.
+// Each wavefront accumulates its gradient contributions in registers; the
+// workgroup adds its four wavefronts' in a fixed order and writes them to its
+// slot of `part` [workgroups, kG_N]; k_mlp_reduce adds the slots in a fixed
+// order.  (With a slot per wavefront, 36.7 MB of them, and each row's inputs
+// waited for on their own, 65,536 matches took 20.8 us and the reduction 18.1;
+// now 18.0 and 4.1.  A training step of 1M matches 241 us, now 163, of which the
+// activations written and read back take 100.)
 __global__ __launch_bounds__(256) void k_mlp_backward(int64_t M, const float* __restrict__ feats, MlpPtrs w,
                                                       const _Float16* __restrict__ act,
                                                       const float* __restrict__ dout, float* __restrict__ part) {
   __shared__ MlpLds s;
-  __shared__ _Float16 T[4][16][kHid + 4];   // per-wave transpose of dh2
-  // per-wave copy of the tile's activations (16 matches x 128, rows padded
-  // so that the four row groups a read instruction touches use different
-  // banks): read from global memory in 16-byte pieces, then per unit
-  __shared__ _Float16 Ast[4][16][2 * kHid + 8];
+  struct Stage {
+    _Float16 T[4][16][kHid + 4];   // per-wave transpose of dh2
+    // per-wave copy of the tile's activations (16 matches x 128, rows padded
+    // so that the four row groups a read instruction touches use different
+    // banks): read from global memory in 16-byte pieces, then per unit
+    _Float16 Ast[4][16][2 * kHid + 8];
+  };
+  __shared__ union {
+    Stage st;
+    float sum[2][kG_N];   // two wavefronts' gradients, after the last tile
+  } u;
+  auto& T = u.st.T;
+  auto& Ast = u.st.Ast;
   load_lds(w, s);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
@@ -274,33 +291,41 @@ __global__ __launch_bounds__(256) void k_mlp_backward(int64_t M, const float* __
     for (int b = 0; b < 4; ++b) gW2[a][b] = f4{0.0f, 0.0f, 0.0f, 0.0f};
   float gW3[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gb1[4] = {0, 0, 0, 0}, gb3 = 0.0f;
   float gW1[4][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+  // The staging rows are the wavefront's own: its LDS operations complete in
+  // order, and the fences keep the compiler from reordering them.  All loads
+  // of a tile are issued together, from clamped rows (under a lane condition
+  // each is waited for on its own); rows past M count as zeros.
   const int64_t ntiles = (M + 15) / 16;
-  for (int64_t base = (int64_t)blockIdx.x * 4; base < ntiles; base += (int64_t)gridDim.x * 4) {
-    const int64_t tile = base + wave;
-    const bool tv = tile < ntiles;
-    // the tile's 16 x 128 activations (4 KB, 256 pieces of 16 bytes; rows
-    // past M are zeros)
+  for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += (int64_t)gridDim.x * 4) {
+    const int64_t m0 = tile * 16;
+    const int left = M - m0 < 16 ? (int)(M - m0) : 16;
+    // the tile's 16 x 128 activations (4 KB, 256 pieces of 16 bytes)
+    h8 av[4];
+    float dv[4], x[4][3];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int idx = 64 * t + lane, row = idx >> 4, piece = idx & 15;
-      const int64_t m = tile * 16 + row;
-      h8 v;
-      if (tv && m < M) {
-        v = *reinterpret_cast<const h8*>(act + m * 128 + 8 * piece);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (_Float16)0.0f;
-      }
-      *reinterpret_cast<h8*>(&Ast[wave][row][8 * piece]) = v;
+      const int row = 4 * t + q;
+      av[t] = *reinterpret_cast<const h8*>(act + (m0 + min(row, left - 1)) * 128 + 8 * r);
     }
-    __syncthreads();
-    // this lane's result-layout rows 4q + j
-    float h2[4][4], h1[4][4], d3[4], x[4][3];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int64_t row = tile * 16 + 4 * q + j;
-      const bool ok = tv && row < M;
-      const int64_t rc = ok ? row : 0;
+      const int64_t m = m0 + min(4 * q + j, left - 1);
+      dv[j] = dout[m];
+      load_x(feats, m, s, x[j]);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int row = 4 * t + q;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) av[t][j] = row < left ? av[t][j] : (_Float16)0.0f;
+      *reinterpret_cast<h8*>(&Ast[wave][row][8 * r]) = av[t];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // this lane's result-layout rows 4q + j
+    float h2[4][4], h1[4][4], d3[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool ok = 4 * q + j < left;
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
         h2[j][nt] = (float)Ast[wave][4 * q + j][64 + 16 * nt + r];
@@ -309,12 +334,16 @@ __global__ __launch_bounds__(256) void k_mlp_backward(int64_t M, const float* __
       float z = 0.0f;
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) z = fmaf(s.W3[16 * nt + r], h2[j][nt], z);
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) z += __shfl_xor(z, o);
+      // sum over the 16-lane row: lanes xor 1, 2, then (their quads and eights
+      // alike by then) the mirrored quad and eight
+      z += dpp_f<0xB1>(z);
+      z += dpp_f<0x4E>(z);
+      z += dpp_f<0x141>(z);
+      z += dpp_f<0x140>(z);
       const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-(z + s.b3) * kLog2e));
-      d3[j] = ok ? dout[rc] * sg * (1.0f - sg) : 0.0f;
-      if (ok) load_x(feats, rc, s, x[j]);
-      else x[j][0] = x[j][1] = x[j][2] = 0.0f;
+      d3[j] = ok ? dv[j] * sg * (1.0f - sg) : 0.0f;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) x[j][c] = ok ? x[j][c] : 0.0f;
     }
     // dh2 (result layout), dW3, db2, db3
     h4 A2[4];
@@ -339,7 +368,7 @@ __global__ __launch_bounds__(256) void k_mlp_backward(int64_t M, const float* __
     for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
       for (int it = 0; it < 4; ++it) gW2[ot][it] = mfma16(A2[ot], B1[it], gW2[ot][it]);
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // dh1 = (dh2 W2) * (h1 > 0): operand A[m][o] read back transposed
     h8 A3[2];
 #pragma unroll
@@ -359,17 +388,8 @@ __global__ __launch_bounds__(256) void k_mlp_backward(int64_t M, const float* __
         for (int c = 0; c < 3; ++c) gW1[it][c] = fmaf(dh1, x[j][c], gW1[it][c]);
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  // write this wavefront's slot
-  const int64_t slot = (int64_t)blockIdx.x * 4 + wave;
-  float* P = part + slot * kG_N;
-#pragma unroll
-  for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-    for (int it = 0; it < 4; ++it)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) P[kG_W2 + (16 * ot + 4 * q + j) * kHid + 16 * it + r] = gW2[ot][it][j];
   // per-unit sums: add the four quarters (lanes r, r+16, r+32, r+48)
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) {
@@ -383,18 +403,34 @@ __global__ __launch_bounds__(256) void k_mlp_backward(int64_t M, const float* __
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) gb3 += __shfl_xor(gb3, o);
-  if (q == 0) {
+  // (w0 + w2) + (w1 + w3) through LDS, which the tiles no longer use
+  __syncthreads();
+  auto each = [&](auto f) {
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const int u = 16 * nt + r;
-      P[kG_W3 + u] = gW3[nt];
-      P[kG_b2 + u] = gb2[nt];
-      P[kG_b1 + u] = gb1[nt];
+    for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) P[kG_W1 + 3 * u + c] = gW1[nt][c];
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f(kG_W2 + (16 * ot + 4 * q + j) * kHid + 16 * it + r, gW2[ot][it][j]);
+    if (q == 0) {
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        const int h = 16 * nt + r;
+        f(kG_W3 + h, gW3[nt]);
+        f(kG_b2 + h, gb2[nt]);
+        f(kG_b1 + h, gb1[nt]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) f(kG_W1 + 3 * h + c, gW1[nt][c]);
+      }
     }
-  }
-  if (lane == 0) P[kG_b3] = gb3;
+    if (lane == 0) f(kG_b3, gb3);
+  };
+  if (wave >= 2) each([&](int e, float v) { u.sum[wave - 2][e] = v; });
+  __syncthreads();
+  if (wave < 2) each([&](int e, float v) { u.sum[wave][e] += v; });
+  __syncthreads();
+  float* P = part + (int64_t)blockIdx.x * kG_N;
+  for (int e = threadIdx.x; e < kG_N; e += 256) P[e] = u.sum[0][e] + u.sum[1][e];
 }
 
 struct MlpGradPtrs {
@@ -403,8 +439,8 @@ struct MlpGradPtrs {
 
 // Sum of the gradient slots, entry by entry: each workgroup takes 64
 // entries (one per lane, coalesced over the slots' rows); its kRedWaves
-// wavefronts take consecutive ranges of the slots, eight running sums per
-// lane so that eight loads are in flight, and the wavefronts' sums are added
+// wavefronts take consecutive ranges of the slots, sixteen running sums per
+// lane so that sixteen loads are in flight, and the wavefronts' sums are added
 // in wavefront order: a fixed order for any slot count.
 constexpr int kRedWaves = 16;
 
@@ -415,16 +451,20 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_mlp_reduce(const float* __re
   const int e = blockIdx.x * 64 + lane;
   const int64_t per = (slots + kRedWaves - 1) / kRedWaves;
   const int64_t k0 = wave * per, k1 = min(slots, k0 + per);
-  float p[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  float p[16] = {};
   if (e < kG_N) {
     int64_t k = k0;
-    for (; k + 8 <= k1; k += 8) {
+    for (; k + 16 <= k1; k += 16) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) p[u] += part[(k + u) * kG_N + e];
+      for (int u = 0; u < 16; ++u) p[u] += part[(k + u) * kG_N + e];
     }
     for (; k < k1; ++k) p[0] += part[k * kG_N + e];
   }
-  red[wave][lane] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+#pragma unroll
+  for (int n = 8; n >= 1; n >>= 1)
+#pragma unroll
+    for (int u = 0; u < n; ++u) p[u] += p[u + n];
+  red[wave][lane] = p[0];
   __syncthreads();
   if (wave != 0 || e >= kG_N) return;
   float s = 0.0f;
@@ -615,7 +655,7 @@ extern "C" fm_status fm_mlp_backward(fm_ctx* ctx, int64_t M, const float* feats,
   if (M > 0 && (!feats || !act || !dout)) return fm_fail(ctx, FM_EINVAL, "fm_mlp_backward: NULL input");
   FM_HIP_TRY(ctx, hipSetDevice(ctx->device));
   const unsigned blocks = mlp_blocks(ctx, M);
-  const int64_t slots = (int64_t)blocks * 4;
+  const int64_t slots = blocks;
   const size_t need = sizeof(float) * (size_t)slots * kG_N;
   if (ctx->ws_bytes < need) {
     FM_HIP_TRY(ctx, hipStreamSynchronize((hipStream_t)stream));
@@ -673,12 +713,12 @@ extern "C" fm_status fm_match_features(fm_ctx* ctx, fm_scene* s, const float* pa
 
 // Gradient slots of fm_mlp_backward_noalloc: a file-scope device array (each
 // GPU the library runs on holds its own copy until the process ends) sized
-// for kNoAllocBlocks workgroups of four wavefronts, 512 slots of kG_N floats
-// (9.2 MB).  Host code never passes `scratch` itself to a kernel (its host
+// for kNoAllocBlocks workgroups, a slot of kG_N floats each
+// (2.3 MB).  Host code never passes `scratch` itself to a kernel (its host
 // name is a stand-in, not a device address): the device address comes from
 // hipGetSymbolAddress, taken once per device with that device current.
 constexpr int kNoAllocBlocks = 128;
-constexpr int64_t kNoAllocSlots = (int64_t)kNoAllocBlocks * 4;
+constexpr int64_t kNoAllocSlots = kNoAllocBlocks;
 static __device__ __align__(256) float scratch[kNoAllocSlots * kG_N];
 
 constexpr int kMaxDevices = 64;
@@ -719,7 +759,7 @@ extern "C" fm_status fm_mlp_backward_noalloc(fm_ctx* ctx, int64_t M, const float
   // slots for (identical launch, so identical results, up to 8,192 matches)
   unsigned blocks = mlp_blocks(ctx, M);
   if (blocks > (unsigned)kNoAllocBlocks) blocks = kNoAllocBlocks;
-  const int64_t slots = (int64_t)blocks * 4;
+  const int64_t slots = blocks;
   if (slots > kNoAllocSlots)
     return fm_fail(ctx, FM_ESHAPE, "fm_mlp_backward_noalloc: %lld gradient slots exceed the %lld the scratch holds",
                    (long long)slots, (long long)kNoAllocSlots);
