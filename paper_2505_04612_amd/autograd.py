@@ -24,7 +24,8 @@ class EpipolarLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g: torch.Tensor):
         (grad,) = ctx.saved_tensors
-        return (g.to(grad.dtype) * grad, None, None, None)
+        # (a scalar does not widen the product: rounded to float32, as the gradient is, in one launch)
+        return (grad * g, None, None, None)
 
 
 def epipolar_loss(params: torch.Tensor, scene: api.Scene, W36: torch.Tensor, inv_Z: float) -> torch.Tensor:
