@@ -828,15 +828,31 @@ __device__ inline void mail_put(MailWord* w, float v, unsigned tag) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// After round `it` of a wavefront's wait: whether to look again.  The wait is
+// bounded as bar_reach's is: if it expires or another workgroup has raised the
+// launch's failure flag, `dead` is set and no later wait of this wavefront
+// goes past its first round.
+__device__ inline bool mail_again(unsigned* __restrict__ bar, unsigned it, bool& dead) {
+  if (dead) return false;
+  if (it % 256 == 0 && (it / 256 >= kBarSpinOuter || bar_load(bar + 64) != 0u)) {
+    dead = true;
+    if (__lane_id() == 0) {
+      __hip_atomic_fetch_add(bar + 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(bar + 96, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return false;
+  }
+  __builtin_amdgcn_s_sleep(1);
+  return true;
+}
+
 // The first W words of the record at byte `off` (a multiple of 16) of the
 // iteration's `bytes` bytes of records once all of them carry `tag` in every
 // lane that needs them; lanes without `need` name any record; every lane of the
 // wavefront calls it, and a record is readable to the next 16 bytes.  Read as
 // 16-byte loads of two words each, past the caches (sc1, as an agent-scope
 // atomic load): what the large graphs are bound by is the number of these
-// requests, about 100 per ns over the card.  The wait is bounded as bar_reach's is: if
-// it expires or another workgroup has raised the launch's failure flag, `dead`
-// is set and no later call of this wavefront waits.
+// requests, about 100 per ns over the card.
 template <int W>
 __device__ inline void mail_take(unsigned* __restrict__ bar, MailWord* in, unsigned bytes, unsigned off, unsigned tag,
                                  bool need, float (&v)[W], bool& dead) {
@@ -855,16 +871,35 @@ __device__ inline void mail_take(unsigned* __restrict__ bar, MailWord* in, unsig
       diff |= (k & 1 ? w[k / 2].w : w[k / 2].y) ^ tag;
       v[k] = __uint_as_float(k & 1 ? w[k / 2].z : w[k / 2].x);
     }
-    if (!__any(need & (diff != 0u)) || dead) return;
-    if (it % 256 == 0 && (it / 256 >= kBarSpinOuter || bar_load(bar + 64) != 0u)) {
-      dead = true;
-      if (__lane_id() == 0) {
-        __hip_atomic_fetch_add(bar + 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(bar + 96, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      return;
+    if (!__any(need & (diff != 0u)) || !mail_again(bar, it, dead)) return;
+  }
+}
+
+// A float64 as two words, and L of them: value e of the records at byte off[e]
+// in the lanes with need[e] (the others name any).
+__device__ inline void mail_put_d(MailWord* w, double v, unsigned tag) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  __hip_atomic_store(w, ((MailWord)tag << 32) | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + 1, ((MailWord)tag << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int L>
+__device__ inline void mail_take_d(unsigned* __restrict__ bar, MailWord* in, unsigned bytes, const unsigned (&off)[L],
+                                   const bool (&need)[L], unsigned tag, double (&v)[L], bool& dead) {
+  using u32x4 = unsigned __attribute__((ext_vector_type(4)));
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(in, 0, (int)bytes, 0x00020000);
+  for (unsigned it = 1;; ++it) {
+    asm volatile("" ::: "memory");
+    u32x4 w[L];
+#pragma unroll
+    for (int e = 0; e < L; ++e) w[e] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off[e], 0, kLoadSc1);
+    bool wait = false;
+#pragma unroll
+    for (int e = 0; e < L; ++e) {
+      wait |= need[e] & (((w[e].y ^ tag) | (w[e].w ^ tag)) != 0u);
+      v[e] = __longlong_as_double((long long)(((unsigned long long)w[e].z << 32) | w[e].x));
     }
-    __builtin_amdgcn_s_sleep(1);
+    if (!__any(wait) || !mail_again(bar, it, dead)) return;
   }
 }
 

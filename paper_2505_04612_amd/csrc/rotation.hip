@@ -434,11 +434,16 @@ __global__ __launch_bounds__(kSolveBlock) void k_ra_solve_cam(RaCamArgs a) {
 //
 // Both columns, against the form with two unconditional passes, the basis in
 // memory, seven barriers a step, and one thread's bisection and pivoted inverse
-// iteration every 10 steps: 200 cameras, 4,849 pairs 6.52 -> 1.08 ms; 1,000
+// iteration every 10 steps: 200 cameras, 4,849 pairs 6.52 -> 1.08 ms
+// (0.97 with the exchanges by mailbox, see k_ra_lanczos); 1,000
 // cameras 38.3 -> 4.7; 5,000 cameras, 209k pairs 166.5 -> 12.9.
 
 constexpr int kLzBlock = 512;           // threads per workgroup
 constexpr int kLzWaves = kLzBlock / 64;
+// Workgroups up to which the exchanges go by mailbox: everyone reads everyone's
+// dots past the caches, whose cost grows with their square (8 % are left of the
+// gain at 63).
+constexpr int kLzMailBlocks = 64;
 constexpr int kLzMaxBlocks = 160;       // workgroups of the automatic grid, at most
 constexpr int kLzMisc = 64 + kLzBlock;  // doubles of small LDS scratch
 // Lanczos steps between convergence checks, and the relative residual
@@ -462,6 +467,7 @@ struct LzArgs {
   double* wbuf;          // [n] the current vector before its scaling
   double* part_h;        // [blocks, lz_hrow(m)] partial dots
   double* part_n;        // [blocks, kLzWaves] partial squared norms
+  MailWord* mail;        // the three of them as mailboxes (two words a value)
   double* gws;           // [blocks, lz_work(rows, m)] (the memory variant)
   float* params;         // [N, 6]
   double* info;          // [4] or null: Ritz value and steps of each column
@@ -705,7 +711,14 @@ __device__ inline void lz_term(const LzEntry& e, const double vc[3], const doubl
   }
 }
 
-template <bool GL>
+// MAIL (few workgroups): the vector, the dots and the norms go from workgroup
+// to workgroup as tagged mailbox values instead of through memory and a grid
+// barrier.  One set of them does: a workgroup publishes an exchange only after
+// it has taken the one before from every workgroup, and each of these had by
+// then taken what is overwritten (the dots before the norms, the vector before
+// the dots).  300 steps at most: 20 cameras 549 -> 473 us, 200 1,190 -> 973, 500 2,330
+// -> 1,871, 1,000 (63 workgroups) 4,312 -> 3,979.
+template <bool GL, bool MAIL>
 __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
   extern __shared__ double lds[];
   GridBar gb = grid_bar(a.bar);
@@ -718,6 +731,25 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
   double* misc = hs + m + 2;               // [64]
   double* red = misc + 64;                 // [kLzBlock]
   const int64_t hrow = lz_hrow(m);
+  // byte offsets of the dots and norms among the mailboxes
+  const unsigned mail_h = 16u * (unsigned)((a.n + 15) / 16 * 16), mail_n = mail_h + 16u * (unsigned)(B * hrow),
+                 mail_bytes = mail_n + 16u * (unsigned)(B * kLzWaves);
+  unsigned tag = 0u;
+  bool dead = false;
+  // a value for the other workgroups, and the point after which they can
+  // be read
+  auto put = [&](double* p, unsigned off, double v) {
+    if constexpr (MAIL)
+      mail_put_d(a.mail + off / 8, v, tag);
+    else
+      store_wt(p, v);
+  };
+  auto exchange = [&] {
+    if constexpr (MAIL)
+      __syncthreads();
+    else
+      grid_barrier_wt(gb);
+  };
   double* ws = GL ? a.gws + blockIdx.x * lz_work(rows, m) : misc + kLzMisc;
   double* w = ws;                          // [rows] the next vector before its scaling
   double* y = w + rows;                    // [rows] the operator's image, orthogonalised in place
@@ -753,11 +785,22 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
   // total of all shares
   auto norm_out = [&](double v) {
     v = wave_sum_d(v);
-    if (lane == 0) store_wt(&a.part_n[(int64_t)blockIdx.x * kLzWaves + wave], v);
+    const int64_t i = (int64_t)blockIdx.x * kLzWaves + wave;
+    if (lane == 0) put(&a.part_n[i], mail_n + 16u * (unsigned)i, v);
   };
   auto norm_in = [&]() {
     double t = 0.0;
-    for (int i = tid; i < B * kLzWaves; i += kLzBlock) t += a.part_n[i];
+    if constexpr (MAIL) {
+      for (int i0 = 64 * wave; i0 < B * kLzWaves; i0 += kLzBlock) {   // uniform over the wavefront
+        const bool need[1] = {i0 + lane < B * kLzWaves};
+        const unsigned off[1] = {need[0] ? mail_n + 16u * (unsigned)(i0 + lane) : 0u};
+        double v[1];
+        mail_take_d(a.bar, a.mail, mail_bytes, off, need, tag, v, dead);
+        t += need[0] ? v[0] : 0.0;
+      }
+    } else {
+      for (int i = tid; i < B * kLzWaves; i += kLzBlock) t += a.part_n[i];
+    }
     t = wave_sum_d(t);
     if (lane == 0) misc[16 + wave] = t;
     __syncthreads();
@@ -767,26 +810,40 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
     return t;
   };
 
-  // static data of the first 64 entries of the wavefront's first camera
+  // static data of the first 64 entries of the wavefront's first camera, and
+  // (MAIL) the vector at their other cameras, taken before the norm so that the
+  // two waits overlap
   LzEntry e0;
   e0.other = -1;
   if (wave < nc) {
     const int q = a.cam_ptr[c0 + wave] + lane;
     if (q < a.cam_ptr[c0 + wave + 1]) e0 = lz_entry(a, q);
   }
+  double v0[3] = {0.0, 0.0, 0.0};
+  auto take_first = [&] {
+    if constexpr (MAIL) {
+      const bool live = e0.other >= 0;
+      const unsigned o = live ? 48u * (unsigned)e0.other : 0u;
+      const unsigned off[3] = {o, o + 16u, o + 32u};
+      const bool need[3] = {live, live, live};
+      mail_take_d(a.bar, a.mail, mail_bytes, off, need, tag, v0, dead);
+    }
+  };
 
   for (int col = 0; col < 2; ++col) {
     const double op_alpha = col ? a.inv_P : 1.0;
     // q_0 = start / |start|
     double acc = 0.0;
+    ++tag;
     for (int r = tid; r < nr; r += kLzBlock) {
       const double x = a.start[col * a.n + row0 + r];
       w[r] = x;
-      store_wt(&a.wbuf[row0 + r], x);
+      put(&a.wbuf[row0 + r], 16u * (unsigned)(row0 + r), x);
       acc += x * x;
     }
     norm_out(acc);
-    grid_barrier_wt(gb);
+    exchange();
+    take_first();
     double inv = 1.0 / sqrt(norm_in());
     double alpha = 0.0, b = 0.0, theta = 0.0;
     int used = m;
@@ -806,16 +863,34 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
         double vc[3], t3[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < 3; ++j) vc[j] = w[3 * cl + j] * inv;
-        for (int q = lo + lane; q < hi; q += 64) {
+        for (int q0 = lo; q0 < hi; q0 += 64) {   // uniform over the wavefront
+          const bool live = q0 + lane < hi;
           LzEntry e;
-          if (cl == wave && q == lo + lane)
+          e.other = 0;
+          if (cl == wave && q0 == lo)
             e = e0;
-          else
-            e = lz_entry(a, q);
+          else if (live)
+            e = lz_entry(a, q0 + lane);
           double vo[3];
+          if constexpr (MAIL) {
+            if (cl == wave && q0 == lo) {
 #pragma unroll
-          for (int j = 0; j < 3; ++j) vo[j] = a.wbuf[3 * (int64_t)e.other + j] * inv;
-          lz_term(e, vc, vo, t3);
+              for (int j = 0; j < 3; ++j) vo[j] = v0[j];
+            } else {
+              const unsigned o = live ? 48u * (unsigned)e.other : 0u;
+              const unsigned off[3] = {o, o + 16u, o + 32u};
+              const bool need[3] = {live, live, live};
+              mail_take_d(a.bar, a.mail, mail_bytes, off, need, tag, vo, dead);
+            }
+          }
+          if (live) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              if constexpr (!MAIL) vo[j] = a.wbuf[3 * (int64_t)e.other + j];
+              vo[j] *= inv;
+            }
+            lz_term(e, vc, vo, t3);
+          }
         }
         // totals in lanes 0, 4 and 8 (entries 0, 1, 2)
         double b2[2], b1[1];
@@ -842,6 +917,7 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
       double nrm2 = 0.0;
       for (int pass = 0; pass < 2; ++pass) {
         const double* src = pass ? w : y;
+        ++tag;
         // partial dots with q_0 .. q_k and (entry k + 1) with the vector
         // itself: eight lanes each
         for (int j = tid >> 3; j <= k + 1; j += kLzBlock / 8) {
@@ -858,16 +934,31 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
           d += dpp_mov_d<0xB1>(d);
           d += dpp_mov_d<0x4E>(d);
           d += dpp_mov_d<0x141>(d);
-          if (l8 == 0) store_wt(&a.part_h[blockIdx.x * hrow + j], d);
+          if (l8 == 0) put(&a.part_h[blockIdx.x * hrow + j], mail_h + 16u * (unsigned)(blockIdx.x * hrow + j), d);
         }
-        grid_barrier_wt(gb);
+        exchange();
         // the dots: threads over the entries and, while these are few, over
         // interleaved parts of the workgroups
         const int width = k + 2 <= 64 ? 64 : (k + 2 <= 128 ? 128 : (k + 2 <= 256 ? 256 : kLzBlock));
         for (int j0 = 0; j0 <= k + 1; j0 += width) {
           const int j = j0 + (tid & (width - 1)), parts = kLzBlock / width;
           double t = 0.0;
-          if (j <= k + 1) {
+          if constexpr (MAIL) {
+            for (int q = tid / width; q < B; q += 4 * parts) {   // uniform over the wavefront: width >= 64
+              unsigned off[4];
+              bool need[4];
+              double p[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                need[e] = j <= k + 1 && q + e * parts < B;
+                off[e] = need[e] ? mail_h + 16u * (unsigned)((q + e * parts) * hrow + j) : 0u;
+              }
+              mail_take_d(a.bar, a.mail, mail_bytes, off, need, tag, p, dead);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) p[e] = need[e] ? p[e] : 0.0;
+              t += (p[0] + p[1]) + (p[2] + p[3]);
+            }
+          } else if (j <= k + 1) {
             const double* ph = a.part_h + j;
             int q = tid / width;
 #pragma unroll 1
@@ -893,17 +984,19 @@ __global__ __launch_bounds__(kLzBlock) void k_ra_lanczos(LzArgs a) {
         }
         __syncthreads();
         acc = 0.0;
+        ++tag;
         combine(hs, k + 1, [&](int r, double t) {
           if (l16 != 0) return;
           const double wr = src[r] - t;
           w[r] = wr;
-          store_wt(&a.wbuf[row0 + r], wr);
+          put(&a.wbuf[row0 + r], 16u * (unsigned)(row0 + r), wr);
           acc = fma(wr, wr, acc);
         });
         norm_out(acc);
         alpha += hs[k];
         const double before = hs[k + 1];
-        grid_barrier_wt(gb);
+        exchange();
+        take_first();
         nrm2 = norm_in();
         if (!(nrm2 < 0.25 * before)) break;
       }
@@ -1099,12 +1192,16 @@ extern "C" fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* s, const float* Rre
   if (s->lz_coop_blocks <= 0) {
     int lds_max = 0, per_cu = 0;
     FM_HIP_TRY(ctx, hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-    for (const void* k : {(const void*)k_ra_lanczos<false>, (const void*)k_ra_lanczos<true>})
+    for (const void* k : {(const void*)k_ra_lanczos<false, false>, (const void*)k_ra_lanczos<false, true>,
+                          (const void*)k_ra_lanczos<true, false>})
       FM_HIP_TRY(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
-    FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ra_lanczos<false>, kLzBlock, lds_max));
+    FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_ra_lanczos<false, false>, kLzBlock, lds_max));
+    int per_cu_m = 0;
+    FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_m, k_ra_lanczos<false, true>, kLzBlock, lds_max));
+    if (per_cu_m < per_cu) per_cu = per_cu_m;
     int per_cu_g = 0;
     FM_HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &per_cu_g, k_ra_lanczos<true>, kLzBlock, sizeof(double) * (kLzMaxSteps + 2 + kLzMisc)));
+                        &per_cu_g, k_ra_lanczos<true, false>, kLzBlock, sizeof(double) * (kLzMaxSteps + 2 + kLzMisc)));
     if (per_cu_g < per_cu) per_cu = per_cu_g;
     s->lz_coop_blocks = per_cu * ctx->num_cu;
     s->lz_lds = lds_max;
@@ -1113,7 +1210,8 @@ extern "C" fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* s, const float* Rre
   // cameras per workgroup: one per wavefront on small graphs, else 16, 32 or a
   // higher multiple of 16, so that a workgroup's rows are whole 128-byte lines
   // (more workgroups make the barriers and the sums of partials dearer, fewer
-  // the operator and the basis products: 200 cameras 25 workgroups 1.08 ms, 13
+  // the operator and the basis products: with
+  // grid barriers: 200 cameras 25 workgroups 1.08 ms, 13
   // 1.23, 50 1.16; 1,000 cameras 63 workgroups 4.7 ms, 32 and 125 5.4; 5,000
   // cameras 157 workgroups 12.9 ms, 105 14.7, 209 13.3)
   int64_t nc = kLzWaves;
@@ -1135,9 +1233,11 @@ extern "C" fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* s, const float* Rre
   if (lv > m) lv = m;
   const size_t lds_bytes = sizeof(double) * (head + (in_lds ? lz_work(rows, m) + lv * (rows | 1) : 0));
   // workspace: V [(m - lv) n] | wbuf [n] | part_h [want lz_hrow(m)] | part_n [want kLzWaves] | gws,
-  // wbuf and part_h at whole 128-byte lines
+  // wbuf and part_h at whole 128-byte lines; as mailboxes twice the size
+  const bool mail = in_lds && want <= kLzMailBlocks;
   const int64_t vpad = ((m - lv) * n + 15) / 16 * 16, wpad = (n + 15) / 16 * 16;
-  const int64_t need = vpad + wpad + want * (lz_hrow(m) + kLzWaves) + (in_lds ? 0 : want * lz_work(rows, m));
+  const int64_t shared = wpad + want * (lz_hrow(m) + kLzWaves);
+  const int64_t need = vpad + (mail ? 2 : 1) * shared + (in_lds ? 0 : want * lz_work(rows, m));
   if (need > s->lz_cap) {
     FM_HIP_TRY(ctx, hipDeviceSynchronize());
     (void)hipFree(s->lz);
@@ -1157,13 +1257,15 @@ extern "C" fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* s, const float* Rre
   a.part_h = a.wbuf + wpad;
   a.part_n = a.part_h + want * lz_hrow(m);
   a.gws = a.part_n + want * kLzWaves;
+  a.mail = reinterpret_cast<MailWord*>(a.wbuf);
   a.n = n; a.N = s->N; a.m = m; a.nc = (int32_t)nc; a.lv = (int32_t)lv;
   a.inv_P = 1.0 / (double)s->P; a.inv_N = 1.0 / (double)s->N;
   fm_timed timer(ctx, FM_K_RA_INIT, st);
   void* args[] = {&a};
-  FM_HIP_TRY(ctx, fm_bar_reset(s->bar, st));
-  hipError_t e = hipLaunchCooperativeKernel(in_lds ? (const void*)k_ra_lanczos<false> : (const void*)k_ra_lanczos<true>,
-                                            dim3((unsigned)want), dim3(kLzBlock), args, lds_bytes, st);
+  FM_HIP_TRY(ctx, mail ? fm_mail_reset(s->bar, a.mail, 2 * shared, st) : fm_bar_reset(s->bar, st));
+  const void* kernel = mail ? (const void*)k_ra_lanczos<false, true>
+                            : (in_lds ? (const void*)k_ra_lanczos<false, false> : (const void*)k_ra_lanczos<true, false>);
+  hipError_t e = hipLaunchCooperativeKernel(kernel, dim3((unsigned)want), dim3(kLzBlock), args, lds_bytes, st);
   if (e != hipSuccess) return fm_fail(ctx, FM_ECOOP, "cooperative launch failed: %s", hipGetErrorString(e));
   return FM_OK;
 }
