@@ -552,7 +552,7 @@ __device__ inline double wave_sum6_loss(double (&acc)[6], double loss, int lane)
 // (One thread summing each iteration's partials in turn costs a chain of
 // loads past the caches on the loop's critical path: 100 traced iterations
 // took 1,070 us on the 200-camera helix graph and 3,528 us on the
-// 5,000-camera street graph, against 533 and 2,074 us so.)  A batch's rows are
+// 5,000-camera street graph, when the change was made against 585 and 2,213 so.)  A batch's rows are
 // rewritten one batch later, when every workgroup has passed barriers that
 // its reader reached after reading.
 constexpr int kTraceBatch = 16;
@@ -601,8 +601,9 @@ __device__ inline void omega_grad(const Gs& f, const double om[3], const double 
 // are read before the selection: read under it, the compiler merges them into
 // one load at a variable index, and the array goes to scratch or to LDS, whose
 // share per thread is found from the dispatch packet in host memory
-// (k_camera_grad at 5,000 cameras 5.0 us against 18, 100 fused iterations at 200
-// cameras 533 against 583 and at 5,000 cameras 2,074 against 2,160).
+// (k_camera_grad at 5,000 cameras 5.0 us against 18; 100 fused iterations, when
+// the change was made, at 200 cameras 533 against 583 and at 5,000 cameras 2,074
+// against 2,160).
 __device__ __forceinline__ double pick9(const double (&g)[9], int q) {
   const double g0 = g[0], g1 = g[1], g2 = g[2], g3 = g[3], g4 = g[4], g5 = g[5], g6 = g[6], g7 = g[7], g8 = g[8];
   double v = g0;
