@@ -338,8 +338,8 @@ __global__ __launch_bounds__(kSolveBlock) void k_ta_solve(TaArgs a) {
   }
 }
 
-// Camera-by-camera variant of the fused loop (the automatic choice): one
-// wavefront per camera; each lane evaluates one of the camera's pairs for a
+// Camera-by-camera variant of the fused loop (the automatic choice where the
+// mailbox loop below does not run): one wavefront per camera; each lane evaluates one of the camera's pairs for a
 // group of runs and keeps its own side of dL/ds, rounded to float32 as the
 // pair records are; the wavefront sums them in a fixed order and lanes
 // 0 .. 3G-1 take the Adam steps.  Every pair is evaluated from both of its
@@ -995,7 +995,7 @@ extern "C" fm_status fm_translation_solve(fm_ctx* ctx, fm_scene* s, const float*
   }
   FM_HIP_TRY(ctx, fm_bar_reset(s->bar, st));
   if (cfg->blocks <= 0) {
-    // automatic grid: the camera loop, one wavefront per camera up to the
+    // automatic grid past the mailbox loop: the camera loop, one wavefront per camera up to the
     // co-resident limit (cameras strided beyond it).  Unlike the epipolar
     // pair term, this one is cheap enough to evaluate twice at any size
     // measured: on the 5,000-camera street graph (185k pairs) 24.0 against
