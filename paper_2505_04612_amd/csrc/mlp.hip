@@ -525,8 +525,19 @@ __device__ inline float log_f32(double x) {
 __device__ inline float angle_f32(double y2, double x) {
   // sqrt(y2) by one step on the reciprocal square root's estimate
   const double c = fmax(y2, 1e-300), h = __builtin_amdgcn_rsq(c), t0 = c * h;
-  const double y = fma(0.5 * t0, fma(-t0, h, 1.0), t0);
-  const double ax = fabs(x), mn = fmin(y, ax), mx = fmax(y, ax);
+  double y = fma(0.5 * t0, fma(-t0, h, 1.0), t0), ax = fabs(x);
+  // past the range of the estimates above (float64 coordinates beyond about
+  // 1e75): infinities count as atan2 counts them, large finite values are scaled
+  if (__builtin_expect(fmax(y2, ax) >= 1e300, 0)) {
+    if (__builtin_isinf(y2) || __builtin_isinf(ax)) {
+      y = __builtin_isinf(y2) ? 1.0 : 0.0;
+      ax = __builtin_isinf(ax) ? 1.0 : 0.0;
+    } else {
+      y *= 0x1p-600;
+      ax *= 0x1p-600;
+    }
+  }
+  const double mn = fmin(y, ax), mx = fmax(y, ax);
   const bool big = mn > 0.41421356237309505 * mx;
   const double num = big ? mn - mx : mn, den = big ? mn + mx : mx;
   const double z = num * rcp_newton(den), w = z * z;
