@@ -526,16 +526,14 @@ __device__ inline float angle_f32(double y2, double x) {
   // sqrt(y2) by one step on the reciprocal square root's estimate
   const double c = fmax(y2, 1e-300), h = __builtin_amdgcn_rsq(c), t0 = c * h;
   double y = fma(0.5 * t0, fma(-t0, h, 1.0), t0), ax = fabs(x);
-  // past the range of the estimates above (float64 coordinates beyond about
-  // 1e75): infinities count as atan2 counts them, large finite values are scaled
-  if (__builtin_expect(fmax(y2, ax) >= 1e300, 0)) {
-    if (__builtin_isinf(y2) || __builtin_isinf(ax)) {
-      y = __builtin_isinf(y2) ? 1.0 : 0.0;
-      ax = __builtin_isinf(ax) ? 1.0 : 0.0;
-    } else {
-      y *= 0x1p-600;
-      ax *= 0x1p-600;
-    }
+  // past the range of the estimates (float64 coordinates beyond about 1e74),
+  // told by the exponents (2e298 and above): infinities count as atan2 counts
+  // them, large finite values are scaled, and a NaN becomes the quotient 0/0
+  const unsigned top = max((unsigned)__double2hiint(y2) & 0x7fffffffu, (unsigned)__double2hiint(x) & 0x7fffffffu);
+  if (__builtin_expect(top >= 0x7de00000u, 0)) {
+    const bool nan = isnan(y2) || isnan(x), yi = isinf(y2), xi = isinf(ax);
+    y = nan ? 0.0 : (yi ? 1.0 : (xi ? 0.0 : y * 0x1p-600));
+    ax = nan ? 0.0 : (xi ? 1.0 : (yi ? 0.0 : ax * 0x1p-600));
   }
   const double mn = fmin(y, ax), mx = fmax(y, ax);
   const bool big = mn > 0.41421356237309505 * mx;
@@ -551,9 +549,7 @@ __device__ inline float angle_f32(double y2, double x) {
   q = fma(q, w, in_sgpr(0.9999999999992447));
   double a = fma(z, q, big ? 0.78539816339744831 : 0.0);
   a = y > ax ? 1.5707963267948966 - a : a;
-  a = x < 0.0 ? 3.1415926535897931 - a : a;
-  // a quotient of non-finite terms stays NaN (fmin and fmax drop one)
-  return (float)(isnan(y2) || isnan(x) ? NAN : a);
+  return (float)(x < 0.0 ? 3.1415926535897931 - a : a);
 }
 
 struct __attribute__((packed, aligned(4))) Feat3 {

@@ -43,3 +43,17 @@ def test_angle_of_huge_coordinates(m1, m2):
     f0 = np.log(np.maximum(r, np.float64(np.float32(1e-4))))
     scale = 3e-14 * np.abs(a).max(axis=1) * np.abs(b).max(axis=1)
     assert np.all(np.abs(got[:, 0] - f0) <= 6.1e-8 * np.abs(f0) + 1e-11 + scale / r)
+
+
+def test_a_nan_coordinate_stays_nan():
+    from paper_2505_04612_amd import api
+    ctx = api.default_context()
+    uv = np.full((70, 4), 0.25)
+    uv[3, 0] = uv[66, 3] = np.nan
+    th = np.zeros((2, 9), np.float32)
+    th[:, 0] = th[:, 4] = 1.0
+    th[1, 6] = 1.0
+    s = api.Scene.from_numpy(ctx, 2, np.array([[0, 1]], np.int32), np.array([0, 70], np.int64), uv, torch.float64)
+    got = api.match_features(s, torch.from_numpy(th).to(ctx.device), 1e-4).cpu().numpy()
+    assert np.array_equal(np.flatnonzero(np.isnan(got[:, 2])), [3, 66])
+    assert np.all(np.abs(got[:, 0] - np.log(np.float64(np.float32(1e-4)))) <= 1e-6)
