@@ -135,7 +135,7 @@ struct fm_scene {
   // workspace
   float* partials = nullptr;      // [n_big, 36]
   double* ess = nullptr;          // [P, 12] essential matrices (reweight: rows of 9) or relative poses (features: rows of 12)
-  float* contrib = nullptr;       // [P, 24] per-pair gradient records
+  float* contrib = nullptr;       // [P, 24] gradient records: 24 floats per pair, or 6 floats or doubles per incidence slot
   float* fo_rec = nullptr;        // [P, 2] per-pair focal-scale gradient records (side i, side j)
   double* loss_part = nullptr;    // [loss_part_cap]
   double* rot = nullptr;          // [2, N, 9] rotations of the current poses (fused solve; two buffers)

@@ -129,20 +129,23 @@ __device__ inline double pair_loss_omega(const float* __restrict__ params, const
   return pair_adjoint(pair_eval(params, rot, ci, cj, w), two_inv_Z, om, dti, dtj);
 }
 
-// Camera-major record layout: the 6 floats of item q of the
+// Camera-major record layout: the 6 numbers of item q of the
 // incidence lists (a pair's side for one camera: its body-frame rotation
 // gradient, -om for camera i and om for camera j, then dL/dt of that camera)
-// at contrib + 6 q, so a camera's records are one contiguous run.
+// at contrib + 6 q, so a camera's records are one contiguous run: float32 in
+// the fused loop, float64 in the standalone gradient (V: a vector of two).
+template <typename V>
 __device__ inline void store_sides(float* __restrict__ contrib, int qi, int qj, const double om[3],
                                    const double dti[3], const double dtj[3]) {
-  float2* di = reinterpret_cast<float2*>(contrib + (int64_t)qi * 6);
-  float2* dj = reinterpret_cast<float2*>(contrib + (int64_t)qj * 6);
-  di[0] = make_float2((float)-om[0], (float)-om[1]);
-  di[1] = make_float2((float)-om[2], (float)dti[0]);
-  di[2] = make_float2((float)dti[1], (float)dti[2]);
-  dj[0] = make_float2((float)om[0], (float)om[1]);
-  dj[1] = make_float2((float)om[2], (float)dtj[0]);
-  dj[2] = make_float2((float)dtj[1], (float)dtj[2]);
+  using T = decltype(V::x);
+  V* di = reinterpret_cast<V*>(contrib) + (int64_t)qi * 3;
+  V* dj = reinterpret_cast<V*>(contrib) + (int64_t)qj * 3;
+  di[0] = V{(T)-om[0], (T)-om[1]};
+  di[1] = V{(T)-om[2], (T)dti[0]};
+  di[2] = V{(T)dti[1], (T)dti[2]};
+  dj[0] = V{(T)om[0], (T)om[1]};
+  dj[1] = V{(T)om[2], (T)dtj[0]};
+  dj[2] = V{(T)dtj[1], (T)dtj[2]};
 }
 
 // Pair phase of the fused pair loop over pairs [first, P) with stride
@@ -159,7 +162,7 @@ __device__ inline double pair_phase_slots(const float* params, const double* rot
   if constexpr (kHold) {
     if (first < P) {
       sum += pair_loss_omega(params, rot, ci0, cj0, w0, two_inv_Z, om, dti, dtj);
-      store_sides(contrib, qi0, qj0, om, dti, dtj);
+      store_sides<float2>(contrib, qi0, qj0, om, dti, dtj);
     }
   }
   for (int64_t n = kHold ? first + stride : first; n < P; n += stride) {
@@ -168,7 +171,7 @@ __device__ inline double pair_phase_slots(const float* params, const double* rot
     const int qi = held0 ? qi0 : (held1 ? qi1 : pair_slot[2 * n]);
     const int qj = held0 ? qj0 : (held1 ? qj1 : pair_slot[2 * n + 1]);
     sum += pair_loss_omega(params, rot, ci, cj, W36 + n * 36, two_inv_Z, om, dti, dtj);
-    store_sides(contrib, qi, qj, om, dti, dtj);
+    store_sides<float2>(contrib, qi, qj, om, dti, dtj);
   }
   return sum;
 }
@@ -179,20 +182,20 @@ __device__ inline double pair_phase_slots(const float* params, const double* rot
 constexpr int kRowItems = 6;
 
 // Summed records of one camera in every lane of its row, from the
-// camera-major layout (slots lo..hi-1, 6 floats each): lane l16 takes slots
+// camera-major layout (slots lo..hi-1, 6 numbers each): lane l16 takes slots
 // lo + l16 + 16 j; the first NE of them are all loaded before any is added
 // (without lane conditions, under which each load is waited for on its own:
 // slots past the end load the last one's record, or a camera without pairs
-// its successor's, and count as 0), then added in slot order, then the rest.
+// its predecessor's, and count as 0), then added in slot order, then the rest.
 // The pair loop on the 5,000-camera street graph (74 pairs per camera) takes
 // 0.5 us less per iteration than with conditional loads.  acc = (om, dL/dt) of the camera.
-template <int NE>
+template <int NE, typename V>
 __device__ inline void row_camera_sums_slots(int lo, int hi, const float* __restrict__ contrib, int lane,
                                              double (&acc)[6]) {
-  const float2* c = reinterpret_cast<const float2*>(contrib);
+  const V* c = reinterpret_cast<const V*>(contrib);
   const int l16 = lane & 15;
-  const int last = hi > lo ? hi - 1 : lo;
-  float2 r[NE][3];
+  const int last = max(hi - 1, 0);
+  V r[NE][3];
 #pragma unroll
   for (int j = 0; j < NE; ++j) {
     const int q = min(lo + l16 + 16 * j, last);
@@ -204,8 +207,8 @@ __device__ inline void row_camera_sums_slots(int lo, int hi, const float* __rest
     const bool live = lo + l16 + 16 * j < hi;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      r[j][k].x = live ? r[j][k].x : 0.0f;
-      r[j][k].y = live ? r[j][k].y : 0.0f;
+      r[j][k].x = live ? r[j][k].x : 0;
+      r[j][k].y = live ? r[j][k].y : 0;
     }
   }
 #pragma unroll
@@ -216,7 +219,7 @@ __device__ inline void row_camera_sums_slots(int lo, int hi, const float* __rest
     acc[3] += r[j][1].y; acc[4] += r[j][2].x; acc[5] += r[j][2].y;
   }
   for (int q = lo + 16 * NE + l16; q < hi; q += 16) {
-    const float2 a0 = c[(int64_t)q * 3], a1 = c[(int64_t)q * 3 + 1], a2 = c[(int64_t)q * 3 + 2];
+    const V a0 = c[(int64_t)q * 3], a1 = c[(int64_t)q * 3 + 1], a2 = c[(int64_t)q * 3 + 2];
     acc[0] += a0.x; acc[1] += a0.y; acc[2] += a1.x;
     acc[3] += a1.y; acc[4] += a2.x; acc[5] += a2.y;
   }
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_phase(const float* __restrict__
   if (n < P) {
     double om[3], dti[3], dtj[3];
     v = pair_loss_omega(params, nullptr, cams[2 * n], cams[2 * n + 1], W36 + n * 36, 2.0 * iz, om, dti, dtj);
-    store_sides(contrib, pair_slot[2 * n], pair_slot[2 * n + 1], om, dti, dtj);
+    store_sides<double2>(contrib, pair_slot[2 * n], pair_slot[2 * n + 1], om, dti, dtj);
   }
   const double t = block_sum(v, lds);
   if (threadIdx.x == 0) loss_part[blockIdx.x] = t;
@@ -249,11 +252,14 @@ __global__ __launch_bounds__(kBlock) void k_pair_phase(const float* __restrict__
 // One 16-lane row per camera: its records summed in a fixed order, the
 // Gram-Schmidt adjoint (the same lanes for four cameras: their float64 chains
 // are what the kernel issues).  The last workgroup, one more than the cameras
-// take, sums the loss partials instead.  The whole call on the 186k-pair
-// street graph: 16.0 us (11.6 the pairs, 5.0 the cameras), against 62.3 with
-// the partials added by one thread, a wavefront per camera and 24-float
-// records; at 1,000 cameras 13.8 against 22.8, both 14 up to 200 cameras, where
-// the launches bound them.
+// take, sums the loss partials instead.  The records are float64: rounded to
+// float32, the gradient was on average 3.5e-8 from 64 bits (relative, 24 graphs
+// of 20 to 3,000 cameras; 2.5e-8 now, the rounding of the result), further
+// than the 3.4e-8 of 24-float records.  The whole call on the 186k-pair street
+// graph: 20.4 us (16.1 with float32 records), against 57.9 with the partials
+// added by one thread, a wavefront per camera and 24-float records; at 1,000
+// cameras 11.8 against 23.5, 12 against 14 to 15 up to 200 cameras, where the
+// launches bound them.
 __global__ __launch_bounds__(kLanes) void k_camera_grad(const float* __restrict__ params,
                                                         const int32_t* __restrict__ cam_ptr,
                                                         const float* __restrict__ contrib, int32_t N,
@@ -276,7 +282,7 @@ __global__ __launch_bounds__(kLanes) void k_camera_grad(const float* __restrict_
   double a1[3], a2[3], t[3], acc6[6], acc[12], g[9];
   load_pose(params, (int)c, a1, a2, t);
   const Gs f = gs_forward(a1, a2);
-  row_camera_sums_slots<kRowItems>(cam_ptr[c], cam_ptr[c + 1], contrib, lane, acc6);
+  row_camera_sums_slots<kRowItems, double2>(cam_ptr[c], cam_ptr[c + 1], contrib, lane, acc6);
   omega_grad(f, acc6, acc6 + 3, acc);
   gs_adjoint(acc, f, a2, g);
   if (l16 < 9) grad[c * 9 + l16] = (float)pick9(g, l16);
@@ -517,7 +523,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_solve(SolveArgs a) {
       }
       if (!live) a1[0] = a2[1] = 1.0;
       const Gs f = gs_forward(a1, a2);
-      row_camera_sums_slots<kRowItems>(lo, hi, a.contrib, lane, acc6);
+      row_camera_sums_slots<kRowItems, float2>(lo, hi, a.contrib, lane, acc6);
       omega_grad(f, acc6, acc6 + 3, acc);
       gs_adjoint(acc, f, a2, g);
       // lanes 0..8 of the row update one parameter each
