@@ -240,12 +240,13 @@ fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* scene, const void* W36, fm_dt
                             double inv_Z, const int64_t* Z_dev, double* loss_trace,
                             fm_stream stream);
 
-/* Failed grid barriers of the persistent launches (fm_epipolar_solve,
+/* Expired waits of the persistent launches (fm_epipolar_solve,
  * fm_translation_solve, fm_rotation_solve, fm_rotation_init) on this scene
  * since the last call (host value in *failures), then cleared.  A wait (at
- * a barrier, or for a neighbour's parameters) is bounded; if it expires, the launch stops at once and its
- * results are invalid.  Synchronises the device.  Not expected to be nonzero:
- * the cooperative launch makes every workgroup resident. */
+ * a barrier, or for a neighbour's values) is bounded to about a second; if one
+ * expires, the launch's other waits end too, the launch runs out without
+ * waiting and its results are invalid.  Synchronises the device.  Not expected
+ * to be nonzero: the cooperative launch makes every workgroup resident. */
 fm_status fm_solve_barrier_failures(fm_ctx* ctx, fm_scene* scene, int64_t* failures);
 
 /* ------------------------------------------------------------------ focal refinement */

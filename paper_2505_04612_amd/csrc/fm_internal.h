@@ -10,6 +10,7 @@
 #include <hip/hip_ext.h>
 
 #include "fastmap_hip.h"
+#include "wait_bound.h"
 
 // Matches per feature work item: one wavefront of 64 lanes, 16 matches per lane.
 constexpr int kLanes = 64;
@@ -829,13 +830,14 @@ __device__ inline void mail_put(MailWord* w, float v, unsigned tag) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// After round `it` of a wavefront's wait: whether to look again.  The wait is
-// bounded as bar_reach's is: if it expires or another workgroup has raised the
-// launch's failure flag, `dead` is set and no later wait of this wavefront
-// goes past its first round.
-__device__ inline bool mail_again(unsigned* __restrict__ bar, unsigned it, bool& dead) {
+// After a round of a wavefront's wait that did not find its words: whether to
+// look again.  The wait is bounded (WaitBound): if it expires or another
+// wavefront has raised the launch's failure flag, `dead` is set (in every
+// lane), and no later wait of this wavefront goes past its first round.
+__device__ inline bool mail_again(unsigned* __restrict__ bar, WaitBound& wb, bool& dead) {
   if (dead) return false;
-  if (it % 256 == 0 && (it / 256 >= kBarSpinOuter || bar_load(bar + 64) != 0u)) {
+  if (!wb.go_on([] { return (unsigned long long)wall_clock64(); },
+                [&] { return __builtin_amdgcn_readfirstlane(bar_load(bar + 64)) != 0u; })) {
     dead = true;
     if (__lane_id() == 0) {
       __hip_atomic_fetch_add(bar + 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -860,7 +862,8 @@ __device__ inline void mail_take(unsigned* __restrict__ bar, MailWord* in, unsig
   using u32x4 = unsigned __attribute__((ext_vector_type(4)));
   constexpr int L = (W + 1) / 2;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(in, 0, (int)bytes, 0x00020000);
-  for (unsigned it = 1;; ++it) {
+  WaitBound wb;
+  for (;;) {
     // (read anew in every round: the builtin alone may be hoisted)
     asm volatile("" ::: "memory");
     u32x4 w[L];
@@ -872,7 +875,7 @@ __device__ inline void mail_take(unsigned* __restrict__ bar, MailWord* in, unsig
       diff |= (k & 1 ? w[k / 2].w : w[k / 2].y) ^ tag;
       v[k] = __uint_as_float(k & 1 ? w[k / 2].z : w[k / 2].x);
     }
-    if (!__any(need & (diff != 0u)) || !mail_again(bar, it, dead)) return;
+    if (!__any(need & (diff != 0u)) || !mail_again(bar, wb, dead)) return;
   }
 }
 
@@ -889,7 +892,8 @@ __device__ inline void mail_take_d(unsigned* __restrict__ bar, MailWord* in, uns
                                    const bool (&need)[L], unsigned tag, double (&v)[L], bool& dead) {
   using u32x4 = unsigned __attribute__((ext_vector_type(4)));
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(in, 0, (int)bytes, 0x00020000);
-  for (unsigned it = 1;; ++it) {
+  WaitBound wb;
+  for (;;) {
     asm volatile("" ::: "memory");
     u32x4 w[L];
 #pragma unroll
@@ -900,7 +904,7 @@ __device__ inline void mail_take_d(unsigned* __restrict__ bar, MailWord* in, uns
       wait |= need[e] & (((w[e].y ^ tag) | (w[e].w ^ tag)) != 0u);
       v[e] = __longlong_as_double((long long)(((unsigned long long)w[e].z << 32) | w[e].x));
     }
-    if (!__any(wait) || !mail_again(bar, it, dead)) return;
+    if (!__any(wait) || !mail_again(bar, wb, dead)) return;
   }
 }
 

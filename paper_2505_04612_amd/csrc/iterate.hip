@@ -661,6 +661,8 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
     f_own = cam_gs(p_own, a2_own);
   }
   GridBar gb = grid_bar(a.bar);
+  // a wait expired: the wavefront does no more than take part in its
+  // workgroup's barriers, of which an untraced launch has none
   bool dead = false;
   StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
   for (int k = 0; k < a.K; ++k) {
@@ -733,11 +735,11 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
       p0 = adam_update_inv(p0, (float)pick9(g, kq), mq, vq, lr, a.b1, a.b2, a.eps, ib1, ib2);
       if (lane < 9) mail_put(out + c * kMailWords + lane, p0, tag + 1u);
     };
-    if (own) {
+    if (own && !dead) {
       camera(std::true_type{}, gwave, s1, p_own, m_own, v_own, a2_own, f_own);
       f_own = cam_gs(p_own, a2_own);
     }
-    for (int64_t c = gwave + nwaves; c < a.N; c += nwaves) {
+    for (int64_t c = gwave + nwaves; c < a.N && !dead; c += nwaves) {
       float p0 = a.params[c * 9 + kq], mq = a.m[c * 9 + kq], vq = a.v[c * 9 + kq];
       double a2[3];
       const Gs f = cam_gs(p0, a2);
@@ -754,6 +756,8 @@ __global__ __launch_bounds__(kCamBlock) void k_solve_cam(CamSolveArgs a) {
         grid_barrier_wt(gb);
         trace_batch(a.loss_part, slots, k, a.K, iz, a.loss_trace, gwave, nwaves, lane);
       }
+    } else if (dead) {
+      break;
     }
   }
   // the first camera's values, kept in registers during the launch

@@ -667,6 +667,8 @@ __global__ __launch_bounds__(kCamBlock) void k_ta_solve_mail(TaMailArgs a) {
     if (lo < hi) e0 = ta_mail_entry(a, lo + lane, hi);
   }
   const int64_t NM = (int64_t)a.N * a.stride;
+  // a wait expired: the wavefront does no more than take part in its
+  // workgroup's barriers, of which an untraced launch has none
   bool dead = false;
   StepSched sch(a.log_frac, a.lr_step0, a.lr_total, a.adam_step0, a.b1, a.b2);
   for (int k = 0; k < a.K; ++k) {
@@ -680,7 +682,7 @@ __global__ __launch_bounds__(kCamBlock) void k_ta_solve_mail(TaMailArgs a) {
     sch.next();
     // (formed here, before the waits: sunk to their use they would follow them)
     asm volatile("" : "+v"(st.lr), "+v"(st.ib1), "+v"(st.ib2));
-    if (own) {
+    if (own && !dead) {
       int r0 = 0;
       for (; r0 + 4 <= a.runs; r0 += 4) ta_mail_group<4>(a, st, c, lo, hi, e0, lane, r0, k, dead);
       if (r0 + 2 <= a.runs) {
@@ -703,6 +705,8 @@ __global__ __launch_bounds__(kCamBlock) void k_ta_solve_mail(TaMailArgs a) {
         for (int sh = 32; sh >= 1; sh >>= 1) t += __shfl_xor(t, sh);
         if (lane == 0) a.trace[(int64_t)r * a.K + kk] = t * a.invP;
       }
+    } else if (dead && !a.trace) {
+      break;
     }
   }
 }
