@@ -817,10 +817,21 @@ __device__ inline void grid_barrier_wt(GridBar& gb) { grid_barrier_t<true>(gb); 
 // generation, no cache invalidation).  A record is `stride` words of 64 bits,
 // each a float32 and the iteration's tag: a word is read and written whole, so
 // a matching tag vouches for its value whatever the order in which the words
-// arrive.  Two records per camera, alternated by iteration: a camera's wavefront
+// arrive.  (Written by one 8-byte atomic store; read as the aligned half of a
+// 16-byte load of one lane, which no document promises to be whole but which a
+// probe found so on gfx950: of 3.1e9 words read from all XCDs while other
+// workgroups stored to them, 46 % of the reads finding a new tag, none held
+// one store's tag with another's value.)
+//
+// Two records per camera, alternated by iteration: a camera's wavefront
 // overwrites the record of iteration k - 1 when it publishes iteration k + 1,
 // after it took every neighbour's iteration k, which each published after it had
-// taken iteration k - 1 (pairs are listed at both of their cameras).  Tags
+// taken iteration k - 1 (pairs are listed at both of their cameras).  Nor can the
+// waits close a circle, however many cameras a wavefront has and passes a
+// camera: a camera's step k needs its neighbours' steps k - 1 and, in its
+// wavefront, the step k of the cameras before it, and every workgroup is
+// resident; so the first unfinished step in the order of (k, place in the
+// wavefront) always has what it needs.  Tags
 // start at 1 and only grow within a launch; fm_mail_reset clears those
 // an earlier launch left.
 using MailWord = unsigned long long;

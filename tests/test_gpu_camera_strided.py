@@ -1,0 +1,59 @@
+"""The epipolar camera loop with several cameras a wavefront and several passes
+of 64 pairs a camera (more than 1,024 cameras of more than 64 pairs), and the
+pair loop on grids that synchronise per XCD, against the oracle's Adam steps."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ea
+from tests import helpers
+
+pytestmark = pytest.mark.gpu
+
+
+# cameras, pairs to each side: two cameras a wavefront and two passes, three
+# and two, five and one
+@pytest.mark.parametrize("N,reach", [(1100, 35), (2300, 34), (4500, 9)])
+def test_loops_follow_oracle_steps(N, reach):
+    from paper_2505_04612_amd import api
+    ctx = api.default_context()
+    rng = np.random.default_rng(N)
+    pairs = np.array([(i, i + k) for i in range(N) for k in range(1, reach + 1) if i + k < N], dtype=np.int32)
+    P, per, K = len(pairs), 9, 17
+    assert P < 81920
+    uv = rng.normal(scale=0.5, size=(per * P, 4))
+    s = api.Scene.from_numpy(ctx, N, pairs, (np.arange(P + 1) * per).astype(np.int64), uv, torch.float64)
+    W = api.build_pair_grams(s)[0]
+    th = rng.normal(size=(N, 9)).astype(np.float32)
+    iz = 1.0 / (per * P)
+    out = []
+    for blocks in (-1, -1, 128, 192):
+        p = torch.from_numpy(th).to(ctx.device)
+        m, v = torch.zeros_like(p), torch.zeros_like(p)
+        tr = torch.zeros(K, dtype=torch.float64, device=ctx.device)
+        api.epipolar_solve(s, W, p, m, v, K, 3e-3, 1e-2, 1e-2, 0, 20, inv_Z=iz, blocks=blocks, loss_trace=tr)
+        out.append((p, m, v, tr))
+    assert s.barrier_failures() == 0
+    for x, y in zip(out[0], out[1]):
+        assert torch.equal(x, y)
+    for x, y in zip(out[2][:3], out[3][:3]):
+        assert torch.equal(x, y)
+    W9 = helpers.expand36(W.cpu().numpy())
+    f32 = helpers.f32
+    sched = ea.Schedule(iters=20, round_len=20, lr_rot=f32(3e-3), lr_t=f32(1e-2), lr_final_frac=f32(1e-2),
+                        beta1=f32(0.9), beta2=f32(0.999), eps=f32(1e-12))
+    ref = th.astype(np.float64)
+    mr, vr = np.zeros_like(ref), np.zeros_like(ref)
+    losses = []
+    for k in range(K):
+        L, g = ea.loss_grad(ref, pairs, W9, iz)
+        losses.append(L)
+        ref, mr, vr = ea.adam_step(ref, g, mr, vr, k + 1, ea.lr_at(sched, k), sched.beta1, sched.beta2, sched.eps)
+    for p, _, _, tr in (out[0], out[2]):
+        # a step moves by lr = 1e-2 times the relative error of its gradient,
+        # 6e-8 of the records over the cancellation c in a camera's sum, and the
+        # parameters are rounded to float32 (2e-7 each step): 1e-5 over 17 steps
+        # for c up to 1e3; a c ten times as large comes up once in 1e4 entries
+        d = np.abs(p.cpu().numpy() - ref)
+        assert d.max() <= 1e-4 and np.mean(d > 1e-5) <= 1e-3, (d.max(), np.mean(d > 1e-5))
+        assert np.allclose(tr.cpu().numpy(), losses, rtol=1e-5, atol=0)
