@@ -228,12 +228,14 @@ typedef struct {
  * params} in ONE persistent cooperative kernel, with no host round trip
  * between iterations.  Two loops, same results up to the order of the float64
  * sums: pair by pair (a per-pair phase writes the records, a per-camera phase
- * sums them and steps Adam, grid-wide barriers between the two), or, for
- * graphs below 81,920 pairs when cfg->blocks is 0, camera by camera (one
- * wavefront per camera evaluates each of its pairs, so every pair is
- * evaluated from both ends, and waits for its neighbours' parameters instead
- * of a grid barrier; cfg->blocks < 0 selects this loop at any size).  params, m, v [N,9] float32 are
- * updated in place.  loss_trace [K] double receives L before each update
+ * sums them and steps Adam, grid-wide barriers between the two), or camera by
+ * camera (one wavefront per camera evaluates each of its pairs, so every pair
+ * is evaluated from both ends, and waits for its neighbours' parameters
+ * instead of a grid barrier).  cfg->blocks 0 takes the camera loop below
+ * 131,072 pairs where each camera has a wavefront of its own (1,024 cameras) or
+ * where few enough cameras of few enough pairs share one, < 0 takes it at any
+ * size, and a workgroup count takes the pair loop.  params, m, v [N,9] float32
+ * are updated in place.  loss_trace [K] double receives L before each update
  * (NULL = not written).  `cfg` is a host pointer. */
 fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* scene, const void* W36, fm_dtype wdtype,
                             float* params, float* m, float* v, int32_t K, const fm_adam_cfg* cfg,

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -675,19 +676,37 @@ __device__ inline float adam_update(float p, float g, float& m, float& v, double
   return adam_update_inv(p, g, m, v, lr, b1, b2, eps, 1.0 / bc1, 1.0 / bc2);
 }
 
-// Pair count below which the epipolar persistent loop runs camera by camera
-// when the caller leaves the grid automatic (the translation and rotation
-// loops, whose pair terms are cheaper, always do): one wavefront
-// per camera evaluates each of its pairs, so every pair is evaluated twice
-// but an iteration has no grid barrier and no record round trip.  Above
-// it, where a wavefront has several cameras and passes of 64 pairs to go
-// through, the pair loop wins.  Measured with float32 Grams, us per iteration
-// (camera vs the better pair grid), street graphs of cameras / pairs: 200 /
-// 4.5k 3.3 vs 8.5; 1,000 / 24k 4.8 vs 12.8; 1,000 / 41k 7.3 vs 13.5;
-// 2,500 / 68k 10.9 vs 14.8; 2,000 / 80k 11.1 vs 15.5; and, with 8-byte reads of
-// the mailboxes, 5,000 / 95k 18.8 vs 15.6; 2,500 / 97k 21.2 vs 15.8; 3,000 / 110k
-// 20.1 vs 17.1.  Dense graphs: 100 / 5k 4.9 vs 10.3, 400 / 60k 14.9 vs 19.7.
-constexpr int64_t kCamLoopMaxPairs = 81920;
+// Whether the automatic grid runs the epipolar persistent loop camera by camera
+// (the rotation and focal loops, whose pair terms are cheaper, always do):
+// one wavefront per camera evaluates each of its pairs, so every pair is
+// evaluated twice, but an iteration has no grid barrier and no record round
+// trip.  What it costs is the chain of a wavefront's cameras (one per wavefront
+// up to 4 num_cu of them) and of each camera's passes of 64 pairs: about 1 us a
+// camera and 2.4 a pass; the pair loop costs about 11.2 us and 45 us per million
+// pairs, more on dense graphs.  Measured with float32 Grams, us per iteration
+// (camera vs the better of three pair grids), banded and street graphs of
+// cameras / pairs:
+//   one camera a wavefront: 200 / 4.8k 3.2 vs 8.5; 1,000 / 25k 4.4 vs 12.8;
+//     600 / 65k 9.9 vs 16.3; 400 / 60k 13.7 vs 19.0; 1,000 / 130k 13.8 vs 21.5
+//   two: 2,000 / 39k 7.0 vs 12.7; 1,100 / 38k 12.0 vs 12.8; 2,000 / 95k 10.8 vs
+//     15.5; 1,300 / 125k (three passes of the second, 4 of 5 wavefronts without
+//     one) 23.8 vs 19.8
+//   three: 3,000 / 18k 10.1 vs 12.5; 3,072 / 61k 10.4 vs 13.2; 2,500 / 68k 10.7
+//     vs 14.5; with two passes 2,600 / 93k 16.8 vs 15.1, 3,000 / 110k 17.8 vs 17.3
+//   four: 4,000 / 24k 13.6 vs 12.3; 3,500 / 35k 13.9 vs 12.8; 4,000 / 80k 14.0 vs
+//     14.5; 4,096 / 122k 15.4 vs 17.2
+//   five and more: 5,000 / 15k 16.9 vs 13.3; 5,000 / 59k 17.5 vs 14.3; 8,000 / 64k
+//     27.0 vs 16.6; 20,000 / 80k 70.0 vs 24.2; 40,000 / 40k 135 vs 33
+// Past kCamLoopMaxPairs the pair loop always runs.
+constexpr int64_t kCamLoopMaxPairs = 131072;
+
+inline bool cam_loop_wins(int64_t N, int64_t P, int num_cu) {
+  if (P >= kCamLoopMaxPairs) return false;
+  const int64_t waves = (int64_t)num_cu * (kCamBlock / 64), cams = (N + waves - 1) / waves;
+  if (cams <= 1) return true;
+  const int64_t passes = std::max<int64_t>(1, (2 * P + 64 * N - 1) / (64 * N));
+  return (double)cams * (1.0 + 2.4 * (double)passes) < 11.2 + 45e-6 * (double)P;
+}
 
 // Workgroup count from which the fused pair loop synchronises with the
 // per-XCD grid_sync instead of the flat grid_barrier.  Per iteration, flat

@@ -824,15 +824,20 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   if (!Z_dev && !(inv_Z >= 0.0)) return fm_fail(ctx, FM_EINVAL, "fm_epipolar_solve: inv_Z must be >= 0");
   if (K == 0) return FM_OK;
   FM_HIP_TRY(ctx, hipSetDevice(ctx->device));
-  // about one pair per thread or one 16-lane row per camera, capped at 16
-  // workgroups below 32k pairs and at 192 above (each workgroup adds about
-  // 0.02 us to each of the two grid barriers per iteration, measured, so
-  // past these sizes a second round of pairs per thread is cheaper than more
-  // workgroups), and at the co-resident limit
+  // about one pair per thread and one 16-lane row per camera, capped at 192
+  // workgroups (each adds about 0.02 us to each of the two grid barriers per
+  // iteration, measured, so past this size a second round of pairs per thread
+  // or of cameras per row is cheaper than more workgroups), and at the
+  // co-resident limit; at least as many as synchronise per XCD.  The graphs
+  // that come here by themselves have 131k pairs, or over 1,024 cameras that
+  // cost more camera by camera (cam_loop_wins): 4,000 cameras / 24k pairs 12.3
+  // us per iteration at 128 workgroups, 15.3 at 125 (flat barrier), 37 at 16;
+  // 20,000 / 40k 23.4 at 192, 25.4 at 128
   int64_t want = grid_for(s->P, kSolveBlock);
   const int64_t want_c = grid_for((int64_t)s->N * 16, kSolveBlock);
   if (want_c > want) want = want_c;
-  if (want > (s->P < 32768 ? 16 : 192)) want = s->P < 32768 ? 16 : 192;
+  if (want < kXcdSyncMinBlocks) want = kXcdSyncMinBlocks;
+  if (want > 192) want = 192;
   if (cfg->blocks > 0) want = cfg->blocks;
   if (want < 1) want = 1;
   if (want > s->coop_blocks) want = s->coop_blocks;
@@ -849,20 +854,20 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   a.lr_step0 = cfg->lr_step0; a.lr_total = cfg->lr_total_steps; a.adam_step0 = cfg->adam_step0;
   a.pair_slot = s->pair_slot;
   void* args[] = {&a};
-  // automatic grid below kCamLoopMaxPairs, or cfg->blocks < 0: the
+  // automatic grid where cam_loop_wins, or cfg->blocks < 0: the
   // camera-centric loop, no barrier in an iteration; a forced workgroup count
-  // or a larger graph (also one
-  // whose records a buffer descriptor does not span) runs the pair loop
-  // (workgroups of two wavefronts while they fit one to a CU: the wavefronts'
-  // scattered reads of the mailboxes spread over twice as many CUs: 100
-  // iterations at 200 cameras 417 us against 433, at 500 677 against 926;
-  // past a workgroup per CU four are better, at 1,000 612 against 673: all with
-  // 8-byte reads)
+  // or any other graph (also one whose records a buffer descriptor does not
+  // span) runs the pair loop.
+  // Workgroups of two wavefronts while they fit one to a CU: the wavefronts'
+  // scattered reads of the mailboxes spread over twice as many CUs (us per
+  // iteration, two against four: 200 cameras 3.16 against 3.40, 500 of 73 pairs
+  // 5.17 and 5.40, 512 of 180 pairs 9.2 and 9.9); past a workgroup per CU four
+  // (600 cameras 3.6 against 6.7, 1,000 4.4 and 6.5).
   const int cam_threads = ((int64_t)s->N + 1) / 2 <= ctx->num_cu ? kCamBlock / 2 : kCamBlock;
   int64_t want_cam = grid_for((int64_t)s->N * 64, cam_threads);
   if (want_cam > s->coop_blocks_cam) want_cam = s->coop_blocks_cam;
   if (want_cam > ctx->num_cu) want_cam = ctx->num_cu;
-  if ((cfg->blocks < 0 || (cfg->blocks == 0 && s->P < kCamLoopMaxPairs)) &&
+  if ((cfg->blocks < 0 || (cfg->blocks == 0 && cam_loop_wins(s->N, s->P, ctx->num_cu))) &&
       2 * kTraceBatch * want_cam * (cam_threads / 64) <= s->loss_part_cap &&
       (int64_t)s->N * kMailWords * (int64_t)sizeof(MailWord) <= INT32_MAX) {
     CamSolveArgs ca;

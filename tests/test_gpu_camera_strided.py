@@ -1,6 +1,7 @@
 """The epipolar camera loop with several cameras a wavefront and several passes
 of 64 pairs a camera (more than 1,024 cameras of more than 64 pairs), and the
-pair loop on grids that synchronise per XCD, against the oracle's Adam steps."""
+pair loop on grids that synchronise per XCD, against the oracle's Adam steps;
+and which of the two loops the automatic grid takes."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +21,7 @@ def test_loops_follow_oracle_steps(N, reach):
     rng = np.random.default_rng(N)
     pairs = np.array([(i, i + k) for i in range(N) for k in range(1, reach + 1) if i + k < N], dtype=np.int32)
     P, per, K = len(pairs), 9, 17
-    assert P < 81920
+    assert P < 131072
     uv = rng.normal(scale=0.5, size=(per * P, 4))
     s = api.Scene.from_numpy(ctx, N, pairs, (np.arange(P + 1) * per).astype(np.int64), uv, torch.float64)
     W = api.build_pair_grams(s)[0]
@@ -57,3 +58,39 @@ def test_loops_follow_oracle_steps(N, reach):
         d = np.abs(p.cpu().numpy() - ref)
         assert d.max() <= 1e-4 and np.mean(d > 1e-5) <= 1e-3, (d.max(), np.mean(d > 1e-5))
         assert np.allclose(tr.cpu().numpy(), losses, rtol=1e-5, atol=0)
+
+
+# cameras, pairs to each side, and whether the automatic grid takes the camera
+# loop (float64 Grams hold the same rule): one camera a wavefront, two passes of
+# two, one pass of three and four on both sides of the line, many sparse cameras
+@pytest.mark.parametrize("N,reach,cam", [(6, 5, True), (400, 230, True), (1024, 90, True), (1100, 35, True),
+                                         (2300, 34, False), (3000, 6, True), (4000, 6, False), (4000, 20, True),
+                                         (9000, 2, False)])
+def test_automatic_loop(N, reach, cam):
+    from paper_2505_04612_amd import api
+    ctx = api.default_context()
+    rng = np.random.default_rng(N + 1)
+    i = np.repeat(np.arange(N), reach)
+    j = i + np.tile(np.arange(1, reach + 1), N)
+    pairs = np.stack([i, j], 1)[j < N].astype(np.int32)
+    P, K = len(pairs), 5
+    uv = rng.normal(scale=0.5, size=(P, 4))
+    s = api.Scene.from_numpy(ctx, N, pairs, np.arange(P + 1, dtype=np.int64), uv, torch.float64)
+    W = torch.randn((P, 36), device=ctx.device, generator=torch.Generator(ctx.device).manual_seed(1))
+    th = torch.from_numpy(rng.normal(size=(N, 9)).astype(np.float32)).to(ctx.device)
+    out = {}
+    for blocks in (0, -1, 128):
+        p = th.clone()
+        m, v = torch.zeros_like(p), torch.zeros_like(p)
+        tr = torch.zeros(K, dtype=torch.float64, device=ctx.device)
+        api.epipolar_solve(s, W, p, m, v, K, 3e-3, 1e-2, 1e-2, 0, 20, inv_Z=1.0 / P, blocks=blocks, loss_trace=tr)
+        out[blocks] = (p, m, v, tr)
+    assert s.barrier_failures() == 0
+    # the camera loop's float64 traces are the same for every launch of it, and
+    # their last bits differ from the pair loop's, whose order of summation
+    # depends on its grid; parameters and moments are the chosen loop's
+    assert all(torch.equal(x, y) for x, y in zip(out[0][:3], out[-1 if cam else 128][:3]))
+    if N >= 100:
+        assert torch.equal(out[0][3], out[-1][3]) == cam
+    torch.testing.assert_close(out[0][3], out[-1][3], rtol=1e-9, atol=0)
+    torch.testing.assert_close(out[-1][1], out[128][1], rtol=0, atol=1e-5 * float(out[128][1].abs().max()))
