@@ -26,7 +26,7 @@ def hipcc() -> str:
 def flags() -> list[str]:
     return [
         f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall",
-        "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unused-result",
+        "-Wno-unused-result",
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
         f"-I{INCLUDE}", f"-I{CSRC}",
     ]

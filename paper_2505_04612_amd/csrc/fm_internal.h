@@ -374,16 +374,6 @@ __device__ inline RowListN<NE> row_list(const int32_t* __restrict__ cam_ptr, con
   return L;
 }
 
-// A row list with no entries (rows past the last camera).
-template <int NE = 4>
-__device__ inline RowListN<NE> empty_row_list() {
-  RowListN<NE> L;
-  L.lo = L.hi = 0;
-#pragma unroll
-  for (int j = 0; j < NE; ++j) L.it[j] = -1;
-  return L;
-}
-
 template <int CTRL>
 __device__ inline double dpp_mov_d(double v) {
   const long long bits = __double_as_longlong(v);

@@ -8,9 +8,9 @@
 // shrinks F toward a trivial zero of the algebraic loss):
 //     L = inv_Z * sum_n f_n^T W_n f_n / f_n^T f_n,  f_n = flatten(F_n).
 // Pair phase: E_n and the quadratic form in float64, dL/dE back through the
-// epipolar adjoint into the epipolar record layout, plus dL/dphi of both
-// cameras; camera phase: the epipolar loop's row sums and Gram-Schmidt
-// adjoint, and the sum of the focal records.
+// epipolar adjoint into a 24-float record (dL/dR and dL/dt of both cameras),
+// plus dL/dphi of both cameras; camera phase: the sums of the records, the
+// Gram-Schmidt adjoint, and the sum of the focal records.
 #include "fm_internal.h"
 
 #include <cmath>
@@ -18,7 +18,7 @@
 namespace {
 
 // One pair's normalised term q = f^T W f / f^T f (returned) and, scaled by
-// 2 iz, its adjoint: the epipolar record of both sides (rec [24]) and
+// 2 iz, its adjoint: the record of both sides (rec [24]) and
 // dL/dphi of both cameras.  A pair whose relative translation vanishes
 // contributes nothing (q, rec and the focal terms are 0).
 template <typename WT>

@@ -39,17 +39,13 @@ __device__ inline f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfm
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// What the backward reads of the weights, besides W2.
 struct MlpLds {
-  float W1[kHid * 3], b1[kHid], b2[kHid], W3[kHid], mean[3], rstd[3], b3;
+  float W3[kHid], mean[3], rstd[3], b3;
 };
 
 __device__ inline void load_lds(const MlpPtrs& w, MlpLds& s) {
-  for (int k = threadIdx.x; k < kHid * 3; k += blockDim.x) s.W1[k] = w.W1[k];
-  for (int k = threadIdx.x; k < kHid; k += blockDim.x) {
-    s.b1[k] = w.b1[k];
-    s.b2[k] = w.b2[k];
-    s.W3[k] = w.W3[k];
-  }
+  for (int k = threadIdx.x; k < kHid; k += blockDim.x) s.W3[k] = w.W3[k];
   if (threadIdx.x < 3) {
     s.mean[threadIdx.x] = w.mean[threadIdx.x];
     s.rstd[threadIdx.x] = 1.0f / w.std[threadIdx.x];

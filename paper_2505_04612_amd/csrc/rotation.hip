@@ -2,9 +2,8 @@
 // Rotation": eq. rotation-objective with the geodesic distance, the 6D
 // rotation parameterisation) on a scene's pair graph.
 //
-// The per-pair records use the epipolar loop's layout ([P, 24] floats: for
-// each side of the pair dL/dR as 3x3 row-major and three unused entries), so
-// the camera side shares its row sums and Gram-Schmidt adjoint.  Parameters
+// The per-pair records are [P, 24] floats: for each side of the pair dL/dR as
+// 3x3 row-major and three unused entries.  Parameters
 // are (a1, a2) per camera, [N, 6].
 #include <algorithm>
 
@@ -13,8 +12,6 @@
 #include <cmath>
 
 namespace {
-
-__device__ inline double pick3d(const double a[3], int k) { return k == 0 ? a[0] : (k == 1 ? a[1] : a[2]); }
 
 // One pair's geodesic term and its record, float64.  With Q = R^{i->j},
 // M = R_j^T Q R_i, c = (tr M - 1)/2 and d = arccos(c) (c clipped to
