@@ -23,12 +23,20 @@ def _ptr(t: torch.Tensor | None) -> int | None:
     return None if t is None else t.data_ptr()
 
 
+# torch's own accessors of the current stream's handle; None where a version of
+# torch does not have them
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     # torch.cuda.current_stream().cuda_stream without the Stream object and the
     # device lookup around it: 0.4 against 2.8 us, in every call of the library
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 def _require(t: torch.Tensor, dtype, shape, name: str, device) -> None:
