@@ -5,7 +5,7 @@
 // t^T A_n t / |Q_n|, A_n = B^T W_n B, B[:, k] = flatten([e_k]_x R_ij); the
 // winner keeps the sign of the pair's prior estimate.
 //
-// A workgroup takes one to kTsBatches batches of kTsPairs pairs.  Lanes of its
+// k_ts_search: a workgroup takes one to kTsBatches batches of kTsPairs pairs.  Lanes of its
 // first wavefront form A_n, one pair each, for all of them (a dependent chain
 // of about 750 instructions that the other wavefronts wait for, so it is paid
 // once per workgroup); every wavefront then holds a batch's form entries in
@@ -18,11 +18,10 @@
 // (value, then index, so the lowest candidate index wins among equal errors)
 // are combined by a reduce-scatter over the lanes and through LDS over the
 // wavefronts.  Bound by float64 VALU issue, 9 to 10 instructions per
-// evaluation.  The form before it gave one pair to each lane and read the
-// monomials from LDS, 48 bytes per evaluation, which bound it: per call with
-// 4,096 candidates, 4.8k pairs 23.0 -> 15.3 us (issued back to back, the host's
-// share of a call is 14 us), 29.5k pairs 75.5 -> 57.3, 186k pairs 372 -> 318,
-// identical outputs.
+// evaluation.  Per call with 4,096 candidates, against k_ts_search_few, which
+// reads the monomials from LDS: 4.8k pairs 15.6 us and 22.9 (issued back to back,
+// the host's share of a call is 11 to 14 us), 29.5k pairs 57.2 and 72.6, 187k
+// pairs 319 and 366.
 #include "fm_internal.h"
 
 #include <cmath>
@@ -234,6 +233,155 @@ __global__ __launch_bounds__(kTsBlock) void k_ts_search(const double* __restrict
   }
 }
 
+constexpr int kTsTile = 1024;   // candidates per LDS tile: six monomials each (48 KB of float64)
+
+// The same search with one lane per (pair, slice of the candidates): S lanes
+// share a pair and visit candidates slice, slice + S, ...; the candidates are
+// staged in LDS tiles and read as broadcasts, which bounds it (48 bytes per
+// evaluation); the S lanes combine their minima (value, then index) with a
+// butterfly, so the lowest candidate index wins among equal errors whatever S
+// is.  Every lane forms its own pair's A_n, so the forms' chain is paid once by
+// a whole launch: what few candidates on a large graph need (ts_few_shape).
+// The evaluations round as k_ts_search's, so the results are the same to the bit.
+__global__ __launch_bounds__(kTsBlock) void k_ts_search_few(const double* __restrict__ W36, const float* __restrict__ params,
+                                                      const int32_t* __restrict__ cams,
+                                                      const int64_t* __restrict__ offsets,
+                                                      const double* __restrict__ cand, int32_t C,
+                                                      const float* __restrict__ t_prior, int64_t P, int S,
+                                                      float* __restrict__ t_out, int32_t* __restrict__ best_out,
+                                                      double* __restrict__ err_out) {
+  __shared__ double tile[kTsTile * 6];
+  const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n = gtid / S;
+  const int slice = (int)(gtid % S);
+  const bool live = n < P;
+  double A6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  int64_t cnt = 0;
+  if (live) {
+    cnt = offsets[n + 1] - offsets[n];
+    double a1[3], a2[3], t[3], Ri[3][3], Rj[3][3], R[3][3];
+    load_pose(params, cams[2 * n], a1, a2, t);
+    gs_matrix(gs_forward(a1, a2), Ri);
+    load_pose(params, cams[2 * n + 1], a1, a2, t);
+    gs_matrix(gs_forward(a1, a2), Rj);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) R[a][b] = Rj[a][0] * Ri[b][0] + Rj[a][1] * Ri[b][1] + Rj[a][2] * Ri[b][2];
+    pair_form(W36 + 36 * n, R, A6);
+  }
+  double best_v = INFINITY;
+  int best_i = 0x7fffffff;
+  for (int base = 0; base < C; base += kTsTile) {
+    const int len = C - base < kTsTile ? C - base : kTsTile;
+    __syncthreads();
+    // each candidate's monomials (x^2, y^2, z^2, xy, xz, yz), once per tile
+    for (int k = threadIdx.x; k < len; k += blockDim.x) {
+      const double x = cand[3 * (int64_t)(base + k)], y = cand[3 * (int64_t)(base + k) + 1],
+                   z = cand[3 * (int64_t)(base + k) + 2];
+      double* m = tile + 6 * k;
+      m[0] = x * x;
+      m[1] = y * y;
+      m[2] = z * z;
+      m[3] = x * y;
+      m[4] = x * z;
+      m[5] = y * z;
+    }
+    __syncthreads();
+    if (live) {
+      // four of this lane's candidates per step: their forms are independent
+      // chains, evaluated as one expression each (the same rounding as one
+      // at a time) and compared in candidate order (the same ties)
+      int c = slice;
+      for (; c + 3 * S < len; c += 4 * S) {
+        double q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double* m = tile + 6 * (c + u * S);
+          q[u] = A6[0] * m[0] + A6[1] * m[1] + A6[2] * m[2] + A6[3] * m[3] + A6[4] * m[4] + A6[5] * m[5];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (q[u] < best_v) {
+            best_v = q[u];
+            best_i = base + c + u * S;
+          }
+      }
+      for (; c < len; c += S) {
+        const double* m = tile + 6 * c;
+        const double q = A6[0] * m[0] + A6[1] * m[1] + A6[2] * m[2] + A6[3] * m[3] + A6[4] * m[4] + A6[5] * m[5];
+        if (q < best_v) {
+          best_v = q;
+          best_i = base + c;
+        }
+      }
+    }
+  }
+  // combine the S lanes of a pair: lower value, then lower index
+  for (int sh = 1; sh < S; sh <<= 1) {
+    const double ov = __shfl_xor(best_v, sh);
+    const int oi = __shfl_xor(best_i, sh);
+    if (ov < best_v || (ov == best_v && oi < best_i)) {
+      best_v = ov;
+      best_i = oi;
+    }
+  }
+  if (!live || slice != 0) return;
+  double tp[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) tp[k] = (double)t_prior[3 * n + k];
+  if (cnt == 0 || best_i >= C) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t_out[3 * n + k] = (float)tp[k];
+    if (best_out) best_out[n] = -1;
+    if (err_out) err_out[n] = 0.0;
+    return;
+  }
+  double tb[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) tb[k] = cand[3 * (int64_t)best_i + k];
+  const double sgn = (tb[0] * tp[0] + tb[1] * tp[1] + tb[2] * tp[2]) < 0.0 ? -1.0 : 1.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) t_out[3 * n + k] = (float)(sgn * tb[k]);
+  if (best_out) best_out[n] = best_i;
+  if (err_out) err_out[n] = best_v / (double)cnt;
+}
+
+// Launch shape of one of the two kernels: workgroups, lanes per pair (few) or
+// batches per workgroup (many), and its estimated time.
+struct TsShape {
+  int64_t blocks;
+  int split;
+  double us;
+};
+
+// The estimates are the work of the fullest CU and what a call takes beside it,
+// fitted to 13 numbers of candidates from 1 to 6,000 on 11 graphs of 4.8k to
+// 187k pairs, within a tenth near the line.  us per call, few against many, with
+// 64, 1,000, 2,000 and 4,096 candidates: 15k pairs 11.7 / 11.7, 17.2 / 16.8, 25.7 /
+// 22.7, 44.1 / 33.5; 45k 12.0 / 23.9, 28.9 / 37.7, 51.7 / 55.8, 98.7 / 90.4; 99k
+// 13.1 / 45.4, 64.7 / 77.9, 122 / 116, 242 / 192; 187k 17.8 / 74.2, 98.4 / 129, 186 /
+// 192, 366 / 319; below 11k pairs many is never slower.
+
+// Lanes per pair: enough (pair, slice) lanes for about two wavefronts per SIMD,
+// at most 64.
+inline TsShape ts_few_shape(int64_t P, int32_t C, int num_cu) {
+  int S = 1;
+  while (S < 64 && P * S < (int64_t)num_cu * 4 * 2 * 64 && S < C) S <<= 1;
+  const int64_t blocks = (P * S + kTsBlock - 1) / kTsBlock, full = (blocks + num_cu - 1) / num_cu;
+  return TsShape{blocks, S, 8.0 + 0.0295 * (double)C * (double)full / S};
+}
+
+// One batch per workgroup until the launch has four workgroups per CU (the
+// co-resident limit by registers), then more, so that the forms' latency is
+// paid less often (186k pairs, 4,096 candidates: 337 us with one batch, 318
+// with eight).
+inline TsShape ts_many_shape(int64_t P, int32_t C, int num_cu) {
+  const int64_t fit = P / ((int64_t)kTsPairs * 4 * num_cu), b = fit < 1 ? 1 : (fit > kTsBatches ? kTsBatches : fit);
+  const int64_t blocks = (P + kTsPairs * b - 1) / (kTsPairs * b), full = b * ((blocks + num_cu - 1) / num_cu);
+  return TsShape{blocks, (int)b, 4.0 + (double)full * (0.75 + 6.5e-4 * (double)C)};
+}
+
 }  // namespace
 
 extern "C" fm_status fm_translation_search(fm_ctx* ctx, fm_scene* s, const double* W36, const float* params,
@@ -247,16 +395,14 @@ extern "C" fm_status fm_translation_search(fm_ctx* ctx, fm_scene* s, const doubl
   if (!W36 || !params || !cand || !t_prior || !t_out)
     return fm_fail(ctx, FM_EINVAL, "fm_translation_search: NULL argument");
   FM_HIP_TRY(ctx, hipSetDevice(ctx->device));
-  // one batch per workgroup until the launch has four workgroups per CU (the
-  // co-resident limit by registers), then more, so that the forms' latency is
-  // paid less often (186k pairs, 4,096 candidates: 337 us with one batch, 318
-  // with eight)
-  int64_t batches = s->P / ((int64_t)kTsPairs * 4 * ctx->num_cu);
-  batches = batches < 1 ? 1 : (batches > kTsBatches ? kTsBatches : batches);
   fm_timed timer(ctx, FM_K_TS_SEARCH, (hipStream_t)stream);
-  hipLaunchKernelGGL(k_ts_search, dim3(grid_for(s->P, (int)(kTsPairs * batches))), dim3(kTsBlock), 0,
-                     (hipStream_t)stream, W36, params, s->pair_cams, s->offsets, cand, C, t_prior, s->P, (int)batches,
-                     t_out, best, err_min);
+  const TsShape few = ts_few_shape(s->P, C, ctx->num_cu), many = ts_many_shape(s->P, C, ctx->num_cu);
+  if (few.us < many.us)
+    hipLaunchKernelGGL(k_ts_search_few, dim3((unsigned)few.blocks), dim3(kTsBlock), 0, (hipStream_t)stream, W36, params,
+                       s->pair_cams, s->offsets, cand, C, t_prior, s->P, few.split, t_out, best, err_min);
+  else
+    hipLaunchKernelGGL(k_ts_search, dim3((unsigned)many.blocks), dim3(kTsBlock), 0, (hipStream_t)stream, W36, params,
+                       s->pair_cams, s->offsets, cand, C, t_prior, s->P, many.split, t_out, best, err_min);
   FM_CHECK_LAUNCH(ctx);
   return FM_OK;
 }
