@@ -20,11 +20,18 @@ constexpr int kTaMaxRuns = 64;
 // The L1 term of eq. global-translation-objective for one pair, float64, from
 // s = o_j - o_i: u = s/|s|, |u - d|_1.  With `g` it also writes
 // dL/ds = (I - u u^T) sign(u - d) * invP / |s| (sign(0) = 0).  A pair whose
-// centres coincide has no direction: term and record are 0, by selection (a
-// branch would keep the chains of several runs from overlapping).
+// centres coincide has no direction: term and record are 0, by selection in the
+// mailbox loop, so that the chains of several runs overlap, else by a branch
+// (BRANCH), with fewer registers and instructions (forced pair loop, 20 cameras
+// and four runs 7.1 us per iteration against 7.6).
+template <bool BRANCH = false>
 __device__ inline double ta_term(const double s[3], const double d[3], double invP, double* g) {
   const double ns = sqrt(s[0] * s[0] + s[1] * s[1] + s[2] * s[2]);
   const bool ok = ns > 0.0;
+  if (BRANCH && !ok) {
+    if (g) g[0] = g[1] = g[2] = 0.0;
+    return 0.0;
+  }
   const double r = 1.0 / ns;
   double u[3], sg[3], term = 0.0, ug = 0.0;
 #pragma unroll
@@ -46,7 +53,7 @@ __device__ inline double ta_term_at(const float* __restrict__ oi, const float* _
   double s[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) s[k] = (double)oj[k] - (double)oi[k];
-  return ta_term(s, d, 0.0, nullptr);
+  return ta_term<true>(s, d, 0.0, nullptr);
 }
 
 // Runs are taken in groups of kTaGroup (the rest in a group of two and a
@@ -80,7 +87,7 @@ __device__ inline void ta_pair_group(const float* __restrict__ centres, int64_t 
     double sv[3], g[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) sv[k] = (double)oj[q][k] - (double)oi[q][k];
-    const double term = ta_term(sv, d, invP, g);
+    const double term = ta_term<true>(sv, d, invP, g);
     rec[(r0 + q) * P + n] = make_float4((float)g[0], (float)g[1], (float)g[2], (float)term);
   }
 }
@@ -395,7 +402,7 @@ __device__ inline TaEntry ta_entry(const TaCamArgs& a, int q) {
 template <int G>
 __device__ inline void ta_cam_group(const TaCamArgs& a, const float* __restrict__ pr, float* __restrict__ pw,
                                     int64_t c, int lo, int hi, int lane, int r0, double lr, double bc1, double bc2,
-                                    double* wl, bool cached, TaEntry e0) {
+                                    double* wl, bool cached, const TaEntry& e0) {
   const int64_t run_stride = (int64_t)a.N * 3;
   // this lane's own coordinate (lanes past 3G repeat the last one)
   const int l3 = lane < 3 * G ? lane : 3 * G - 1;
@@ -407,35 +414,40 @@ __device__ inline void ta_cam_group(const TaCamArgs& a, const float* __restrict_
   for (int j = 0; j < 12; ++j) acc[j] = 0.0;
 #pragma unroll
   for (int g = 0; g < G; ++g) ls[g] = 0.0;
-  for (int q = lo + lane; q < hi; q += 64) {
-    // (selected in registers: the entry chosen by a branch goes to scratch)
-    const bool held = cached && q == lo + lane;
-    TaEntry e{};
-    if (!held) e = ta_entry(a, q);
-    const int item = held ? e0.item : e.item, ci = held ? e0.ci : e.ci, cj = held ? e0.cj : e.cj;
-    const float dx = held ? e0.dx : e.dx, dy = held ? e0.dy : e.dy, dz = held ? e0.dz : e.dz;
-    const double d[3] = {(double)dx, (double)dy, (double)dz};
+  auto add = [&](const TaEntry& e) {
+    const double d[3] = {(double)e.dx, (double)e.dy, (double)e.dz};
     float oi[G][3], oj[G][3];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        oi[g][k] = pr[(r0 + g) * run_stride + 3 * (int64_t)ci + k];
-        oj[g][k] = pr[(r0 + g) * run_stride + 3 * (int64_t)cj + k];
+        oi[g][k] = pr[(r0 + g) * run_stride + 3 * (int64_t)e.ci + k];
+        oj[g][k] = pr[(r0 + g) * run_stride + 3 * (int64_t)e.cj + k];
       }
-    const double sgn = (item & 1) ? 1.0 : -1.0;
-    const double first = (item & 1) ? 0.0 : 1.0;
+    const double sgn = (e.item & 1) ? 1.0 : -1.0;
+    const double first = (e.item & 1) ? 0.0 : 1.0;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       double sv[3], gr[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) sv[k] = (double)oj[g][k] - (double)oi[g][k];
-      const double term = ta_term(sv, d, a.invP, gr);
+      const double term = ta_term<true>(sv, d, a.invP, gr);
 #pragma unroll
       for (int k = 0; k < 3; ++k) acc[3 * g + k] += sgn * (double)(float)gr[k];
       ls[g] += first * (double)(float)term;
     }
+  };
+  // the held entry apart: chosen inside the loop it costs a selection of six
+  // values, or goes to scratch.  us per iteration with this and ta_term's branch,
+  // against both selected (and both branched on in the loop): 200 cameras of 50
+  // pairs, 32 runs 19.7 and 22.0 (21.5); 1,000, 64 runs 36.8 and 44.9 (43.3); 3,000
+  // of 40, 4 runs 11.3 and 11.3 (11.8); 300 of 223, one run 6.55 and 6.35 (7.45)
+  int q = lo + lane;
+  if (cached) {
+    if (q < hi) add(e0);
+    q += 64;
   }
+  for (; q < hi; q += 64) add(ta_entry(a, q));
   wave_sum12(acc, lane);
   double gl = acc[0];
 #pragma unroll
@@ -467,9 +479,7 @@ __global__ __launch_bounds__(kSolveBlock) void k_ta_solve_cam(TaCamArgs a) {
   const int64_t RS = (int64_t)a.runs * a.part_stride;
   double* wl = a.trace ? wloss[wv] : nullptr;
   // static data of the first 64 incidence entries of this wavefront's first
-  // camera (one per lane) and its slot range, read once for the launch (100
-  // iterations of four runs at 200 cameras: 480 us with this and ta_term's
-  // selection, 497 before)
+  // camera (one per lane) and its slot range, read once for the launch
   TaEntry e0{};
   int lo0 = 0, hi0 = 0;
   if (gwave < a.N) {
@@ -711,8 +721,8 @@ __global__ __launch_bounds__(kCamBlock) void k_ta_solve_mail(TaMailArgs a) {
   }
 }
 
-// Whether the mailbox loop runs: every camera has a wavefront of its own, one to
-// a SIMD, and the cameras have at most 192 pairs on average.  Past that the
+// Whether the mailbox loop can run: every camera has a wavefront of its own, one
+// to a SIMD, and the cameras have at most 192 pairs on average.  Past that the
 // passes of 64 pairs, each waiting for requests that the caches do not serve,
 // cost more than the barrier: us per iteration, mailbox against barrier, for
 // four runs (one run) at 1,000 cameras of 20 pairs 3.4 against 7.8, of 78
@@ -720,6 +730,28 @@ __global__ __launch_bounds__(kCamBlock) void k_ta_solve_mail(TaMailArgs a) {
 // cameras of 298 9.6 against 9.0, at 800 of 350 15.2 against 12.8 (8.2, 8.3).
 inline bool ta_mail_fits(const fm_scene* s, int num_cu) {
   return s->N <= num_cu * (kCamBlock / 64) && s->P <= 96 * (int64_t)s->N;
+}
+
+// Whether it does.  Every group of four runs waits for its own words, where the
+// barrier loop waits once for all of them, so past a number of groups the barrier
+// is cheaper: it costs more the more cameras there are, and a group costs more
+// the more passes a camera takes.  us per iteration, mailbox against barrier, with
+// 4, 8 and 16 runs: 200 cameras of 48 pairs 3.8 / 5.0, 6.5 / 7.1, 11.5 / 11.3; of
+// 80 5.3 / 6.1, 9.6 / 9.1, 17.6 / 15.3; 500 of 51 3.9 / 6.2, 6.6 / 8.2, 11.6 /
+// 12.0; 1,000 of 51 4.5 / 8.5, 7.1 / 10.5, 12.4 / 14.3; of 88 6.9 / 9.6, 10.9 / 12.6,
+// 19.1 / 18.6; of 172 9.8 / 10.6, 18.5 / 14.8, 34 / 23.  Below 128 cameras the
+// barrier is cheap: 50 of 11 pairs 5.0 / 5.0, 8.8 / 7.6, of 38 3.8 / 4.9, 6.5 / 7.0.
+// Cameras of 4 pairs or so make the barrier's groups dear (200 cameras, 16 runs
+// 12.2 / 21.2).  A traced launch is faster by mailbox at any number of runs (the
+// barrier loop adds up each iteration's partials in one thread: 1.2 to 20 times).
+inline bool ta_mail_wins(const fm_scene* s, int runs, bool trace) {
+  if (trace) return true;
+  const int64_t groups = (runs + 3) / 4, N = s->N, ends = 2 * s->P, passes = (ends + 64 * N - 1) / (64 * N);
+  if (passes > 2) return groups <= 1;
+  if (passes == 2) return groups <= 1 + N / 450;
+  if (N >= 8 && ends <= 5 * N) return groups <= 6;
+  if (N < 128) return groups <= (ends >= 22 * N ? 2 : 1);
+  return groups <= 2 + N / 300;
 }
 
 // ------------------------------------------------------------------ merge of runs
@@ -978,7 +1010,7 @@ extern "C" fm_status fm_translation_solve(fm_ctx* ctx, fm_scene* s, const float*
   a.b1 = cfg->beta1; a.b2 = cfg->beta2; a.eps = cfg->eps;
   a.lr_step0 = cfg->lr_step0; a.lr_total = cfg->lr_total_steps; a.adam_step0 = cfg->adam_step0;
   void* args[] = {&a};
-  if (cfg->blocks <= 0 && ta_mail_fits(s, ctx->num_cu)) {
+  if (cfg->blocks <= 0 && ta_mail_fits(s, ctx->num_cu) && ta_mail_wins(s, runs, loss_trace != nullptr)) {
     TaMailArgs ma;
     ma.centres = centres; ma.m = m; ma.v = v;
     ma.cams = s->pair_cams; ma.dirs = dirs; ma.cam_ptr = s->cam_ptr; ma.cam_items = s->cam_items;
@@ -989,7 +1021,9 @@ extern "C" fm_status fm_translation_solve(fm_ctx* ctx, fm_scene* s, const float*
     ma.lr_step0 = a.lr_step0; ma.lr_total = a.lr_total; ma.adam_step0 = a.adam_step0;
     void* margs[] = {&ma};
     FM_HIP_TRY(ctx, fm_mail_reset(s->bar, s->ta_mail, 2 * (int64_t)s->N * ma.stride, st));
-    // two wavefronts a workgroup while these fit one to a CU
+    // two wavefronts a workgroup while these fit one to a CU (100 iterations of
+    // four runs, two against four: 200 cameras 341 us against 371, 500 353 and
+    // 380; past that four: 700 cameras 376 against 417)
     const int threads = ((int64_t)s->N + 1) / 2 <= ctx->num_cu ? kCamBlock / 2 : kCamBlock;
     fm_timed timer(ctx, FM_K_TA_SOLVE, st);
     hipError_t e = hipLaunchCooperativeKernel((const void*)k_ta_solve_mail, dim3(grid_for((int64_t)s->N * 64, threads)),
