@@ -191,10 +191,13 @@ __device__ inline void stream_rows(const void* __restrict__ uv, int64_t start, i
   const int ti = nfull * STRIDE + lid;
   const bool tok = ti < count;
   if (one_tail) traw = load_raw<DT>(tok ? p + nfull * STRIDE : base);
-  if constexpr (BATCH > 4) {
+  if constexpr (BATCH > 4 && STRIDE == kLanes && WMODE == W_IRLS && BUILD) {
     // whole batches without row tests, then one partial batch (171M matches in
     // the pass's 4,096-match items: 362 us a call against 367 with every row
-    // tested and unrolled over the item, in twice the code)
+    // tested and unrolled over the item, in twice the code).  Only where the
+    // residual and the Gram are both formed: the other forms and the four-pair
+    // groups are shorter per row and lose by the loop (Grams of given weights,
+    // 5,000 cameras of 700 matches a pair, 270 us a call against 248)
     const RawT* __restrict__ q = p;
     int64_t mq = m0;
     int left = nfull;
