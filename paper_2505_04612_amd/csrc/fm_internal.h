@@ -134,6 +134,7 @@ struct fm_scene {
   int32_t* cam_ptr = nullptr;     // [N+1] incidence list offsets
   int32_t* cam_items = nullptr;   // [2P] 2*pair + side (0: camera is i_n, 1: j_n), pair order
   int32_t* pair_slot = nullptr;   // [2P] position of item 2*pair + side in cam_items
+  int32_t max_pairs = 0;          // the most pairs of any camera
   // workspace
   float* partials = nullptr;      // [n_big, 36]
   double* ess = nullptr;          // [P, 12] essential matrices (reweight: rows of 9) or relative poses (features: rows of 12)
@@ -670,12 +671,13 @@ __device__ inline float adam_update(float p, float g, float& m, float& v, double
 // (the rotation and focal loops, whose pair terms are cheaper, always do):
 // one wavefront per camera evaluates each of its pairs, so every pair is
 // evaluated twice, but an iteration has no grid barrier and no record round
-// trip.  What it costs is the chain of a wavefront's cameras (one per wavefront
-// up to 4 num_cu of them) and of each camera's passes of 64 pairs: about 1 us a
-// camera and 2.4 a pass; the pair loop costs about 11.2 us and 45 us per million
-// pairs, more on dense graphs.  Measured with float32 Grams, us per iteration
-// (camera vs the better of three pair grids), banded and street graphs of
-// cameras / pairs:
+// trip.  What it costs is the longest chain of a wavefront's cameras (one per
+// wavefront up to 4 num_cu of them) and of each camera's passes of 64 pairs, the
+// camera with the most pairs among them: about 1 us a camera and 2.4 a pass; the
+// pair loop costs about 11.2 us, 45 us per million pairs, and 16 us per thousand
+// pairs of that camera (past its first 128 or so).  Measured with float32 Grams,
+// us per iteration (camera vs the better of three pair grids), banded and street
+// graphs of cameras / pairs:
 //   one camera a wavefront: 200 / 4.8k 3.2 vs 8.5; 1,000 / 25k 4.4 vs 12.8;
 //     600 / 65k 9.9 vs 16.3; 400 / 60k 13.7 vs 19.0; 1,000 / 130k 13.8 vs 21.5
 //   two: 2,000 / 39k 7.0 vs 12.7; 1,100 / 38k 12.0 vs 12.8; 2,000 / 95k 10.8 vs
@@ -687,15 +689,17 @@ __device__ inline float adam_update(float p, float g, float& m, float& v, double
 //     14.5; 4,096 / 122k 15.4 vs 17.2
 //   five and more: 5,000 / 15k 16.9 vs 13.3; 5,000 / 59k 17.5 vs 14.3; 8,000 / 64k
 //     27.0 vs 16.6; 20,000 / 80k 70.0 vs 24.2; 40,000 / 40k 135 vs 33
+//   a ring and one camera of 250, 500 and 999 pairs at 1,000 cameras 9.8 vs 12.8,
+//     17.5 vs 15.7, 35 vs 25; of 2,499 at 2,500 92 vs 50
 // Past kCamLoopMaxPairs the pair loop always runs.
 constexpr int64_t kCamLoopMaxPairs = 131072;
 
-inline bool cam_loop_wins(int64_t N, int64_t P, int num_cu) {
+inline bool cam_loop_wins(int64_t N, int64_t P, int64_t max_pairs, int num_cu) {
   if (P >= kCamLoopMaxPairs) return false;
   const int64_t waves = (int64_t)num_cu * (kCamBlock / 64), cams = (N + waves - 1) / waves;
-  if (cams <= 1) return true;
-  const int64_t passes = std::max<int64_t>(1, (2 * P + 64 * N - 1) / (64 * N));
-  return (double)cams * (1.0 + 2.4 * (double)passes) < 11.2 + 45e-6 * (double)P;
+  auto camera = [](int64_t pairs) { return 1.0 + 2.4 * (double)std::max<int64_t>(1, (pairs + 63) / 64); };
+  const double cam_us = camera(max_pairs) + (double)(cams - 1) * camera(N > 0 ? (2 * P + N - 1) / N : 0);
+  return cam_us < 11.2 + 45e-6 * (double)P + 0.0165 * (double)std::max<int64_t>(0, max_pairs - 128);
 }
 
 // Workgroup count from which the fused pair loop synchronises with the

@@ -182,29 +182,29 @@ __device__ inline double pair_phase_slots(const float* params, const double* rot
 constexpr int kRowItems = 6;
 
 // Summed records of one camera in every lane of its row, from the
-// camera-major layout (slots lo..hi-1, 6 numbers each): lane l16 takes slots
-// lo + l16 + 16 j; the first NE of them are all loaded before any is added
+// camera-major layout (slots lo..hi-1, 6 numbers each; a row is LANES lanes):
+// lane l takes slots lo + l + LANES j; the first NE of them are all loaded before any is added
 // (without lane conditions, under which each load is waited for on its own:
 // slots past the end load the last one's record, or a camera without pairs
 // its predecessor's, and count as 0), then added in slot order, then the rest.
 // The pair loop on the 5,000-camera street graph (74 pairs per camera) takes
 // 0.5 us less per iteration than with conditional loads.  acc = (om, dL/dt) of the camera.
-template <int NE, typename V>
+template <int NE, typename V, int LANES = 16>
 __device__ inline void row_camera_sums_slots(int lo, int hi, const float* __restrict__ contrib, int lane,
                                              double (&acc)[6]) {
   const V* c = reinterpret_cast<const V*>(contrib);
-  const int l16 = lane & 15;
+  const int l = lane & (LANES - 1);
   const int last = max(hi - 1, 0);
   V r[NE][3];
 #pragma unroll
   for (int j = 0; j < NE; ++j) {
-    const int q = min(lo + l16 + 16 * j, last);
+    const int q = min(lo + l + LANES * j, last);
 #pragma unroll
     for (int k = 0; k < 3; ++k) r[j][k] = c[(int64_t)q * 3 + k];
   }
 #pragma unroll
   for (int j = 0; j < NE; ++j) {
-    const bool live = lo + l16 + 16 * j < hi;
+    const bool live = lo + l + LANES * j < hi;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       r[j][k].x = live ? r[j][k].x : 0;
@@ -218,12 +218,20 @@ __device__ inline void row_camera_sums_slots(int lo, int hi, const float* __rest
     acc[0] += r[j][0].x; acc[1] += r[j][0].y; acc[2] += r[j][1].x;
     acc[3] += r[j][1].y; acc[4] += r[j][2].x; acc[5] += r[j][2].y;
   }
-  for (int q = lo + 16 * NE + l16; q < hi; q += 16) {
+  for (int q = lo + LANES * NE + l; q < hi; q += LANES) {
     const V a0 = c[(int64_t)q * 3], a1 = c[(int64_t)q * 3 + 1], a2 = c[(int64_t)q * 3 + 2];
     acc[0] += a0.x; acc[1] += a0.y; acc[2] += a1.x;
     acc[3] += a1.y; acc[4] += a2.x; acc[5] += a2.y;
   }
-  row_sum6(acc, lane);
+  if constexpr (LANES == 16) {
+    row_sum6(acc, lane);
+  } else {
+    double v = row_partial6(acc, lane);
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[k] = __shfl(v, 8 * (k / 3) + 2 * (k % 3));
+  }
 }
 
 // ------------------------------------------------------------------ standalone loss + gradient
@@ -249,9 +257,12 @@ __global__ __launch_bounds__(kBlock) void k_pair_phase(const float* __restrict__
   if (threadIdx.x == 0) loss_part[blockIdx.x] = t;
 }
 
-// One 16-lane row per camera: its records summed in a fixed order, the
-// Gram-Schmidt adjoint (the same lanes for four cameras: their float64 chains
-// are what the kernel issues).  The last workgroup, one more than the cameras
+// One row of LANES lanes per camera: its records summed in a fixed order, the
+// Gram-Schmidt adjoint (rows of 16: the same lanes for four cameras, whose
+// float64 chains are what the kernel issues; of 64 where a camera has more than
+// kWideCamera pairs, which 16 lanes take too long to add: 2,500 cameras, one of
+// 2,499 pairs, 42.6 us a call by rows of 16, 26.6 by wavefronts when the choice
+// was made).  The last workgroup, one more than the cameras
 // take, sums the loss partials instead.  The records are float64: rounded to
 // float32, the gradient was on average 3.5e-8 from 64 bits (relative, 24 graphs
 // of 20 to 3,000 cameras; 2.5e-8 now, the rounding of the result), further
@@ -260,6 +271,9 @@ __global__ __launch_bounds__(kBlock) void k_pair_phase(const float* __restrict__
 // added by one thread, a wavefront per camera and 24-float records; at 1,000
 // cameras 11.8 against 23.5, 12 against 14 to 15 up to 200 cameras, where the
 // launches bound them.
+constexpr int kWideCamera = 1024;
+
+template <int LANES>
 __global__ __launch_bounds__(kLanes) void k_camera_grad(const float* __restrict__ params,
                                                         const int32_t* __restrict__ cam_ptr,
                                                         const float* __restrict__ contrib, int32_t N,
@@ -276,16 +290,16 @@ __global__ __launch_bounds__(kLanes) void k_camera_grad(const float* __restrict_
     if (threadIdx.x == 0) *loss = v * (Z_dev ? 1.0 / (double)(*Z_dev > 0 ? *Z_dev : 1) : inv_Z);
     return;
   }
-  const int lane = threadIdx.x & 63, l16 = lane & 15;
-  const int64_t c = ((int64_t)blockIdx.x * kLanes + threadIdx.x) >> 4;
+  const int lane = threadIdx.x & 63, l = lane & (LANES - 1);
+  const int64_t c = ((int64_t)blockIdx.x * kLanes + threadIdx.x) / LANES;
   if (c >= N) return;   // whole rows leave together: the row exchanges stay within live rows
   double a1[3], a2[3], t[3], acc6[6], acc[12], g[9];
   load_pose(params, (int)c, a1, a2, t);
   const Gs f = gs_forward(a1, a2);
-  row_camera_sums_slots<kRowItems, double2>(cam_ptr[c], cam_ptr[c + 1], contrib, lane, acc6);
+  row_camera_sums_slots<kRowItems, double2, LANES>(cam_ptr[c], cam_ptr[c + 1], contrib, lane, acc6);
   omega_grad(f, acc6, acc6 + 3, acc);
   gs_adjoint(acc, f, a2, g);
-  if (l16 < 9) grad[c * 9 + l16] = (float)pick9(g, l16);
+  if (l < 9) grad[c * 9 + l] = (float)pick9(g, l);
 }
 
 static fm_status check_w(fm_ctx* ctx, const char* fn, const void* W36, fm_dtype wdt, int64_t P) {
@@ -317,10 +331,12 @@ extern "C" fm_status fm_epipolar_loss_grad(fm_ctx* ctx, fm_scene* s, const void*
                        s->pair_slot, (const float*)W36, s->P, inv_Z, Z_dev, s->contrib, s->loss_part);
   }
   FM_CHECK_LAUNCH(ctx);
-  const unsigned cam_blocks = grad ? grid_for((int64_t)s->N * 16, kLanes) : 0u, gc = cam_blocks + (loss ? 1u : 0u);
+  const bool wide = s->max_pairs > kWideCamera;
+  const unsigned cam_blocks = grad ? grid_for((int64_t)s->N * (wide ? 64 : 16), kLanes) : 0u,
+                 gc = cam_blocks + (loss ? 1u : 0u);
   if (gc > 0) {
   fm_timed timer(ctx, FM_K_CAMERA, st);
-  hipLaunchKernelGGL(k_camera_grad, dim3(gc), dim3(kLanes), 0, st, params, s->cam_ptr, s->contrib, s->N,
+  hipLaunchKernelGGL(wide ? k_camera_grad<64> : k_camera_grad<16>, dim3(gc), dim3(kLanes), 0, st, params, s->cam_ptr, s->contrib, s->N,
                      s->loss_part, (int64_t)gp, inv_Z, Z_dev, grad, loss, cam_blocks);
   }
   FM_CHECK_LAUNCH(ctx);
@@ -867,7 +883,7 @@ extern "C" fm_status fm_epipolar_solve(fm_ctx* ctx, fm_scene* s, const void* W36
   int64_t want_cam = grid_for((int64_t)s->N * 64, cam_threads);
   if (want_cam > s->coop_blocks_cam) want_cam = s->coop_blocks_cam;
   if (want_cam > ctx->num_cu) want_cam = ctx->num_cu;
-  if ((cfg->blocks < 0 || (cfg->blocks == 0 && cam_loop_wins(s->N, s->P, ctx->num_cu))) &&
+  if ((cfg->blocks < 0 || (cfg->blocks == 0 && cam_loop_wins(s->N, s->P, s->max_pairs, ctx->num_cu))) &&
       2 * kTraceBatch * want_cam * (cam_threads / 64) <= s->loss_part_cap &&
       (int64_t)s->N * kMailWords * (int64_t)sizeof(MailWord) <= INT32_MAX) {
     CamSolveArgs ca;

@@ -277,10 +277,13 @@ __global__ void k_pair_slots(const int32_t* cam_items, int64_t total, int32_t* p
   if (q < total) pair_slot[cam_items[q]] = (int32_t)q;
 }
 
-__global__ void k_slot_camera(const int32_t* cam_ptr, int32_t N, int32_t* cam_of_slot) {
+// The camera of each incidence slot, and the most slots any camera has.
+__global__ void k_slot_camera(const int32_t* cam_ptr, int32_t N, int32_t* cam_of_slot, int32_t* most) {
   int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < N)
+  if (c < N) {
     for (int q = cam_ptr[c]; q < cam_ptr[c + 1]; ++q) cam_of_slot[q] = c;
+    atomicMax(most, cam_ptr[c + 1] - cam_ptr[c]);
+  }
 }
 
 // ------------------------------------------------------------------ scene
@@ -435,7 +438,7 @@ extern "C" fm_status fm_scene_create(fm_ctx* ctx, int64_t P, int64_t M, int32_t 
   SCENE_TRY(hipMalloc(&s->cam_items, sizeof(int32_t) * (2 * P + 1)));
   SCENE_TRY(hipMalloc(&s->pair_slot, sizeof(int32_t) * (2 * P + 1)));
   SCENE_TRY(hipMalloc(&tmp_i32, sizeof(int32_t) * (N + 1 + 4 * P + 2)));
-  int32_t* cursor = tmp_i32;                 // [N+1]
+  int32_t* cursor = tmp_i32;                 // [N], then the most pairs of a camera
   int32_t* unsorted = tmp_i32 + N + 1;       // [2P+1]
   int32_t* slot_cam = unsorted + 2 * P + 1;  // [2P+1]
   SCENE_TRY(hipMemsetAsync(s->cam_ptr, 0, sizeof(int32_t) * (N + 1), st));
@@ -448,8 +451,10 @@ extern "C" fm_status fm_scene_create(fm_ctx* ctx, int64_t P, int64_t M, int32_t 
     hipLaunchKernelGGL(k_cam_scatter, dim3(grid_for(P, kBlock)), dim3(kBlock), 0, st, cams, P, s->cam_ptr,
                        cursor, unsorted);
     SCENE_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_slot_camera, dim3(grid_for(N, kBlock)), dim3(kBlock), 0, st, s->cam_ptr, N, slot_cam);
+    hipLaunchKernelGGL(k_slot_camera, dim3(grid_for(N, kBlock)), dim3(kBlock), 0, st, s->cam_ptr, N, slot_cam,
+                       cursor + N);
     SCENE_TRY(hipGetLastError());
+    SCENE_TRY(hipMemcpyAsync(&s->max_pairs, cursor + N, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     hipLaunchKernelGGL(k_cam_sort, dim3(grid_for(2 * P, kBlock)), dim3(kBlock), 0, st, s->cam_ptr, slot_cam,
                        unsorted, 2 * P, s->cam_items);
     SCENE_TRY(hipGetLastError());

@@ -739,18 +739,24 @@ inline bool ta_mail_fits(const fm_scene* s, int num_cu) {
 // 4, 8 and 16 runs: 200 cameras of 48 pairs 3.8 / 5.0, 6.5 / 7.1, 11.5 / 11.3; of
 // 80 5.3 / 6.1, 9.6 / 9.1, 17.6 / 15.3; 500 of 51 3.9 / 6.2, 6.6 / 8.2, 11.6 /
 // 12.0; 1,000 of 51 4.5 / 8.5, 7.1 / 10.5, 12.4 / 14.3; of 88 6.9 / 9.6, 10.9 / 12.6,
-// 19.1 / 18.6; of 172 9.8 / 10.6, 18.5 / 14.8, 34 / 23.  Below 128 cameras the
-// barrier is cheap: 50 of 11 pairs 5.0 / 5.0, 8.8 / 7.6, of 38 3.8 / 4.9, 6.5 / 7.0.
-// Cameras of 4 pairs or so make the barrier's groups dear (200 cameras, 16 runs
-// 12.2 / 21.2).  A traced launch is faster by mailbox at any number of runs (the
-// barrier loop adds up each iteration's partials in one thread: 1.2 to 20 times).
+// 19.1 / 18.6; of 172 9.8 / 10.6, 18.5 / 14.8, 34 / 23.  Below 120 cameras the
+// barrier is cheap: 50 of 11 pairs 5.0 / 5.0, 8.8 / 7.6, of 38 3.8 / 4.9, 6.5 /
+// 7.0 (measured, without a reason found, the mailboxes gain all the same with two
+// passes, 127 of 74 pairs 5.4 / 7.8, 9.7 / 13.2, 17.7 / 23.9, and with cameras of
+// 4 pairs or so, 200 cameras 12.2 / 21.2 with 16 runs).  Passes are those of the
+// camera with the most pairs: a ring of 1,000 cameras and one of 500 pairs 9.8 /
+// 12.3 with one run, 16.4 / 16.0 with four, one of 999 17.4 / 17.4 and 34 / 27.
+// A traced launch is faster by mailbox at any number of runs (the barrier loop
+// adds up each iteration's partials in one thread: 1.2 to 20 times).
 inline bool ta_mail_wins(const fm_scene* s, int runs, bool trace) {
   if (trace) return true;
-  const int64_t groups = (runs + 3) / 4, N = s->N, ends = 2 * s->P, passes = (ends + 64 * N - 1) / (64 * N);
+  const int64_t groups = (runs + 3) / 4, N = s->N, ends = 2 * s->P, passes = (s->max_pairs + 63) / 64;
+  if (passes > 8) return false;
+  if (passes > 4) return runs <= 2;
   if (passes > 2) return groups <= 1;
-  if (passes == 2) return groups <= 1 + N / 450;
-  if (N >= 8 && ends <= 5 * N) return groups <= 6;
-  if (N < 128) return groups <= (ends >= 22 * N ? 2 : 1);
+  if (passes == 2) return groups <= (N < 160 ? 2 : 1 + N / 450);
+  if (N >= 8 && ends <= 7 * N) return groups <= 6;
+  if (N < 120) return groups <= (ends >= 22 * N ? 2 : 1);
   return groups <= 2 + N / 300;
 }
 
