@@ -423,16 +423,19 @@ fm_status fm_rotation_solve(fm_ctx* ctx, fm_scene* scene, const float* Rrel, flo
  * c1 x c2 by the 6D map).  Each eigenvector comes from at most `steps`
  * Lanczos steps (at most 3N and 4096) with full reorthogonalisation, both in
  * one persistent cooperative launch of `blocks` workgroups of 512 threads
- * (0 = automatic; at most one per camera and the co-resident limit, at least
- * one per 1,024 cameras), started from start[col] ([2, 3N] float64, device; the
+ * (0 = automatic; a count is raised to one per 256 cameras and lowered to one
+ * per camera and to the co-resident limit), started from start[col] ([2, 3N] float64, device; the
  * caller's random vectors), and the smallest eigenpair of the Lanczos
  * tridiagonal matrix; the steps end early once the Ritz pair's residual
  * bound |beta_k s_k| is below 1e-11 of |T| (checked every 10 steps).  info [4] double (device, NULL = not written): smallest eigenvalue
  * and steps taken, first then second problem.  The pair graph must be
  * connected (a camera in no pair makes the first problem's minimiser
  * meaningless); an empty graph returns FM_ESHAPE.  Uses a per-scene
- * workspace of at most (steps + 5) x 3N doubles and some (steps + 20) per
- * workgroup, grown on demand (the growing call synchronises the device). */
+ * workspace of at most steps x 3N doubles of basis rows, 3N and some
+ * (steps + 25) per workgroup of exchanged values (twice that up to 64
+ * workgroups) and, where a workgroup's vectors do not fit its LDS (over 1,024
+ * steps or 1,024 cameras a workgroup), 9N and 5 steps per workgroup more;
+ * grown on demand (the growing call synchronises the device). */
 fm_status fm_rotation_init(fm_ctx* ctx, fm_scene* scene, const float* Rrel, const double* start,
                            int32_t steps, int32_t blocks, float* params, double* info, fm_stream stream);
 
