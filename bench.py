@@ -269,15 +269,15 @@ def bench_translation(ctx, s, sc, runs: int = 4, iters: int = 1000, final_iters:
         n_it += 1
     P = sc.num_pairs
     return {
-        "kernel": "k_ta_solve_cam (persistent, one wavefront per camera: each pair's L1 term + adjoint from "
-                  "both cameras, Adam, 1 grid barrier)",
+        "kernel": "k_ta_solve_mail (persistent, one wavefront per camera: each pair's L1 term + adjoint from "
+                  "both cameras, Adam; the neighbours' centres by mailbox)",
         "pairs": P, "cameras": sc.num_cams, "runs": runs, "iters": iters, "final_iters": final_iters,
         "run_iters_per_s": runs * iters / (ms_runs / 1e3),
         "us_per_iter_all_runs": ms_runs * 1e3 / iters,
         "us_per_iter_one_run": ms_final * 1e3 / final_iters,
         "stage_wall_ms": wall * 1e3,
-        "bound": "latency (one grid barrier per iteration; each pair read from both cameras: "
-                 "2 x %d B per pair and run through L2)" % (8 + 12 + 24),
+        "bound": "latency (one exchange between neighbours per iteration; each pair evaluated from both "
+                 "cameras: 2 x %d B of mailbox words per pair and run)" % 24,
         "centre_err_vs_truth": {"median": float(np.median(err)), "max": float(err.max()),
                                 "single_run_max": run_err},
         "inputs": "unit relative translations from the true poses, 2 deg noise, 10 % outlier pairs; "
@@ -450,8 +450,8 @@ def bench_mlp(ctx, M: int, reps: int = 20) -> dict:
     t_bwd = timed(lambda: api.mlp_backward(ctx, w, feats, act, dout, g))
     fl = 2.0 * 64 * 64
     return {
-        "kernels": "k_mlp_forward (64x64 layer on v_mfma_f32_16x16x32_f16, 64->1 layer on v_mfma_f32_16x16x16_f16), "
-                   "k_mlp_backward (dh1 on "
+        "kernels": "k_mlp_forward (3->64 layer on v_mfma_f32_16x16x4_f32, 64x64 and 64->1 layers on "
+                   "v_mfma_f32_16x16x32_f16), k_mlp_backward (dh1 on "
                    "v_mfma_f32_16x16x32_f16, dW2 on v_mfma_f32_16x16x16_f16) + k_mlp_reduce",
         "matches": M,
         "forward_us": t_fwd * 1e6, "forward_matches_per_s": M / t_fwd,
@@ -516,7 +516,7 @@ def bench_search(ctx, s, sc, C: int = 4096, reps: int = 20, cpu_pairs: int = 200
     gs.grid_search(full, np.diff(sc.offsets)[:cpu_pairs], Rij, cand_np, t_true[:cpu_pairs])
     t_cpu = time.perf_counter() - t0
     return {
-        "kernel": "k_ts_search (per-pair 3x3 form from the Gram, candidates in LDS, argmin over lane slices)",
+        "kernel": "k_ts_search (per-pair 3x3 forms from the Gram in scalar registers, lanes over the candidates)",
         "pairs": P, "candidates": C, "us_per_launch": per * 1e6, "evals_per_s": evals,
         "roofline": {"bound": "alu", "achieved": flops / 1e12, "peak": FP64_PEAK_T, "unit": "TFLOP/s",
                      "frac": flops / 1e12 / FP64_PEAK_T, "flops_per_eval": 11},
@@ -579,13 +579,13 @@ def bench_rotation(ctx, s, sc, steps: int = 300, iters: int = 500, cpu_budget: f
         t_it += time.perf_counter() - t
         n_it += 1
     return {
-        "kernels": "k_ra_lanczos (2 persistent launches, one per column) + k_ra_solve_cam (persistent, one "
+        "kernels": "k_ra_lanczos (1 persistent launch for both columns) + k_ra_solve_cam (persistent, one "
                    "wavefront per camera: geodesic loss + adjoint of each pair from both cameras, Adam)",
         "pairs": P, "cameras": sc.num_cams, "lanczos_steps": [int(lz[1]), int(lz[3])], "iters": iters,
         "init_ms": init_ms, "us_per_lanczos_step": init_ms * 1e3 / max(lz[1] + lz[3], 1),
         "iters_per_s": iters / (solve_ms / 1e3), "us_per_iter": solve_ms * 1e3 / iters,
         "stage_wall_ms": wall * 1e3,
-        "bound": "latency (Lanczos: 6 grid barriers per step; solve: 1 per iteration)",
+        "bound": "latency (Lanczos: 2 exchanges between workgroups per step; solve: 1 grid barrier per iteration)",
         "rel_rot_err_vs_truth_deg": {"init_median": float(np.median(e_init)), "init_max": float(e_init.max()),
                                      "final_median": float(np.median(e_fin)), "final_max": float(e_fin.max())},
         "inputs": "relative rotations from the true poses, 2 deg noise, 10 % random-rotation outlier pairs",
