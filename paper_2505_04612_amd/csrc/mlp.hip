@@ -513,24 +513,20 @@ __device__ inline float log_f32(double x) {
   return __builtin_isinf(x) ? INFINITY : r;
 }
 
-// atan2(sqrt(y2), x) for y2 >= 0, relative error below 1e-12: the octant's
-// ratio t = min/max, reduced by atan t = pi/4 + atan((t - 1)/(t + 1)) above
-// tan(pi/8) (numerator and denominator, so one reciprocal serves both), then
-// z P(z^2) with the degree-7 polynomial that interpolates atan(z)/z at the
-// Chebyshev nodes of [0, tan^2(pi/8)] (7.6e-13).
-__device__ inline float angle_f32(double y2, double x) {
-  // sqrt(y2) by one step on the reciprocal square root's estimate
+// sqrt(y2) for y2 of up to 2e298 or so, 1e-150 at the least, by one step on the
+// reciprocal square root's estimate.
+__device__ inline double sqrt_newton(double y2) {
   const double c = fmax(y2, 1e-300), h = __builtin_amdgcn_rsq(c), t0 = c * h;
-  double y = fma(0.5 * t0, fma(-t0, h, 1.0), t0), ax = fabs(x);
-  // past the range of the estimates (float64 coordinates beyond about 1e74),
-  // told by the exponents (2e298 and above): infinities count as atan2 counts
-  // them, large finite values are scaled, and a NaN becomes the quotient 0/0
-  const unsigned top = max((unsigned)__double2hiint(y2) & 0x7fffffffu, (unsigned)__double2hiint(x) & 0x7fffffffu);
-  if (__builtin_expect(top >= 0x7de00000u, 0)) {
-    const bool nan = isnan(y2) || isnan(x), yi = isinf(y2), xi = isinf(ax);
-    y = nan ? 0.0 : (yi ? 1.0 : (xi ? 0.0 : y * 0x1p-600));
-    ax = nan ? 0.0 : (xi ? 1.0 : (yi ? 0.0 : ax * 0x1p-600));
-  }
+  return fma(0.5 * t0, fma(-t0, h, 1.0), t0);
+}
+
+// atan2(y, ax) for y, ax >= 0, and pi less that where `neg`; relative error
+// below 1e-12: the octant's ratio t = min/max, reduced by atan t = pi/4 +
+// atan((t - 1)/(t + 1)) above tan(pi/8) (numerator and denominator, so one
+// reciprocal serves both), then z P(z^2) with the degree-7 polynomial that
+// interpolates atan(z)/z at the Chebyshev nodes of [0, tan^2(pi/8)] (7.6e-13).
+// 0 and 0 give NaN.
+__device__ inline float angle_f32(double y, double ax, bool neg) {
   const double mn = fmin(y, ax), mx = fmax(y, ax);
   const bool big = mn > 0.41421356237309505 * mx;
   const double num = big ? mn - mx : mn, den = big ? mn + mx : mx;
@@ -545,7 +541,7 @@ __device__ inline float angle_f32(double y2, double x) {
   q = fma(q, w, in_sgpr(0.9999999999992447));
   double a = fma(z, q, big ? 0.78539816339744831 : 0.0);
   a = y > ax ? 1.5707963267948966 - a : a;
-  return (float)(x < 0.0 ? 3.1415926535897931 - a : a);
+  return (float)(neg ? 3.1415926535897931 - a : a);
 }
 
 struct __attribute__((packed, aligned(4))) Feat3 {
@@ -597,11 +593,37 @@ __global__ __launch_bounds__(256) void k_features(const void* __restrict__ uv, c
     const double a0 = fma(R[0], u1, fma(R[1], v1, R[2])), a1 = fma(R[3], u1, fma(R[4], v1, R[5])),
                  a2 = fma(R[6], u1, fma(R[7], v1, R[8]));
     const double c0 = fma(-a2, v2, a1), c1 = fma(a2, u2, -a0), c2 = fma(a0, v2, -a1 * u2);
-    const double res = fabs(fma(th[0], c0, fma(th[1], c1, th[2] * c2)));
+    double res = fabs(fma(th[0], c0, fma(th[1], c1, th[2] * c2)));
+    const double y2 = fma(c0, c0, fma(c1, c1, c2 * c2)), x = fma(a0, u2, fma(a1, v2, a2));
+    double y = sqrt_newton(y2), ax = fabs(x);
+    // Past the range of the estimates (float64 coordinates beyond about 1e74, or
+    // ones that are not finite, which x then is not either), told by the
+    // exponents (2e298 and above): of finite coordinates infinities count as
+    // atan2 counts them and large values are scaled; otherwise the angle is
+    // NaN, and the residual the form x2~^T (E x1~), whose sums of infinities
+    // the triple product does not have.
+    const unsigned top = max((unsigned)__double2hiint(y2) & 0x7fffffffu, (unsigned)__double2hiint(x) & 0x7fffffffu);
+    if (__builtin_expect(top >= 0x7de00000u, 0)) {
+      const bool fin = isfinite(u1) && isfinite(v1) && isfinite(u2) && isfinite(v2);
+      const bool nan = !fin || isnan(y2) || isnan(x), yi = isinf(y2), xi = isinf(ax);
+      y = nan ? 0.0 : (yi ? 1.0 : (xi ? 0.0 : y * 0x1p-600));
+      ax = nan ? 0.0 : (xi ? 1.0 : (yi ? 0.0 : ax * 0x1p-600));
+      if (!fin) {
+        double e[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const int p = (k + 1) % 3, q = (k + 2) % 3;   // row k of [t_hat]_x R
+          const double E0 = th[p] * R[3 * q] - th[q] * R[3 * p], E1 = th[p] * R[3 * q + 1] - th[q] * R[3 * p + 1],
+                       E2 = th[p] * R[3 * q + 2] - th[q] * R[3 * p + 2];
+          e[k] = E0 * u1 + E1 * v1 + E2;
+        }
+        res = fabs(u2 * e[0] + v2 * e[1] + e[2]);
+      }
+    }
     Feat3 f;
     f.f0 = log_f32(res > delta ? res : delta);
     f.f1 = f1;
-    f.f2 = angle_f32(fma(c0, c0, fma(c1, c1, c2 * c2)), fma(a0, u2, fma(a1, v2, a2)));
+    f.f2 = angle_f32(y, ax, x < 0.0);
     reinterpret_cast<Feat3*>(feats)[m] = f;
   }
 }
