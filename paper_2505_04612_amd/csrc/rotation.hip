@@ -664,7 +664,8 @@ __device__ inline double lz_tridiag(const double* al, const double* be, int m, d
   }
   n2 = wave_sum_d(n2);
   sum = wave_sum_d(sum);
-  const double sc = (sum < 0.0 ? -1.0 : 1.0) / sqrt(n2);
+  // (a matrix that is not finite has no eigenvector: its vector is NaN too)
+  const double sc = isnan(theta) ? theta : (sum < 0.0 ? -1.0 : 1.0) / sqrt(n2);
   __syncthreads();
   for (int i = threadIdx.x; i < m; i += kLzBlock) s[i] *= sc;
   __syncthreads();
