@@ -87,4 +87,5 @@ def test_infinite_coordinates(dtype):
     f0 = np.log(np.where(r > np.float32(1e-4), r, np.float64(np.float32(1e-4))))
     assert np.array_equal(np.isnan(got[:, 2]), any_hit)
     assert np.array_equal(np.isinf(got[:, 0]), np.isinf(f0)) and np.isinf(f0).sum() > 100
-    assert np.all(np.abs(got[:, 0] - f0)[any_hit & np.isfinite(f0)] <= 1e-6)
+    fin = any_hit & np.isfinite(f0)
+    assert np.all(np.abs(got[fin, 0] - f0[fin]) <= 1e-6)
